@@ -904,6 +904,9 @@ int ensure_atoms(cf_ctx *c, int64_t atoms, int np) {
   return CF_OK;
 }
 
+// atoms per pose, rounded up (sizes the per-atom launches)
+int mean_atoms(const cf_pose_batch *b) { return (int)(((int64_t)b->n_atoms + b->n_poses - 1) / b->n_poses); }
+
 int64_t atoms_cap_for(const cf_pose_batch *b, int np) {
   return std::min<int64_t>((int64_t)b->n_atoms, (int64_t)np * CF_MAX_POSE_ATOMS);
 }
@@ -1004,7 +1007,7 @@ int cf_build_graphs(cf_ctx *c, const cf_pose_batch *b, cf_csr *cov, cf_csr *nc, 
     return fail(CF_ERR_INVALID_ARG, "bad CSR arguments");
   if ((rc = ensure(c, c->deg, (size_t)2 * b->n_atoms * sizeof(int32_t)))) return rc;
   if ((rc = ensure(c, c->pose_tot, (size_t)4 * b->n_poses * sizeof(int64_t)))) return rc;
-  CF_HIP(cf::launch_graph(b->atom_off, b->n_atoms, b->xyz, 0, b->n_poses, c->desc.r_cov_u, c->desc.r_nc_u, cov->row_ptr,
+  CF_HIP(cf::launch_graph(b->atom_off, b->n_atoms, b->xyz, 0, b->n_poses, mean_atoms(b), c->desc.r_cov_u, c->desc.r_nc_u, cov->row_ptr,
                           cov->col, cov->capacity, nc->row_ptr, nc->col, nc->capacity, (int32_t *)c->deg.p,
                           (int64_t)b->n_atoms, (int64_t *)c->pose_tot.p, c->status, (hipStream_t)stream));
   return CF_OK;
@@ -1107,7 +1110,7 @@ int cf_score_poses(cf_ctx *c, const cf_pose_batch *b, int G, float *scores, void
     Range rg(c, "cf.graph_sgcnn");
     CF_HIP(hipStreamWaitEvent(s2, c->ev_fork, 0));
     hipEvent_t eg = tbegin(c, s2);
-    CF_HIP(cf::launch_graph(b->atom_off, b->n_atoms, b->xyz, p0, np, c->desc.r_cov_u, c->desc.r_nc_u, (int32_t *)c->cov_row.p,
+    CF_HIP(cf::launch_graph(b->atom_off, b->n_atoms, b->xyz, p0, np, mean_atoms(b), c->desc.r_cov_u, c->desc.r_nc_u, (int32_t *)c->cov_row.p,
                             (int32_t *)c->cov_col.p, acap * 16, (int32_t *)c->nc_row.p, (int32_t *)c->nc_col.p,
                             acap * 96, (int32_t *)c->deg.p, acap, (int64_t *)c->pose_tot.p, c->status, s2));
     // algorithmic bytes: coordinates read once, two row-pointer arrays and 4 B per
@@ -1223,7 +1226,7 @@ int cf_backward(cf_ctx *c, const cf_pose_batch *b, int G, const float *dscore, f
     CF_HIP(cf::launch_splat(b->atom_off, b->n_atoms, b->xyz, b->feat, cen, p0, np, G, c->grid.p, 2, grid_cpad(c),
                             c->splatwork.p, acap, c->status, s));
     if ((rc = run_cnn(c, G, np, (float *)c->cnn_lat.p, s, nullptr, true))) return rc;
-    CF_HIP(cf::launch_graph(b->atom_off, b->n_atoms, b->xyz, p0, np, d.r_cov_u, d.r_nc_u, (int32_t *)c->cov_row.p,
+    CF_HIP(cf::launch_graph(b->atom_off, b->n_atoms, b->xyz, p0, np, mean_atoms(b), d.r_cov_u, d.r_nc_u, (int32_t *)c->cov_row.p,
                             (int32_t *)c->cov_col.p, acap * 16, (int32_t *)c->nc_row.p, (int32_t *)c->nc_col.p,
                             acap * 96, (int32_t *)c->deg.p, acap, (int64_t *)c->pose_tot.p, c->status, s));
     const int32_t *rp[2] = {(int32_t *)c->cov_row.p, (int32_t *)c->nc_row.p};

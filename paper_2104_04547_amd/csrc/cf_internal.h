@@ -69,6 +69,15 @@ __device__ inline void xcd_order(int &x, int &y, int &z) {
   y = l / (gz * gx);
 }
 
+// Blocks of `rows` atoms given to each pose of a batch whose poses have `mean_atoms`
+// atoms on average (host): enough for poses up to twice the mean, and never more than
+// the largest possible pose has.  Workgroups of a larger pose take several blocks.
+inline int pose_blocks(int n_atoms, int mean_atoms, int rows) {
+  const int most = (n_atoms < CF_MAX_POSE_ATOMS ? n_atoms : CF_MAX_POSE_ATOMS);
+  const int want = 2 * mean_atoms < most ? 2 * mean_atoms : most;
+  return want < 1 ? 1 : (want + rows - 1) / rows;
+}
+
 // Zero K steps past the end of the packed tap-pair / tap-quad weights: the conv
 // kernels prefetch weight fragments up to this many steps ahead.
 constexpr int kConvPadSteps = 6;
@@ -107,8 +116,8 @@ int64_t splat_work_bytes(int n_poses, int64_t atoms, int G);
 hipError_t launch_grid_repack(const void *src, int src_bf16, int n_vox, void *dst, int dst_bf16,
                               int cpad, hipStream_t s, int64_t chunk4_vpp = 0);
 
-hipError_t launch_graph(const int32_t *atom_off, int n_atoms, const int32_t *xyz, int p0, int n_poses, int r_cov,
-                        int r_nc, int32_t *cov_row, int32_t *cov_col, int64_t cov_cap, int32_t *nc_row,
+hipError_t launch_graph(const int32_t *atom_off, int n_atoms, const int32_t *xyz, int p0, int n_poses, int mean_atoms,
+                        int r_cov, int r_nc, int32_t *cov_row, int32_t *cov_col, int64_t cov_cap, int32_t *nc_row,
                         int32_t *nc_col, int64_t nc_cap, int32_t *deg_scratch, int64_t n_chunk_cap,
                         int64_t *pose_scratch, int64_t *status, hipStream_t s);
 
