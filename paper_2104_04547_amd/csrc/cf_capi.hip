@@ -1044,7 +1044,7 @@ int cf_sgcnn_fwd(cf_ctx *c, const cf_pose_batch *b, const cf_csr *cov, const cf_
   if ((rc = ensure(c, c->hbuf, (size_t)acap * c->sg_floats * sizeof(float)))) return rc;
   for (int p0 = 0; p0 < b->n_poses; p0 += chunk) {
     const int np = std::min(chunk, b->n_poses - p0);
-    CF_HIP(cf::launch_sgcnn(c->sg, c->bf16, b->atom_off, b->n_atoms, b->feat, b->is_lig, p0, np, cov->row_ptr, cov->col,
+    CF_HIP(cf::launch_sgcnn(c->sg, c->bf16, b->atom_off, b->n_atoms, b->feat, b->is_lig, p0, np, mean_atoms(b), cov->row_ptr, cov->col,
                             cov->capacity, nc->row_ptr, nc->col, nc->capacity, 1, (float *)c->hbuf.p, acap,
                             sg_latent + (size_t)p0 * c->sgw, c->status, s));
   }
@@ -1127,7 +1127,7 @@ int cf_score_poses(cf_ctx *c, const cf_pose_batch *b, int G, float *scores, void
       }
     }
     eg = tbegin(c, s2);
-    CF_HIP(cf::launch_sgcnn(c->sg, c->bf16, b->atom_off, b->n_atoms, b->feat, b->is_lig, p0, np, (int32_t *)c->cov_row.p,
+    CF_HIP(cf::launch_sgcnn(c->sg, c->bf16, b->atom_off, b->n_atoms, b->feat, b->is_lig, p0, np, mean_atoms(b), (int32_t *)c->cov_row.p,
                             (int32_t *)c->cov_col.p, acap * 16, (int32_t *)c->nc_row.p, (int32_t *)c->nc_col.p,
                             acap * 96, 0, (float *)c->hbuf.p, acap, (float *)c->sg_lat.p, c->status, s2));
     tend(c, s2, eg, "sgcnn", atoms * c->sg_flop_atom, atoms * 4.0 * CF_NCH);

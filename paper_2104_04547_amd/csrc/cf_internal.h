@@ -180,10 +180,11 @@ struct SgWeights {
   const bf16_t *ih_hi[2], *ih_lo[2];      // N = 3Hs
   const bf16_t *hh_hi[2], *hh_lo[2];      // N = 3Hs
 };
+// mean_atoms: atoms per pose of the whole batch (splits the launches only).
 // csr_global = 1: rows indexed by global atom id and columns are global ids (the
 // public neighbour-list layout); 0: both are relative to the first atom of pose p0.
 hipError_t launch_sgcnn(const SgWeights &W, int bf16, const int32_t *atom_off, int n_atoms, const float *feat,
-                        const uint8_t *is_lig, int p0, int n_poses, const int32_t *cov_row,
+                        const uint8_t *is_lig, int p0, int n_poses, int mean_atoms, const int32_t *cov_row,
                         const int32_t *cov_col, int64_t cov_cap, const int32_t *nc_row,
                         const int32_t *nc_col, int64_t nc_cap, int csr_global, float *hbuf,
                         int64_t hcap_atoms, float *sg_latent, int64_t *status, hipStream_t s);

@@ -7,13 +7,16 @@
 // state with a gated recurrent unit shared by the rounds of a stage; a gated sum
 // over the ligand atoms ("gather") gives the latent that enters the fusion head.
 //
-// Design: one workgroup per pose (a pose's states, <= 4096 x H floats, stay in
-// L2 between rounds).  Atoms are processed in blocks: the neighbour sums are
-// segmented CSR reductions (consecutive lanes = consecutive features, so a
-// neighbour row is one coalesced read) staged in LDS, then the message and GRU
-// products run on the block.
-//   * plain form: float32 FMAs, weights staged in LDS, each thread owning one
-//     output feature for several atoms;
+// Design: a round is one launch over blocks of a pose's atoms (64 at width 64), so
+// that a lone pose spreads over the chip and a batch's large poses do not outlast
+// the rest; the states of all poses ping-pong between two buffers from launch to
+// launch, and the workgroups of a pose are neighbours on one XCD, under one L2.  (One
+// workgroup per pose walking its blocks round by round took 1.32 ms for one
+// 690-atom pose, 2.9 ms for 200 poses of 200-1500 atoms and 4.8 ms for 33 poses of the
+// staged plain form: its chain of dependent phases was the whole time.  Now 0.24, 0.73
+// and 0.64 ms.)  The neighbour sums are segmented CSR reductions
+// (consecutive lanes = consecutive features, so a neighbour row is one coalesced
+// read) staged in LDS, then the message and GRU products run on the block.
 //   * precision form (H = 32 or 64): the products run on the matrix cores as
 //     v_mfma_f32_32x32x16_bf16 with every float32 operand split into a bfloat16
 //     pair (hi + lo) and three products per term (hi*hi + hi*lo + lo*hi), float32
@@ -21,6 +24,12 @@
 //     ~0.1 pK; the split keeps ~16 mantissa bits.  Each wave owns a 32-atom x
 //     32-feature tile of all six GRU gate products, so the gates, the state
 //     update and the store happen straight from the accumulators.
+//   * plain form: the same on the float32 matrix instruction (32x32x2); width 16,
+//     which has no matrix-core tile, keeps one workgroup per pose with float32 FMAs
+//     and the weights in LDS.
+#include <algorithm>
+#include <utility>
+
 #include "cf_internal.h"
 
 namespace cf {
@@ -28,7 +37,6 @@ namespace cf {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kGather = 8;  // neighbour rows per batch of the neighbour sums
 
 __device__ inline float sigm(float x) { return 1.0f / (1.0f + expf(-x)); }
 
@@ -464,168 +472,192 @@ __device__ void sg_block(const SgWeights &W, int stage, int r, const int32_t *__
     __syncthreads();
 }
 
-// K rounds of one stage at width H (rounds r0 .. r0+K-1 of the weight lists, GRU
-// of stage `stage`) over all the pose's atom blocks; states ping-pong between cur
-// and nxt (row stride H).
-template <int H, bool F32>
-__device__ void sg_rounds(const SgWeights &W, int stage, int r0, int K, const int32_t *__restrict__ rowp,
-                          const int32_t *__restrict__ colp, int64_t cap, int csr_global, int a0, int base,
-                          int64_t lb, int n, float *&cur, float *&nxt, float *lds, int64_t *status) {
-  for (int r = r0; r < r0 + K; ++r) {
-    for (int blk = 0; blk < n; blk += SgTile<H>::BLK)
-      sg_block<H, F32>(W, stage, r, rowp, colp, cap, csr_global, a0, base, lb, n, blk, cur, nxt, lds, status);
-    __threadfence();
-    __syncthreads();
-    float *tmp = cur;
-    cur = nxt;
-    nxt = tmp;
-  }
+// The pose of work item `it` of n_poses * nbx (pose-major, renumbered so that the
+// items of a pose run on one XCD): its first block of atoms, its atom range and its
+// first row lb in the state buffers.  False (nothing to do) for an empty or malformed
+// pose, which is reported when `report` is set.
+__device__ inline bool sg_item(const int32_t *__restrict__ atom_off, int n_atoms, int p0, int nbx, int64_t hcap,
+                               bool report, int &pl, int &b0, int &a0, int &n, int &base, int64_t &lb,
+                               int64_t *status) {
+  int x, y, z;
+  xcd_order(x, y, z);
+  pl = x / nbx;
+  b0 = x % nbx;
+  base = atom_off[p0];
+  int a1;
+  const bool ok = pose_range(atom_off, p0 + pl, n_atoms, a0, a1);
+  n = a1 - a0;
+  lb = (int64_t)a0 - base;
+  const bool bad = !ok || lb < 0 || lb + n > hcap;
+  if (bad && report && b0 == 0 && threadIdx.x == 0) dev_fail(status, kDevBadOffsets);
+  return !bad && n > 0;
 }
+
+constexpr int kEmbedRows = 32;  // atoms per workgroup of the embedding and the covalent gather
 
 template <int H>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_sgcnn_mfma(
-    SgWeights W, const int32_t *__restrict__ atom_off, int n_atoms, const float *__restrict__ feat,
-    const uint8_t *__restrict__ is_lig, int p0, const int32_t *__restrict__ cov_row,
-    const int32_t *__restrict__ cov_col, int64_t cov_cap, const int32_t *__restrict__ nc_row,
-    const int32_t *__restrict__ nc_col, int64_t nc_cap, int csr_global, float *__restrict__ hbuf, int64_t hcap,
-    float *__restrict__ sg_latent, int64_t *__restrict__ status) {
-  // rounds: A | M | Hc; readout (after the rounds): Wg | Wv | red, in the same
-  // space, so that several poses share a CU
+__global__ __launch_bounds__(kThreads) void k_sg_embed(SgWeights W, const int32_t *__restrict__ atom_off, int n_atoms,
+                                                       const float *__restrict__ feat, int p0, int nbx,
+                                                       float *__restrict__ h0, int64_t hcap,
+                                                       int64_t *__restrict__ status) {
+  int pl, b0, a0, n, base;
+  int64_t lb;
+  if (!sg_item(atom_off, n_atoms, p0, nbx, hcap, true, pl, b0, a0, n, base, lb, status)) return;
+  for (int blk = b0 * kEmbedRows; blk < n; blk += nbx * kEmbedRows)
+    sg_embed<H>(W, feat, a0 + blk, min(kEmbedRows, n - blk), lb + blk, h0);
+}
+
+// One round: the states of cur advanced into nxt.
+template <int H, bool F32>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(H == 128 || F32 ? 2 : 3))) void k_sg_round(
+    SgWeights W, int stage, int r, const int32_t *__restrict__ atom_off, int n_atoms, int p0, int nbx,
+    const int32_t *__restrict__ rowp, const int32_t *__restrict__ colp, int64_t cap, int csr_global,
+    const float *__restrict__ cur, float *__restrict__ nxt, int64_t hcap, int64_t *__restrict__ status) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
-  static_assert((H + CF_NCH) * H + H * H + kThreads <= SgTile<H>::FLOATS, "readout staging must fit");
-  const int t = threadIdx.x;
+  int pl, b0, a0, n, base;
+  int64_t lb;
+  if (!sg_item(atom_off, n_atoms, p0, nbx, hcap, false, pl, b0, a0, n, base, lb, status)) return;
+  for (int blk = b0 * SgTile<H>::BLK; blk < n; blk += nbx * SgTile<H>::BLK)
+    sg_block<H, F32>(W, stage, r, rowp, colp, cap, csr_global, a0, base, lb, n, blk, cur, nxt, lds, status);
+}
+
+// ---- PotentialNet staging: the covalent stage at width HC closes with a per-atom
+// gather, g_i = sigmoid(W_g1 [h_i; x_i] + b) * (W_v1 h_i + b_v1), and a linear
+// embedding to width HN, h_i = W_e2 g_i + b; the readout's gate reads [h; g].  Small
+// per-atom work: float32 FMAs with the weights read through the caches. ----
+template <int HC, int HN>
+__global__ __launch_bounds__(kThreads) void k_sg_mid(SgWeights W, const int32_t *__restrict__ atom_off, int n_atoms,
+                                                     const float *__restrict__ feat, int p0, int nbx,
+                                                     const float *__restrict__ cur, float *__restrict__ gb,
+                                                     float *__restrict__ h2, int64_t hcap,
+                                                     int64_t *__restrict__ status) {
+  __shared__ float g[kEmbedRows * HC];
+  int pl, b0, a0, n, base;
+  int64_t lb;
+  if (!sg_item(atom_off, n_atoms, p0, nbx, hcap, false, pl, b0, a0, n, base, lb, status)) return;
+  for (int blk = b0 * kEmbedRows; blk < n; blk += nbx * kEmbedRows) {
+    const int nr = min(kEmbedRows, n - blk);
+    for (int e = threadIdx.x; e < nr * HC; e += kThreads) {
+      const int i = e / HC, o = e % HC;
+      const float *hi = cur + (lb + blk + i) * HC;
+      const float *xi = feat + (int64_t)(a0 + blk + i) * CF_NCH;
+      float gt = W.mid_gate_b[o], vl = W.mid_val_b[o];
+#pragma unroll 8
+      for (int k = 0; k < HC; ++k) {
+        const float hk = hi[k];
+        gt += W.mid_gate_wT[k * HC + o] * hk;
+        vl += W.mid_val_wT[k * HC + o] * hk;
+      }
+      for (int c = 0; c < CF_NCH; ++c) gt += W.mid_gate_wT[(HC + c) * HC + o] * xi[c];
+      const float gv = sigm(gt) * vl;
+      gb[(lb + blk + i) * HC + o] = gv;
+      g[e] = gv;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < nr * HN; e += kThreads) {
+      const int i = e / HN, o = e % HN;
+      float v = W.embed2_b[o];
+#pragma unroll 8
+      for (int k = 0; k < HC; ++k) v += W.embed2_wT[k * HN + o] * g[i * HC + k];
+      h2[(lb + blk + i) * HN + o] = v;
+    }
+    __syncthreads();
+  }
+}
+
+// Gated readout, one workgroup per pose: s = sum over ligand atoms of
+// sigmoid(W_g [h; u] + b_g) * (W_v h + b_v), u the atom's U raw features (row stride
+// U) or its covalent gather.  The threads form G groups of H; group g sums the
+// ligand atoms i = g mod G in ascending order, then the groups are added in order.  The
+// ligand atoms are listed per group first (a pose has a few dozen in hundreds), and a
+// thread takes four of its group's atoms together, so that a weight is read once for
+// four of them.
+template <int H, int U>
+__global__ __launch_bounds__(kThreads) void k_sg_readout(SgWeights W, const int32_t *__restrict__ atom_off,
+                                                         int n_atoms, const float *__restrict__ cur,
+                                                         const float *__restrict__ u, int u_local,
+                                                         const uint8_t *__restrict__ is_lig, int p0, int64_t hcap,
+                                                         float *__restrict__ sg_latent) {
+  constexpr int G = kThreads / H, NA = 4, WAVES = kThreads / 64;
+  static_assert(64 % G == 0, "a wave holds whole turns of the groups");
+  __shared__ uint16_t list[G][CF_MAX_POSE_ATOMS / G];
+  __shared__ int cnt[WAVES][G];
+  __shared__ float red[kThreads];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int pl = blockIdx.x;
   const int base = atom_off[p0];
+  float *out = sg_latent + (int64_t)pl * H;
   int a0, a1;
   const bool ok = pose_range(atom_off, p0 + pl, n_atoms, a0, a1);
   const int n = a1 - a0;
   const int64_t lb = (int64_t)a0 - base;
   if (!ok || n <= 0 || lb < 0 || lb + n > hcap) {
-    if (t == 0 && (!ok || lb < 0 || lb + n > hcap)) dev_fail(status, kDevBadOffsets);
-    if (t < H) sg_latent[(int64_t)pl * H + t] = 0.0f;
+    if (t < H) out[t] = 0.0f;
     return;
   }
-  float *cur = hbuf, *nxt = hbuf + hcap * H;
-  sg_embed<H>(W, feat, a0, n, lb, cur);
-  __threadfence();
-  __syncthreads();
-  sg_rounds<H, false>(W, 0, 0, W.K_c, cov_row, cov_col, cov_cap, csr_global, a0, base, lb, n, cur, nxt, lds, status);
-  sg_rounds<H, false>(W, 1, W.K_c, W.K_n, nc_row, nc_col, nc_cap, csr_global, a0, base, lb, n, cur, nxt, lds,
-                      status);
-  float *Wg = lds, *Wv = lds + (H + CF_NCH) * H, *red = Wv + H * H;
-  for (int e = t; e < (H + CF_NCH) * H; e += kThreads) Wg[e] = W.gate_wT[e];
-  for (int e = t; e < H * H; e += kThreads) Wv[e] = W.val_wT[e];
-  __syncthreads();
-  sg_readout<H>(W, cur, feat, is_lig, a0, n, lb, Wg, Wv, red, sg_latent + (int64_t)pl * H);
-}
-
-// ---- PotentialNet staging: covalent stage at width HC, per-atom gather,
-// linear embedding to width HN, non-covalent stage at HN, readout over ligand
-// atoms whose gate reads [h; g].  The per-atom work outside the rounds is small
-// (float32 FMAs with the weights read through the caches). ----
-
-// g_i = sigmoid(W_g1 [h_i; x_i] + b) * (W_v1 h_i + b), width HC
-template <int HC>
-__device__ void sg_mid_gather(const SgWeights &W, const float *__restrict__ cur, const float *__restrict__ feat,
-                              int a0, int n, int64_t lb, float *__restrict__ gb) {
-  for (int e = threadIdx.x; e < n * HC; e += kThreads) {
-    const int i = e / HC, o = e % HC;
-    const float *hi = cur + (lb + i) * HC;
-    const float *xi = feat + (int64_t)(a0 + i) * CF_NCH;
-    float gt = W.mid_gate_b[o], vl = W.mid_val_b[o];
-    for (int k = 0; k < HC; ++k) {
-      const float hk = hi[k];
-      gt += W.mid_gate_wT[k * HC + o] * hk;
-      vl += W.mid_val_wT[k * HC + o] * hk;
+  unsigned long long turn = 0;
+#pragma unroll
+  for (int q = 0; q < 64; q += G) turn |= 1ull << q;
+  const int lg = lane % G;
+  int run = 0;  // atoms listed so far for group lg
+  for (int c0 = 0; c0 < n; c0 += kThreads) {
+    const int i = c0 + t;
+    const bool lig = i < n && is_lig[a0 + i];
+    const unsigned long long m = __ballot(lig) & (turn << lg);
+    if (lane < G) cnt[wave][lane] = __popcll(m);
+    __syncthreads();
+    int at = run;
+    for (int w = 0; w < WAVES; ++w) {
+      const int k = cnt[w][lg];
+      if (w < wave) at += k;
+      run += k;
     }
-    for (int c = 0; c < CF_NCH; ++c) gt += W.mid_gate_wT[(HC + c) * HC + o] * xi[c];
-    gb[(lb + i) * HC + o] = sigm(gt) * vl;
+    if (lig) list[lg][at + __popcll(m & ((1ull << lane) - 1))] = (uint16_t)i;
+    __syncthreads();
   }
-}
-
-// h_i = W_e2 g_i + b, width HN
-template <int HC, int HN>
-__device__ void sg_embed2(const SgWeights &W, const float *__restrict__ gb, int n, int64_t lb, float *__restrict__ h) {
-  for (int e = threadIdx.x; e < n * HN; e += kThreads) {
-    const int i = e / HN, o = e % HN;
-    const float *gi = gb + (lb + i) * HC;
-    float v = W.embed2_b[o];
-    for (int k = 0; k < HC; ++k) v += W.embed2_wT[k * HN + o] * gi[k];
-    h[(lb + i) * HN + o] = v;
-  }
-}
-
-// s = sum over ligand atoms of sigmoid(W_g [h; g] + b_g) * (W_v h + b_v), width HN
-template <int HC, int HN>
-__device__ void sg_readout_staged(const SgWeights &W, const float *__restrict__ cur, const float *__restrict__ gb,
-                                  const uint8_t *__restrict__ is_lig, int a0, int n, int64_t lb, float *red,
-                                  float *out) {
-  constexpr int G = kThreads / HN;
-  const int o = threadIdx.x % HN, g = threadIdx.x / HN;
+  if (t < G) cnt[0][t] = run;  // thread t < G holds the total of group t
+  __syncthreads();
+  const int o = t % H, g = t / H;
+  const int total = cnt[0][g];
   float acc = 0.0f;
-  for (int i = g; i < n; i += G) {
-    if (!is_lig[a0 + i]) continue;
-    const float *hi = cur + (lb + i) * HN;
-    const float *gi = gb + (lb + i) * HC;
-    float gt = W.gate_b[o], vl = W.val_b[o];
-    for (int k = 0; k < HN; ++k) {
-      const float hk = hi[k];
-      gt += W.gate_wT[k * HN + o] * hk;
-      vl += W.val_wT[k * HN + o] * hk;
+  for (int q0 = 0; q0 < total; q0 += NA) {
+    const float *hi[NA], *ui[NA];
+    float gt[NA], vl[NA];
+#pragma unroll
+    for (int q = 0; q < NA; ++q) {
+      const int i = list[g][min(q0 + q, total - 1)];
+      hi[q] = cur + (lb + i) * H;
+      ui[q] = u + (u_local ? lb + i : (int64_t)(a0 + i)) * U;
+      gt[q] = W.gate_b[o];
+      vl[q] = W.val_b[o];
     }
-    for (int k = 0; k < HC; ++k) gt += W.gate_wT[(HN + k) * HN + o] * gi[k];
-    acc += sigm(gt) * vl;
+#pragma unroll 8
+    for (int k = 0; k < H; ++k) {
+      const float wg = W.gate_wT[k * H + o], wv = W.val_wT[k * H + o];
+#pragma unroll
+      for (int q = 0; q < NA; ++q) {
+        const float hk = hi[q][k];
+        gt[q] += wg * hk;
+        vl[q] += wv * hk;
+      }
+    }
+#pragma unroll 8
+    for (int c = 0; c < U; ++c) {
+      const float wg = W.gate_wT[(H + c) * H + o];
+#pragma unroll
+      for (int q = 0; q < NA; ++q) gt[q] += wg * ui[q][c];
+    }
+#pragma unroll
+    for (int q = 0; q < NA; ++q)
+      if (q0 + q < total) acc += sigm(gt[q]) * vl[q];
   }
-  red[g * HN + o] = acc;
+  red[t] = acc;
   __syncthreads();
-  if ((int)threadIdx.x < HN) {
+  if (t < H) {
     float s = 0.0f;
-    for (int q = 0; q < G; ++q) s += red[q * HN + threadIdx.x];
-    out[threadIdx.x] = s;
+    for (int q = 0; q < G; ++q) s += red[q * H + t];
+    out[t] = s;
   }
-}
-
-template <int HC, int HN, bool F32>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_sgcnn_staged(
-    SgWeights W, const int32_t *__restrict__ atom_off, int n_atoms, const float *__restrict__ feat,
-    const uint8_t *__restrict__ is_lig, int p0, const int32_t *__restrict__ cov_row,
-    const int32_t *__restrict__ cov_col, int64_t cov_cap, const int32_t *__restrict__ nc_row,
-    const int32_t *__restrict__ nc_col, int64_t nc_cap, int csr_global, float *__restrict__ hbuf, int64_t hcap,
-    float *__restrict__ sg_latent, int64_t *__restrict__ status) {
-  extern __shared__ __attribute__((aligned(16))) float lds[];
-  static_assert(kThreads % HN == 0 && HC <= HN, "stage widths");
-  const int t = threadIdx.x;
-  const int pl = blockIdx.x;
-  const int base = atom_off[p0];
-  int a0, a1;
-  const bool ok = pose_range(atom_off, p0 + pl, n_atoms, a0, a1);
-  const int n = a1 - a0;
-  const int64_t lb = (int64_t)a0 - base;
-  if (!ok || n <= 0 || lb < 0 || lb + n > hcap) {
-    if (t == 0 && (!ok || lb < 0 || lb + n > hcap)) dev_fail(status, kDevBadOffsets);
-    if (t < HN) sg_latent[(int64_t)pl * HN + t] = 0.0f;
-    return;
-  }
-  // Each stage has its own pair of state buffers indexed at its own row stride:
-  // the workgroups of a launch run different poses at different stages at the
-  // same time, so one buffer indexed at two strides would let a pose's wide rows
-  // overwrite another pose's narrow ones.  Layout (floats): covalent states
-  // 2 x [hcap][HC], covalent gather [hcap][HC], non-covalent states 2 x [hcap][HN].
-  float *cur = hbuf, *nxt = hbuf + hcap * HC, *gb = hbuf + 2 * hcap * HC;
-  float *cur2 = gb + hcap * HC, *nxt2 = cur2 + hcap * HN;
-  sg_embed<HC>(W, feat, a0, n, lb, cur);
-  __threadfence();
-  __syncthreads();
-  sg_rounds<HC, F32>(W, 0, 0, W.K_c, cov_row, cov_col, cov_cap, csr_global, a0, base, lb, n, cur, nxt, lds, status);
-  sg_mid_gather<HC>(W, cur, feat, a0, n, lb, gb);
-  __threadfence();
-  __syncthreads();
-  sg_embed2<HC, HN>(W, gb, n, lb, cur2);
-  __threadfence();
-  __syncthreads();
-  sg_rounds<HN, F32>(W, 1, W.K_c, W.K_n, nc_row, nc_col, nc_cap, csr_global, a0, base, lb, n, cur2, nxt2, lds,
-                     status);
-  sg_readout_staged<HC, HN>(W, cur2, gb, is_lig, a0, n, lb, lds, sg_latent + (int64_t)pl * HN);
 }
 
 template <typename K>
@@ -634,65 +666,90 @@ void set_lds_attr(K kernel, size_t lds) {
                             (int)lds);
 }
 
-template <int H>
-hipError_t launch_h(const SgWeights &W, int mfma, const int32_t *atom_off, int n_atoms, const float *feat,
-                    const uint8_t *is_lig, int p0, int n_poses, const int32_t *cov_row, const int32_t *cov_col,
-                    int64_t cov_cap, const int32_t *nc_row, const int32_t *nc_col, int64_t nc_cap, int csr_global,
-                    float *hbuf, int64_t hcap, float *sg_latent, int64_t *status, hipStream_t s) {
-  static_assert((H + CF_NCH) * H <= 3 * H * H, "readout weights must fit the staging area");
-  if constexpr (H >= 32) {
-    if (mfma) {
-      const size_t lds = sizeof(float) * SgTile<H>::FLOATS;
-      static bool attr = false;
-      if (!attr) {
-        set_lds_attr(&k_sgcnn_mfma<H>, lds);
-        attr = true;
-      }
-      hipLaunchKernelGGL((k_sgcnn_mfma<H>), dim3(n_poses), dim3(kThreads), lds, s, W, atom_off, n_atoms, feat,
-                         is_lig, p0, cov_row, cov_col, cov_cap, nc_row, nc_col, nc_cap, csr_global, hbuf, hcap,
-                         sg_latent, status);
-      return hipGetLastError();
-    }
-  }
-  const size_t lds = sizeof(SgShared<H>);
+// arguments of one SG-CNN call
+struct SgCall {
+  const int32_t *atom_off;
+  int n_atoms;
+  const float *feat;
+  const uint8_t *is_lig;
+  int p0, n_poses, mean_atoms;
+  const int32_t *row[2], *col[2];  // covalent, non-covalent
+  int64_t cap[2];
+  int csr_global;
+  float *hbuf;
+  int64_t hcap;
+  float *latent;
+  int64_t *status;
+};
+
+// rounds r0 .. r0 + K - 1 of a stage; cur and nxt are swapped after each
+template <int H, bool F32>
+hipError_t launch_rounds(const SgWeights &W, const SgCall &c, int stage, int r0, int K, float *&cur, float *&nxt,
+                         hipStream_t s) {
+  const size_t lds = sizeof(float) * SgTile<H>::FLOATS;
   static bool attr = false;
   if (!attr) {
-    set_lds_attr(&k_sgcnn_f32<H>, lds);
+    set_lds_attr(&k_sg_round<H, F32>, lds);
     attr = true;
   }
-  hipLaunchKernelGGL((k_sgcnn_f32<H>), dim3(n_poses), dim3(kThreads), lds, s, W, atom_off, n_atoms, feat, is_lig,
-                     p0, cov_row, cov_col, cov_cap, nc_row, nc_col, nc_cap, csr_global, hbuf, hcap, sg_latent,
-                     status);
+  const int nbx = pose_blocks(c.n_atoms, c.mean_atoms, SgTile<H>::BLK);
+  for (int r = r0; r < r0 + K; ++r) {
+    hipLaunchKernelGGL((k_sg_round<H, F32>), dim3((unsigned)c.n_poses * nbx), dim3(kThreads), lds, s, W, stage, r,
+                       c.atom_off, c.n_atoms, c.p0, nbx, c.row[stage], c.col[stage], c.cap[stage], c.csr_global, cur,
+                       nxt, c.hcap, c.status);
+    std::swap(cur, nxt);
+  }
   return hipGetLastError();
 }
 
-template <int HC, int HN>
-hipError_t launch_staged(const SgWeights &W, int bf16, const int32_t *atom_off, int n_atoms, const float *feat,
-                         const uint8_t *is_lig, int p0, int n_poses, const int32_t *cov_row, const int32_t *cov_col,
-                         int64_t cov_cap, const int32_t *nc_row, const int32_t *nc_col, int64_t nc_cap,
-                         int csr_global, float *hbuf, int64_t hcap, float *sg_latent, int64_t *status,
-                         hipStream_t s) {
-  constexpr int fl = SgTile<HC>::FLOATS > SgTile<HN>::FLOATS ? SgTile<HC>::FLOATS : SgTile<HN>::FLOATS;
-  const size_t lds = sizeof(float) * (fl > kThreads ? fl : kThreads);
-  if (bf16) {
-    static bool attr = false;
-    if (!attr) {
-      set_lds_attr(&k_sgcnn_staged<HC, HN, false>, lds);
-      attr = true;
-    }
-    hipLaunchKernelGGL((k_sgcnn_staged<HC, HN, false>), dim3(n_poses), dim3(kThreads), lds, s, W, atom_off,
-                       n_atoms, feat, is_lig, p0, cov_row, cov_col, cov_cap, nc_row, nc_col, nc_cap, csr_global,
-                       hbuf, hcap, sg_latent, status);
-  } else {
-    static bool attr = false;
-    if (!attr) {
-      set_lds_attr(&k_sgcnn_staged<HC, HN, true>, lds);
-      attr = true;
-    }
-    hipLaunchKernelGGL((k_sgcnn_staged<HC, HN, true>), dim3(n_poses), dim3(kThreads), lds, s, W, atom_off,
-                       n_atoms, feat, is_lig, p0, cov_row, cov_col, cov_cap, nc_row, nc_col, nc_cap, csr_global,
-                       hbuf, hcap, sg_latent, status);
-  }
+template <int H>
+hipError_t launch_embed(const SgWeights &W, const SgCall &c, float *h0, hipStream_t s) {
+  const int nbx = pose_blocks(c.n_atoms, c.mean_atoms, kEmbedRows);
+  hipLaunchKernelGGL(k_sg_embed<H>, dim3((unsigned)c.n_poses * nbx), dim3(kThreads), 0, s, W, c.atom_off, c.n_atoms,
+                     c.feat, c.p0, nbx, h0, c.hcap, c.status);
+  return hipGetLastError();
+}
+
+template <int H, bool F32>
+hipError_t launch_flat(const SgWeights &W, const SgCall &c, hipStream_t s) {
+  float *cur = c.hbuf, *nxt = c.hbuf + c.hcap * H;
+  hipError_t e = launch_embed<H>(W, c, cur, s);
+  if (e == hipSuccess) e = launch_rounds<H, F32>(W, c, 0, 0, W.K_c, cur, nxt, s);
+  if (e == hipSuccess) e = launch_rounds<H, F32>(W, c, 1, W.K_c, W.K_n, cur, nxt, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_sg_readout<H, CF_NCH>), dim3(c.n_poses), dim3(kThreads), 0, s, W, c.atom_off, c.n_atoms, cur,
+                     c.feat, 0, c.is_lig, c.p0, c.hcap, c.latent);
+  return hipGetLastError();
+}
+
+// Each stage has its own pair of state buffers at its own row stride.  Layout
+// (floats): covalent states 2 x [hcap][HC], covalent gather [hcap][HC],
+// non-covalent states 2 x [hcap][HN].
+template <int HC, int HN, bool F32>
+hipError_t launch_staged(const SgWeights &W, const SgCall &c, hipStream_t s) {
+  float *cur = c.hbuf, *nxt = c.hbuf + c.hcap * HC, *gb = c.hbuf + 2 * c.hcap * HC;
+  float *cur2 = gb + c.hcap * HC, *nxt2 = cur2 + c.hcap * HN;
+  hipError_t e = launch_embed<HC>(W, c, cur, s);
+  if (e == hipSuccess) e = launch_rounds<HC, F32>(W, c, 0, 0, W.K_c, cur, nxt, s);
+  if (e != hipSuccess) return e;
+  const int nbx = pose_blocks(c.n_atoms, c.mean_atoms, kEmbedRows);
+  hipLaunchKernelGGL((k_sg_mid<HC, HN>), dim3((unsigned)c.n_poses * nbx), dim3(kThreads), 0, s, W, c.atom_off,
+                     c.n_atoms, c.feat, c.p0, nbx, cur, gb, cur2, c.hcap, c.status);
+  e = launch_rounds<HN, F32>(W, c, 1, W.K_c, W.K_n, cur2, nxt2, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_sg_readout<HN, HC>), dim3(c.n_poses), dim3(kThreads), 0, s, W, c.atom_off, c.n_atoms, cur2, gb,
+                     1, c.is_lig, c.p0, c.hcap, c.latent);
+  return hipGetLastError();
+}
+
+// width 16: one workgroup per pose
+hipError_t launch_h16(const SgWeights &W, const SgCall &c, hipStream_t s) {
+  constexpr int H = 16;
+  static_assert((H + CF_NCH) * H <= 3 * H * H, "readout weights must fit the staging area");
+  const size_t lds = sizeof(SgShared<H>);
+  hipLaunchKernelGGL((k_sgcnn_f32<H>), dim3(c.n_poses), dim3(kThreads), lds, s, W, c.atom_off, c.n_atoms, c.feat,
+                     c.is_lig, c.p0, c.row[0], c.col[0], c.cap[0], c.row[1], c.col[1], c.cap[1], c.csr_global, c.hbuf,
+                     c.hcap, c.latent, c.status);
   return hipGetLastError();
 }
 
@@ -704,32 +761,29 @@ bool sgcnn_staged_supported(int hc, int hn) {
 }
 
 hipError_t launch_sgcnn(const SgWeights &W, int bf16, const int32_t *atom_off, int n_atoms, const float *feat,
-                        const uint8_t *is_lig, int p0, int n_poses, const int32_t *cov_row,
+                        const uint8_t *is_lig, int p0, int n_poses, int mean_atoms, const int32_t *cov_row,
                         const int32_t *cov_col, int64_t cov_cap, const int32_t *nc_row,
                         const int32_t *nc_col, int64_t nc_cap, int csr_global, float *hbuf,
                         int64_t hcap_atoms, float *sg_latent, int64_t *status, hipStream_t s) {
   if (n_poses <= 0) return hipSuccess;
+  const SgCall c{atom_off, n_atoms, feat,       is_lig,     p0,   n_poses,    mean_atoms, {cov_row, nc_row}, {cov_col, nc_col},
+                 {cov_cap, nc_cap}, csr_global, hbuf, hcap_atoms, sg_latent,  status};
+  // the split-bfloat16 products need the split weight copies (precision form, H >= 32)
+  const bool split = bf16 && W.msg_hi[0] != nullptr;
   if (W.staged) {
-    // the precision form needs the split-bfloat16 weight copies
-    const int split = bf16 && W.msg_hi[0] != nullptr;
     if (bf16 && !split) return hipErrorInvalidValue;
-#define CF_ST(HC, HN)                                                                                             if (W.H == HC && W.H2 == HN)                                                                                      return launch_staged<HC, HN>(W, split, atom_off, n_atoms, feat, is_lig, p0, n_poses, cov_row, cov_col,                                       cov_cap, nc_row, nc_col, nc_cap, csr_global, hbuf, hcap_atoms, sg_latent, status, s);
+#define CF_ST(HC, HN)                                                                            \
+  if (W.H == HC && W.H2 == HN)                                                                   \
+    return split ? launch_staged<HC, HN, false>(W, c, s) : launch_staged<HC, HN, true>(W, c, s);
     CF_ST(32, 64)
     CF_ST(32, 128)
     CF_ST(64, 128)
 #undef CF_ST
     return hipErrorInvalidValue;
   }
-  // the matrix-core path needs the split-bfloat16 weight copies (precision form, H >= 32)
-  const int mfma = bf16 && W.msg_hi[0] != nullptr;
-#define CF_SG(HH)                                                                                              \
-  if (W.H == HH)                                                                                               \
-    return launch_h<HH>(W, mfma, atom_off, n_atoms, feat, is_lig, p0, n_poses, cov_row, cov_col, cov_cap,      \
-                        nc_row, nc_col, nc_cap, csr_global, hbuf, hcap_atoms, sg_latent, status, s);
-  CF_SG(16)
-  CF_SG(32)
-  CF_SG(64)
-#undef CF_SG
+  if (W.H == 16) return launch_h16(W, c, s);
+  if (W.H == 32) return split ? launch_flat<32, false>(W, c, s) : launch_flat<32, true>(W, c, s);
+  if (W.H == 64) return split ? launch_flat<64, false>(W, c, s) : launch_flat<64, true>(W, c, s);
   return hipErrorInvalidValue;
 }
 
