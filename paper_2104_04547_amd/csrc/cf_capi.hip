@@ -10,6 +10,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -111,6 +112,7 @@ struct cf_ctx {
   DevBuf splatwork;                        // per-atom normalisers and per-tile atom lists
   DevBuf convwork;          // scratch of the frequency-domain conv (spectra)
   std::map<int, std::vector<int>> variants;  // per G
+  std::set<int> pinned;                      // G whose variants the caller set: run exactly those
 };
 
 namespace {
@@ -338,6 +340,7 @@ int run_cnn(cf_ctx *c, int G, int np, float *cnn_lat, hipStream_t s, hipEvent_t 
   std::vector<int> var;
   int rc = variants_for(c, G, var);
   if (rc) return rc;
+  const bool fit = c->pinned.count(G) == 0;
   {
     int64_t work = 0;
     int D = G;
@@ -402,7 +405,7 @@ int run_cnn(cf_ctx *c, int G, int np, float *cnn_lat, hipStream_t s, hipEvent_t 
       continue;
     }
     hipEvent_t e = tbegin(c, s);
-    CF_HIP(cf::launch_conv(var[i], L, c->bf16, t[i], res, c->act[i].p, np, D, c->convwork.p, s));
+    CF_HIP(cf::launch_conv(var[i], L, c->bf16, t[i], res, c->act[i].p, np, D, c->convwork.p, s, fit));
     if (e) {
       const double vox = (double)Do * Do * Do * np;
       const double flop = 2.0 * L.cin * L.cout * L.k * L.k * L.k * vox;
@@ -1474,6 +1477,7 @@ int cf_set_conv_variants(cf_ctx *c, int G, const int32_t *variants, int32_t n_la
     if (D < 1) return fail(CF_ERR_UNSUPPORTED, "grid too small for the conv stack");
   }
   c->variants[G] = v;
+  c->pinned.insert(G);
   return CF_OK;
 }
 
@@ -1546,6 +1550,7 @@ int cf_autotune(cf_ctx *c, int G, int32_t n_poses, void *stream) {
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   c->variants[G] = best;
+  c->pinned.erase(G);
   return CF_OK;
 }
 

@@ -323,7 +323,15 @@ struct Conv8Cfg {
   // epilogue: output rows go through LDS in groups of MBG 32-row blocks per row group
   static constexpr int MBG = (NWM * 32 * NT * 2 * MB <= HALO) ? MB : ((NWM * 32 * NT * 2 * 2 <= HALO && MB % 2 == 0) ? 2 : 1);
   static constexpr int EPI = NWM * 32 * MBG * NT * 2;
-  static constexpr int LDS = HALO > EPI ? HALO : EPI;
+  // Fine tiles (one or two 32 x 32 blocks per wave): a pair has 32 or 64 MFMA cycles, less
+  // than the scalar arithmetic of its tap offsets (~60 instructions, 230 cycles a pair
+  // measured), so those come from a table in LDS: 16-bit counts of 16 bytes, [K half][entry],
+  // entry p + 5 for pair p, read eight entries at a time a group ahead.
+  static constexpr int BLOCKS = MB * NB;
+  static constexpr bool FINE = BLOCKS <= 2 && PP == 1;
+  static constexpr int ENT = (PAIRS + 5 + 32 + 7) / 8 * 8;
+  static constexpr int TAB = FINE ? 2 * ENT * 2 : 0;
+  static constexpr int LDS = TAB + (HALO > EPI ? HALO : EPI);
   // Waves per SIMD the tile allows: a halo above half the LDS leaves one
   // workgroup per CU, so a four-wave workgroup owns its SIMDs' whole register file
   // (512 per lane); six-wave workgroups run two per CU (three waves per SIMD).
@@ -334,6 +342,20 @@ struct Conv8Cfg {
   static constexpr int NV1 = HZ * HY * HX, HITER = (PP * NV1 + NW * 64 - 1) / (NW * 64);
   static constexpr int HB_MAX = WPE == 1 ? 40 : (MB * NB <= 4 ? 16 : 6);
   static constexpr int HB = HITER < HB_MAX ? HITER : HB_MAX;
+  // Software pipeline of the pair walk: weight fragments PF pairs ahead, row fragments
+  // AD - 1 pairs ahead (PF a multiple of AD).  Several poses per workgroup mean one
+  // workgroup per CU and weights beyond L2 (the 64 -> 128 stride-2 layer): six pairs
+  // ahead there (5 % faster than four; eight spill at 256 registers).  A wave of one or
+  // two 32 x 32 blocks has 32 or 64 MFMA cycles per pair to cover an LDS and an L2
+  // round trip: deeper rings, in the registers that the small accumulator leaves.
+  static constexpr int AD = FINE ? 4 : 2;
+  // fine tiles keep each thread's halo addresses in registers for all chunks and, where
+  // the voxels themselves fit too, load the next chunk's during the walk of this one
+  static constexpr bool AHEAD = FINE && HITER <= 9;
+  static constexpr int PF = PP > 1 ? 6 : BLOCKS == 1 ? 16 : BLOCKS == 2 ? 8 : ((NB <= 2 && KS > 3) ? 4 : 2);
+  static_assert(PF % AD == 0 && (!FINE || PF % 8 == 0), "the unrolled walk indexes the rings at compile time");
+  static_assert(!FINE || HALO / 16 < 65536, "16-bit table entries");
+  static constexpr int WGCU = (163840 / LDS < WPE * 4 / NW ? 163840 / LDS : WPE * 4 / NW) < 1 ? 1 : (163840 / LDS < WPE * 4 / NW ? 163840 / LDS : WPE * 4 / NW);
   static_assert(NW % WN == 0 && NT % (32 * WN) == 0, "waves split the columns in 32-column blocks");
   static_assert(WM % 32 == 0, "rows per wave must be a multiple of 32");
   static_assert(LDS <= 163840, "halo exceeds LDS");
@@ -361,9 +383,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(Conv8Cf
                                                     int nchunks, int cout_pad32, int cout, int cout_store, int nty,
                                                     int ntx, int wbytes) {
   using C = Conv8Cfg<KS, S, TZ, TY, TX, NW, NT, WN, PP>;
-  __shared__ __attribute__((aligned(16))) char lds[C::LDS];
+  __shared__ __attribute__((aligned(16))) char lds_all[C::LDS];
+  char *lds = lds_all + C::TAB;  // halo; epilogue rows
   int tile, pblk, nblk;
-  xcd_order(tile, pblk, nblk);
+  if constexpr (C::FINE)
+    xcd_order_by_z(tile, pblk, nblk);
+  else
+    xcd_order(tile, pblk, nblk);
   const int pose0 = pblk * PP;
   const int n0 = nblk * NT;
   const int tz0 = (tile / (nty * ntx)) * TZ, ty0 = ((tile / ntx) % nty) * TY, tx0 = (tile % ntx) * TX;
@@ -418,47 +444,106 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(Conv8Cf
     const int t1 = (2 * p + 1 < C::TAPS) ? tapoff(ez, ey, ex) : t0;
     return khalf ? t1 : t0;
   };
-  // weight prefetch distance in pairs, even (the row fragments ping-pong inside
-  // the unrolled pair loop); the packed weights carry kConvPadSteps zero pairs past
-  // the end.  Several poses per workgroup means one workgroup per CU and weights
-  // beyond L2 (the 64 -> 128 stride-2 layer): six pairs ahead there (5 % faster
-  // than four; eight spill at 256 registers)
-  constexpr int kPF = PP > 1 ? 6 : ((C::NB <= 2 && KS > 3) ? 4 : 2);
-  static_assert(kPF <= kConvPadSteps, "prefetch past the weight padding");
+  // the rings read past the last pair: zero weights of the padding, or zeros from
+  // beyond the buffer; neither reaches an MFMA
+  constexpr int kPF = C::PF, AD = C::AD;
+  uint16_t *tab = reinterpret_cast<uint16_t *>(lds_all);
+  if constexpr (C::FINE) {
+    for (int e = threadIdx.x; e < 2 * C::ENT; e += NTH) {
+      const int p = e % C::ENT - 5, t = 2 * p + e / C::ENT;
+      // past the last tap (zero weights): the pair's first tap; past the last pair: offset 0
+      const int u = p < 0 || p >= C::PAIRS ? 0 : t < C::TAPS ? t : t - 1;
+      tab[e] = (uint16_t)(tapoff(u / (KS * KS), (u / KS) % KS, u % KS) >> 4);
+    }
+  }
   const int pair_bytes = nchunks * cout_pad32 * 16 * 2;
   const __amdgpu_buffer_rsrc_t wrs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(wpk), (short)0, wbytes, 0x00020000);
-  for (int chunk = 0; chunk < nchunks; ++chunk) {
-    if (chunk) __syncthreads();
-    // the chunk's first channel of the workgroup's first pose (uniform); voxel
-    // offsets from it fit 32 bits (PP * D^3 * cin_pad elements), which keeps the
-    // per-voxel address arithmetic out of 64-bit multiplies
+  // Fine tiles run when few workgroups do, all in step and all missing L2 on the same
+  // weights, a ring's depth per trip to memory.  So the first workgroups of an XCD each
+  // touch a share of the next chunk's weights (one word per 128-byte line) a chunk ahead.
+  constexpr int kLinesPair = NT * 32 / 128, kLines = kLinesPair * C::PAIRS;
+  constexpr int kWarm = 4;  // lines per thread at most
+  const int wg = (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) / 8;
+  const int nwg = max(1, (int)(gridDim.x * gridDim.y * gridDim.z) / 8);
+  const int share = min(nwg, 32);
+  uint32_t touched[kWarm];
+  auto warm = [&](int chunk) {
+#pragma unroll
+    for (int i = 0; i < kWarm; ++i) {
+      const int l = wg + share * ((int)threadIdx.x + i * NTH);
+      const int off = (l / kLinesPair) * pair_bytes + (chunk * cout_pad32 + n0) * 32 + (l % kLinesPair) * 128;
+      touched[i] = 0;
+      if (wg < share && l < kLines && chunk < nchunks) touched[i] = __builtin_amdgcn_raw_buffer_load_b32(wrs, off, 0, 0);
+    }
+  };
+  auto warm_done = [&]() {
+#pragma unroll
+    for (int i = 0; i < kWarm; ++i) asm volatile("" ::"v"(touched[i]));  // keeps the loads
+  };
+  constexpr int kHv = C::FINE ? C::HITER : 1;
+  int hsrc[kHv], hdst[kHv];  // element and LDS offsets of this thread's halo voxels, -1: none
+  uint4 hnext[kHv];
+  auto halo_fetch = [&](int chunk) {
     const bf16_t *cin0 = in + pose_in * cin_pad + chunk * 8;
 #pragma unroll
-    for (int it0 = 0; it0 < HITER; it0 += HB) {
-      uint4 hv[HB];
+    for (int it = 0; it < kHv; ++it)
+      hnext[it] = hsrc[it] >= 0 ? *reinterpret_cast<const uint4 *>(cin0 + hsrc[it]) : make_uint4(0, 0, 0, 0);
+  };
+  if constexpr (C::FINE) {
 #pragma unroll
-      for (int it = it0; it < it0 + HB && it < HITER; ++it) {
-        const int v = it * NTH + (int)threadIdx.x;
-        hv[it - it0] = make_uint4(0, 0, 0, 0);
-        if (v < NV) {
-          const int pp = PP == 1 ? 0 : v / C::NV1, vl = PP == 1 ? v : v % C::NV1;
-          const int hx = vl % C::HX, hy = (vl / C::HX) % C::HY, hz = vl / (C::HX * C::HY);
-          const int gz = oz + hz, gy = oy + hy, gx = ox + hx;
-          if ((unsigned)gz < (unsigned)D && (unsigned)gy < (unsigned)D && (unsigned)gx < (unsigned)D &&
-              (PP == 1 || pose0 + pp < n_poses))
-            hv[it - it0] = *reinterpret_cast<const uint4 *>(cin0 + (((pp * D + gz) * D + gy) * D + gx) * cin_pad);
+    for (int it = 0; it < kHv; ++it) {
+      const int v = it * NTH + (int)threadIdx.x;
+      const int hx = v % C::HX, hy = (v / C::HX) % C::HY, hz = v / (C::HX * C::HY);
+      const int gz = oz + hz, gy = oy + hy, gx = ox + hx;
+      const bool inside = (unsigned)gz < (unsigned)D && (unsigned)gy < (unsigned)D && (unsigned)gx < (unsigned)D;
+      hsrc[it] = v < NV && inside ? ((gz * D + gy) * D + gx) * cin_pad : -1;
+      hdst[it] = v < NV ? stored_index(hz, C::HZ, S) * C::SLAB + stored_index(hy, C::HY, S) * C::ROW +
+                              stored_index(hx, C::HX, S) * 16
+                        : -1;
+    }
+    halo_fetch(0);
+    warm(0);
+    warm_done();
+  }
+  for (int chunk = 0; chunk < nchunks; ++chunk) {
+    if (chunk) __syncthreads();
+    if constexpr (C::FINE) {
+      if (!C::AHEAD && chunk) halo_fetch(chunk);
+#pragma unroll
+      for (int it = 0; it < kHv; ++it)
+        if (hdst[it] >= 0) *reinterpret_cast<uint4 *>(lds + hdst[it]) = hnext[it];
+    } else {
+      // the chunk's first channel of the workgroup's first pose (uniform); voxel
+      // offsets from it fit 32 bits (PP * D^3 * cin_pad elements), which keeps the
+      // per-voxel address arithmetic out of 64-bit multiplies
+      const bf16_t *cin0 = in + pose_in * cin_pad + chunk * 8;
+#pragma unroll
+      for (int it0 = 0; it0 < HITER; it0 += HB) {
+        uint4 hv[HB];
+#pragma unroll
+        for (int it = it0; it < it0 + HB && it < HITER; ++it) {
+          const int v = it * NTH + (int)threadIdx.x;
+          hv[it - it0] = make_uint4(0, 0, 0, 0);
+          if (v < NV) {
+            const int pp = PP == 1 ? 0 : v / C::NV1, vl = PP == 1 ? v : v % C::NV1;
+            const int hx = vl % C::HX, hy = (vl / C::HX) % C::HY, hz = vl / (C::HX * C::HY);
+            const int gz = oz + hz, gy = oy + hy, gx = ox + hx;
+            if ((unsigned)gz < (unsigned)D && (unsigned)gy < (unsigned)D && (unsigned)gx < (unsigned)D &&
+                (PP == 1 || pose0 + pp < n_poses))
+              hv[it - it0] = *reinterpret_cast<const uint4 *>(cin0 + (((pp * D + gz) * D + gy) * D + gx) * cin_pad);
+          }
         }
-      }
 #pragma unroll
-      for (int it = it0; it < it0 + HB && it < HITER; ++it) {
-        const int v = it * NTH + (int)threadIdx.x;
-        if (v < NV) {
-          const int pp = PP == 1 ? 0 : v / C::NV1, vl = PP == 1 ? v : v % C::NV1;
-          const int hx = vl % C::HX, hy = (vl / C::HX) % C::HY, hz = vl / (C::HX * C::HY);
-          const int off = pp * C::HALO1 + stored_index(hz, C::HZ, S) * C::SLAB + stored_index(hy, C::HY, S) * C::ROW +
-                          stored_index(hx, C::HX, S) * 16;
-          *reinterpret_cast<uint4 *>(lds + off) = hv[it - it0];
+        for (int it = it0; it < it0 + HB && it < HITER; ++it) {
+          const int v = it * NTH + (int)threadIdx.x;
+          if (v < NV) {
+            const int pp = PP == 1 ? 0 : v / C::NV1, vl = PP == 1 ? v : v % C::NV1;
+            const int hx = vl % C::HX, hy = (vl / C::HX) % C::HY, hz = vl / (C::HX * C::HY);
+            const int off = pp * C::HALO1 + stored_index(hz, C::HZ, S) * C::SLAB + stored_index(hy, C::HY, S) * C::ROW +
+                            stored_index(hx, C::HX, S) * 16;
+            *reinterpret_cast<uint4 *>(lds + off) = hv[it - it0];
+          }
         }
       }
     }
@@ -467,7 +552,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(Conv8Cf
 #pragma unroll
     for (int nb = 0; nb < C::NB; ++nb) vb[nb] = ((chunk * cout_pad32 + n0 + ncol0 + nb * 32 + lrow) * 16 + khalf * 8) * 2;
     // software pipeline: the weight fragments of pair p + kPF and the LDS row
-    // fragments of pair p + 1 are in flight while the MFMAs of pair p issue.  The
+    // fragments of pair p + AD - 1 are in flight while the MFMAs of pair p issue.  The
     // pair loop is unrolled by kPF so that both rings are indexed at compile time
     // (no register moves, so no wait on the newest loads).
     uint4 bq[kPF][C::NB];
@@ -477,19 +562,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(Conv8Cf
       for (int nb = 0; nb < C::NB; ++nb)
         bq[q][nb] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(wrs, vb[nb], q * pair_bytes, 0));
     int soff = kPF * pair_bytes;
-    uint4 ar[2][C::MB];
-    {
-      const int t0 = pair_toff(0, 0, 0, 0);
-#pragma unroll
-      for (int mb = 0; mb < C::MB; ++mb) ar[0][mb] = *reinterpret_cast<const uint4 *>(lds + rowoff[mb] + t0);
+    if constexpr (C::FINE) {
+      if (C::AHEAD && chunk + 1 < nchunks) halo_fetch(chunk + 1);
+      warm(chunk + 1);
     }
-    int dz = 0, dy = 0, dx = 2;  // first tap of pair 1
-    auto pair = [&](const int p, const int ph) {
-      // the last pair re-reads offset 0 of its rows (inside the halo) instead
-      const int tn = (p + 1 < C::PAIRS) ? pair_toff(p + 1, dz, dy, dx) : 0;
-#pragma unroll
-      for (int mb = 0; mb < C::MB; ++mb) ar[(ph + 1) & 1][mb] = *reinterpret_cast<const uint4 *>(lds + rowoff[mb] + tn);
-      __builtin_amdgcn_sched_barrier(0);  // keep those reads ahead of this pair's MFMAs
+    uint4 ar[AD][C::MB];
+    int dz = 0, dy = 0, dx = 0;  // first tap of the pair whose rows are read next
+    auto next_pair = [&]() {
       dx += 2;
       if (dx >= KS) {
         dx -= KS;
@@ -498,11 +577,42 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(Conv8Cf
           ++dz;
         }
       }
+    };
+    // fine tiles: packed offsets of the next kPF pairs to read (tw) and of those after (tx)
+    constexpr int kTw = C::FINE ? kPF / 8 : 1;
+    uint4 tw[kTw], tx[kTw];
+    const uint4 *tab8 = reinterpret_cast<const uint4 *>(tab + khalf * C::ENT) + 1;  // entry 8 = pair 3
+    if constexpr (C::FINE) {
+#pragma unroll
+      for (int i = 0; i < kTw; ++i) tw[i] = tab8[i];
+    }
+#pragma unroll
+    for (int d = 0; d < AD - 1; ++d) {
+      const int t0 = C::FINE ? tab[khalf * C::ENT + d + 5] * 16 : pair_toff(d, dz, dy, dx);
+#pragma unroll
+      for (int mb = 0; mb < C::MB; ++mb) ar[d][mb] = *reinterpret_cast<const uint4 *>(lds + rowoff[mb] + t0);
+      if constexpr (!C::FINE) next_pair();
+    }
+    auto pair = [&](const int p, const int ph) {
+      // past the last pair: offset 0 of its rows (inside the halo) instead
+      int tn;
+      if constexpr (C::FINE) {
+        const uint4 g = tw[ph >> 3];
+        const uint32_t t = (ph & 6) == 0 ? g.x : (ph & 6) == 2 ? g.y : (ph & 6) == 4 ? g.z : g.w;
+        tn = (int)((ph & 1) ? t >> 16 : t & 0xffffu) * 16;
+      } else {
+        tn = (p + AD - 1 < C::PAIRS) ? pair_toff(p + AD - 1, dz, dy, dx) : 0;
+      }
+#pragma unroll
+      for (int mb = 0; mb < C::MB; ++mb)
+        ar[(ph + AD - 1) % AD][mb] = *reinterpret_cast<const uint4 *>(lds + rowoff[mb] + tn);
+      __builtin_amdgcn_sched_barrier(0);  // keep those reads ahead of this pair's MFMAs
+      if constexpr (!C::FINE) next_pair();
 #pragma unroll
       for (int mb = 0; mb < C::MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < C::NB; ++nb)
-          acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ar[ph & 1][mb]),
+          acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ar[ph % AD][mb]),
                                                                  __builtin_bit_cast(bf16x8, bq[ph][nb]), acc[mb][nb],
                                                                  0, 0, 0);
 #pragma unroll
@@ -514,12 +624,21 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(Conv8Cf
     // analysis keeps every weight load of the ring in flight), then the rest
     constexpr int kFull = C::PAIRS / kPF * kPF;
     for (int p0 = 0; p0 < kFull; p0 += kPF) {
+      if constexpr (C::FINE) {
+#pragma unroll
+        for (int i = 0; i < kTw; ++i) tx[i] = tab8[(p0 + kPF) / 8 + i];
+      }
 #pragma unroll
       for (int ph = 0; ph < kPF; ++ph) pair(p0 + ph, ph);
+      if constexpr (C::FINE) {
+#pragma unroll
+        for (int i = 0; i < kTw; ++i) tw[i] = tx[i];
+      }
     }
 #pragma unroll
     for (int ph = 0; ph < kPF; ++ph)
       if (kFull + ph < C::PAIRS) pair(kFull + ph, ph);
+    if constexpr (C::FINE) warm_done();
   }
 
   // ---- epilogue through LDS, MBG row blocks per wave at a time ----
@@ -591,8 +710,19 @@ struct Conv4Cfg {
   static constexpr int PAD = (KS - 1) / 2;
   static constexpr int HZ = TZ * S + KS - S, HY = TY * S + KS - S, HX = TX * S + KS - S;
   static constexpr int ROW = HX * 8 + 8, SLAB = HY * ROW, HALO = HZ * SLAB;  // bytes
-  static constexpr int TAPS = KS * KS * KS, QUADS = (TAPS + 3) / 4, TAB = QUADS * 4 * 4;
+  static constexpr int TAPS = KS * KS * KS, QUADS = (TAPS + 3) / 4;
   static constexpr int MT = TZ * TY * TX, WM = MT / NW, MB = WM / 32, NB = NT / 32;
+  // Software pipeline of the quad walk, as in k_conv8: weight fragments PF quads ahead,
+  // row fragments AD - 1 quads ahead.
+  static constexpr int BLOCKS = MB * NB, AD = BLOCKS <= 2 ? 4 : 2;
+  static constexpr int PF = BLOCKS <= 2 ? 8 : 4;  // big tiles: weights stay in L2, six quads ahead measured 6 % slower
+  // LDS table of tap offsets into the halo.  AD = 2: one word per tap, read a quad
+  // ahead.  AD = 4: LDS reads return in order, so a table read per quad would wait for
+  // the row reads before it; the offsets of a quad are packed instead (two 16-bit
+  // counts of 8 bytes per K half) and read eight quads at a time, a group ahead:
+  // [half][entry], entry q + 1 for quad q (eight entries from a multiple of 4)
+  static constexpr int ENT = (QUADS + 2 * PF + 8) / 4 * 4;
+  static constexpr int TAB = AD == 2 ? QUADS * 4 * 4 : 2 * ENT * 4;
   static constexpr int MBG = (NW * 32 * NT * 2 * MB <= HALO) ? MB : ((NW * 32 * NT * 2 * 2 <= HALO && MB % 2 == 0) ? 2 : 1);
   static constexpr int EPI = NW * 32 * MBG * NT * 2;
   static constexpr int LDS = TAB + (HALO > EPI ? HALO : EPI);
@@ -602,8 +732,10 @@ struct Conv4Cfg {
   // voxels per thread, else two batches (the 21^3 halo of the first layer: 37
   // voxels per thread in 19 + 18 instead of batches of 8, 4-5 % faster)
   static constexpr int HB = HITER <= 20 ? HITER : (HITER + 1) / 2;
+  static constexpr int WGCU = 163840 / LDS < WPE * 4 / NW ? 163840 / LDS : WPE * 4 / NW;
   static_assert(WM % 32 == 0, "rows per wave must be a multiple of 32");
   static_assert(LDS <= 163840, "halo exceeds LDS");
+  static_assert(AD == 2 || (PF == 8 && AD == 4 && HALO / 8 < 65536), "packed table of the deep walk");
 };
 
 template <int KS, int S, int TZ, int TY, int TX, int NW, int NT>
@@ -613,7 +745,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(Conv4Cf
     int cout_store, int nty, int ntx, int wbytes, int chunk_major) {
   using C = Conv4Cfg<KS, S, TZ, TY, TX, NW, NT>;
   __shared__ __attribute__((aligned(16))) char lds[C::LDS];
-  int *tab = reinterpret_cast<int *>(lds);  // [QUADS * 4] tap offsets into the halo
+  constexpr int AD = C::AD;
+  int *tab = reinterpret_cast<int *>(lds);  // tap offsets into the halo (Conv4Cfg)
   char *halo = lds + C::TAB;
   int tile, pose, nblk;
   xcd_order(tile, pose, nblk);
@@ -623,14 +756,19 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(Conv4Cf
   const int khalf = lane >> 5, lrow = lane & 31;
   constexpr int NTH = NW * 64;
   constexpr int HZ2 = (C::HZ + 1) / 2, HY2 = (C::HY + 1) / 2, HX2 = (C::HX + 1) / 2;
-  for (int t = threadIdx.x; t < C::QUADS * 4; t += NTH) {
-    int off = 0;  // taps past the last read offset 0 (their weights are zero)
-    if (t < C::TAPS) {
-      const int dz = t / (KS * KS), dy = (t / KS) % KS, dx = t % KS;
-      off = (S == 1 ? dz : (dz & 1) * HZ2 + (dz >> 1)) * C::SLAB + (S == 1 ? dy : (dy & 1) * HY2 + (dy >> 1)) * C::ROW +
-            (S == 1 ? dx : (dx & 1) * HX2 + (dx >> 1)) * 8;
+  auto tap_off = [&](int t) {
+    if (t >= C::TAPS) return 0;  // taps past the last read offset 0 (their weights are zero)
+    const int dz = t / (KS * KS), dy = (t / KS) % KS, dx = t % KS;
+    return (S == 1 ? dz : (dz & 1) * HZ2 + (dz >> 1)) * C::SLAB + (S == 1 ? dy : (dy & 1) * HY2 + (dy >> 1)) * C::ROW +
+           (S == 1 ? dx : (dx & 1) * HX2 + (dx >> 1)) * 8;
+  };
+  if constexpr (AD == 2) {
+    for (int t = threadIdx.x; t < C::QUADS * 4; t += NTH) tab[t] = tap_off(t);
+  } else {
+    for (int e = threadIdx.x; e < 2 * C::ENT; e += NTH) {
+      const int h = e / C::ENT, q = e % C::ENT - 1, t = 4 * q + 2 * h;
+      tab[e] = q < 0 ? 0 : (tap_off(t) >> 3) | (tap_off(t + 1) >> 3) << 16;
     }
-    tab[t] = off;
   }
   int rowoff[C::MB];
 #pragma unroll
@@ -650,8 +788,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(Conv4Cf
   const int oz = tz0 * S - C::PAD, oy = ty0 * S - C::PAD, ox = tx0 * S - C::PAD;
   const int64_t pose_in = (int64_t)pose * D * D * D;
   constexpr int NV = C::HZ * C::HY * C::HX;
-  constexpr int kPF = 4;  // weights stay in L2 here: six quads ahead measured 6 % slower
-  static_assert(kPF <= kConvPadSteps, "prefetch past the weight padding");
+  constexpr int kPF = C::PF;  // past the last quad: zeros of the padding or from beyond the buffer
   const int quad_bytes = nchunks * cout_pad32 * 16 * 2;
   const __amdgpu_buffer_rsrc_t wrs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(wpk), (short)0, wbytes, 0x00020000);
@@ -701,32 +838,46 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(Conv4Cf
       for (int nb = 0; nb < C::NB; ++nb)
         bq[q][nb] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(wrs, vb[nb], q * quad_bytes, 0));
     int soff = kPF * quad_bytes;
-    // row fragments one quad ahead: two 8-byte reads per row block (taps t, t + 1)
-    uint4 ar[2][C::MB];
-    {
-      const int t0 = tab[2 * khalf], t1 = tab[2 * khalf + 1];
+    // row fragments AD - 1 quads ahead: two 8-byte reads per row block (taps t, t + 1)
+    uint4 ar[AD][C::MB];
+    auto rows = [&](uint4 (&dst)[C::MB], int t0, int t1) {
 #pragma unroll
       for (int mb = 0; mb < C::MB; ++mb) {
         const uint2 lo = *reinterpret_cast<const uint2 *>(halo + rowoff[mb] + t0);
         const uint2 hi = *reinterpret_cast<const uint2 *>(halo + rowoff[mb] + t1);
-        ar[0][mb] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+        dst[mb] = make_uint4(lo.x, lo.y, hi.x, hi.y);
       }
+    };
+    // deep walk: packed offsets of the next eight quads to read (tw) and of the eight
+    // after them (tx)
+    uint4 tw[2], tx[2];
+    const uint4 *tab8 = reinterpret_cast<const uint4 *>(tab + khalf * C::ENT) + 1;  // entry 4 = quad 3
+    if constexpr (AD == 2) {
+      rows(ar[0], tab[2 * khalf], tab[2 * khalf + 1]);
+    } else {
+#pragma unroll
+      for (int d = 0; d < AD - 1; ++d) {
+        const uint32_t t = (uint32_t)tab[khalf * C::ENT + d + 1];
+        rows(ar[d], (int)(t & 0xffffu) * 8, (int)(t >> 16) * 8);
+      }
+      tw[0] = tab8[0];
+      tw[1] = tab8[1];
     }
     auto quad = [&](const int q, const int ph) {
-      const int qn = q + 1 < C::QUADS ? q + 1 : q;
-      const int t0 = tab[4 * qn + 2 * khalf], t1 = tab[4 * qn + 2 * khalf + 1];
-#pragma unroll
-      for (int mb = 0; mb < C::MB; ++mb) {
-        const uint2 lo = *reinterpret_cast<const uint2 *>(halo + rowoff[mb] + t0);
-        const uint2 hi = *reinterpret_cast<const uint2 *>(halo + rowoff[mb] + t1);
-        ar[(ph + 1) & 1][mb] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+      if constexpr (AD == 2) {
+        const int qn = q + 1 < C::QUADS ? q + 1 : q;
+        rows(ar[(ph + 1) & 1], tab[4 * qn + 2 * khalf], tab[4 * qn + 2 * khalf + 1]);
+      } else {
+        const uint4 g = tw[ph >> 2];
+        const uint32_t t = (ph & 3) == 0 ? g.x : (ph & 3) == 1 ? g.y : (ph & 3) == 2 ? g.z : g.w;
+        rows(ar[(ph + AD - 1) % AD], (int)(t & 0xffffu) * 8, (int)(t >> 16) * 8);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int mb = 0; mb < C::MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < C::NB; ++nb)
-          acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ar[ph & 1][mb]),
+          acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ar[ph % AD][mb]),
                                                                  __builtin_bit_cast(bf16x8, bq[ph][nb]), acc[mb][nb],
                                                                  0, 0, 0);
 #pragma unroll
@@ -738,8 +889,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(Conv4Cf
     // analysis keeps every weight load of the ring in flight), then the rest
     constexpr int kFull = C::QUADS / kPF * kPF;
     for (int q0 = 0; q0 < kFull; q0 += kPF) {
+      if constexpr (AD > 2) {
+        tx[0] = tab8[q0 / 4 + 2];
+        tx[1] = tab8[q0 / 4 + 3];
+      }
 #pragma unroll
       for (int ph = 0; ph < kPF; ++ph) quad(q0 + ph, ph);
+      if constexpr (AD > 2) {
+        tw[0] = tx[0];
+        tw[1] = tx[1];
+      }
     }
 #pragma unroll
     for (int ph = 0; ph < kPF; ++ph)
@@ -814,6 +973,7 @@ struct Variant {
   int pairs;  // 1: bf16 8-channel tap-pair kernel (k_conv8, weights in wpk8); 2: 4-channel tap quads (k_conv4, wpk4)
   hipError_t (*launch_bf16)(const ConvLayer &, const void *, const void *, void *, int, int, hipStream_t);
   hipError_t (*launch_f32)(const ConvLayer &, const void *, const void *, void *, int, int, hipStream_t);
+  int pp, blocks, wgcu;  // poses per workgroup, 32 x 32 blocks per wave, workgroups per CU (tap kernels)
 };
 
 template <int KS, int S, int TZ, int TY, int TX, int NW, int NT, int WN, int PP>
@@ -845,29 +1005,33 @@ hipError_t launch_t(const ConvLayer &L, const void *in, const void *res, void *o
 #define CF_VARIANT(KS, S, TZ, TY, TX, NW, NT)                                                 \
   Variant {                                                                                   \
     "k" #KS "s" #S "_t" #TZ "x" #TY "x" #TX "_w" #NW "_n" #NT, KS, S, TZ, TY, TX, NW, NT, 0,   \
-        &launch_t<bf16_t, KS, S, TZ, TY, TX, NW, NT>, &launch_t<float, KS, S, TZ, TY, TX, NW, NT> \
+        &launch_t<bf16_t, KS, S, TZ, TY, TX, NW, NT>, &launch_t<float, KS, S, TZ, TY, TX, NW, NT>, 1, 0, 1 \
   }
 #define CF_VARIANT8(KS, S, TZ, TY, TX, NW, NT)                                                   \
   Variant {                                                                                      \
     "p8k" #KS "s" #S "_t" #TZ "x" #TY "x" #TX "_w" #NW "_n" #NT, KS, S, TZ, TY, TX, NW, NT, 1,   \
-        &launch_p<KS, S, TZ, TY, TX, NW, NT, 1, 1>, nullptr                                      \
+        &launch_p<KS, S, TZ, TY, TX, NW, NT, 1, 1>, nullptr, 1,                                  \
+        Conv8Cfg<KS, S, TZ, TY, TX, NW, NT, 1, 1>::BLOCKS, Conv8Cfg<KS, S, TZ, TY, TX, NW, NT, 1, 1>::WGCU \
   }
 // WN waves across the columns (each wave: NT / WN columns of its row group)
 #define CF_VARIANT8N(KS, S, TZ, TY, TX, NW, NT, WN)                                                      \
   Variant {                                                                                              \
     "p8k" #KS "s" #S "_t" #TZ "x" #TY "x" #TX "_w" #NW "c" #WN "_n" #NT, KS, S, TZ, TY, TX, NW, NT, 1,   \
-        &launch_p<KS, S, TZ, TY, TX, NW, NT, WN, 1>, nullptr                                             \
+        &launch_p<KS, S, TZ, TY, TX, NW, NT, WN, 1>, nullptr, 1,                                         \
+        Conv8Cfg<KS, S, TZ, TY, TX, NW, NT, WN, 1>::BLOCKS, Conv8Cfg<KS, S, TZ, TY, TX, NW, NT, WN, 1>::WGCU \
   }
 #define CF_VARIANT4(KS, S, TZ, TY, TX, NW, NT)                                                   \
   Variant {                                                                                      \
     "q4k" #KS "s" #S "_t" #TZ "x" #TY "x" #TX "_w" #NW "_n" #NT, KS, S, TZ, TY, TX, NW, NT, 2,   \
-        &launch_q<KS, S, TZ, TY, TX, NW, NT>, nullptr                                            \
+        &launch_q<KS, S, TZ, TY, TX, NW, NT>, nullptr, 1,                                        \
+        Conv4Cfg<KS, S, TZ, TY, TX, NW, NT>::BLOCKS, Conv4Cfg<KS, S, TZ, TY, TX, NW, NT>::WGCU   \
   }
 // ... and PP poses per workgroup
 #define CF_VARIANT8P(KS, S, TZ, TY, TX, NW, NT, WN, PP)                                                           \
   Variant {                                                                                                       \
     "p8k" #KS "s" #S "_t" #TZ "x" #TY "x" #TX "_w" #NW "c" #WN "_n" #NT "_p" #PP, KS, S, TZ, TY, TX, NW, NT, 1,   \
-        &launch_p<KS, S, TZ, TY, TX, NW, NT, WN, PP>, nullptr                                                     \
+        &launch_p<KS, S, TZ, TY, TX, NW, NT, WN, PP>, nullptr, PP,                                                \
+        Conv8Cfg<KS, S, TZ, TY, TX, NW, NT, WN, PP>::BLOCKS, Conv8Cfg<KS, S, TZ, TY, TX, NW, NT, WN, PP>::WGCU    \
   }
 
 const Variant kVariants[] = {
@@ -929,6 +1093,65 @@ const Variant kVariants[] = {
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
+// Finer tiles for batches that leave the chip idle at the variants above; chosen by
+// fit_tile only, so that variant ids stay what callers may have stored.
+const Variant kFineTiles[] = {
+    CF_VARIANT8N(7, 2, 4, 4, 4, 4, 64, 2),   // 12^3 outputs exactly, one 32 x 32 block per wave
+    CF_VARIANT8N(3, 1, 4, 4, 4, 4, 64, 2),
+    CF_VARIANT8N(3, 2, 4, 4, 4, 4, 64, 2),
+    CF_VARIANT8(5, 1, 4, 4, 8, 4, 32),
+    CF_VARIANT4(7, 2, 4, 4, 8, 4, 64),
+    CF_VARIANT4(5, 2, 4, 4, 8, 4, 32),
+    CF_VARIANT4(5, 1, 4, 4, 8, 4, 32)
+};
+
+bool tap_kernel_ok(const Variant &V, const ConvLayer &L) {
+  if (V.ks != L.k || V.s != L.stride || L.cout_pad32 % V.nt != 0) return false;
+  return V.pairs == 2 ? L.wpk4 && L.cin_pad % 4 == 0 : V.pairs == 1 && L.wpk8 && L.cin_pad % 8 == 0;
+}
+
+// Estimated time of a tap kernel, in cycles per K step: rounds of resident workgroups,
+// each as long as the matrix cores of its fullest CU need, but no less than one step
+// takes a lone workgroup.  Measured: the matrix cores reach 60 % with eight 32 x 32
+// blocks per wave, 50 % with four to six, 42 % with two and 33 % with one (each block
+// then reads its own row and weight fragment); a lone workgroup's step is ~550 cycles
+// with big tiles, 120 with fine ones and 250 with fine tap quads (their halo loads).
+double tile_cost(const Variant &V, const ConvLayer &L, int Do, int n_poses) {
+  constexpr int kCUs = 256;
+  const int64_t tiles = (int64_t)((Do + V.tz - 1) / V.tz) * ((Do + V.ty - 1) / V.ty) * ((Do + V.tx - 1) / V.tx);
+  const int64_t wg = tiles * ((n_poses + V.pp - 1) / V.pp) * (L.cout_pad32 / V.nt);
+  const double busy = V.blocks >= 8 ? 0.6 : V.blocks >= 4 ? 0.5 : V.blocks >= 2 ? 0.42 : 0.33;
+  const double step = V.blocks * 32.0 * (V.nw > 4 ? V.nw / 4.0 : 1.0) / busy;
+  const double lat = V.blocks > 2 ? 550.0 : V.pairs == 2 ? 250.0 : 120.0;
+  auto round = [&](int64_t per_cu) { return std::max(lat, per_cu * step); };
+  const int64_t full = wg / (kCUs * V.wgcu), rest = wg % (kCUs * V.wgcu);
+  return full * round(V.wgcu) + (rest ? round((rest + kCUs - 1) / kCUs) : 0.0);
+}
+
+// The tile for a batch of n_poses: the variant itself, unless another tile of the same
+// kernel is estimated a tenth faster.  Tiles of one kernel add the same products in
+// the same order, so the choice changes no result (a pose scores the same in any batch).
+// Measured, 64 -> 128 7^3 stride-2 layer, 384-row tiles of two poses against 64 x 64
+// tiles: 411 / 73 us for one 24^3 pose (9 workgroups of the big tile on 256 CUs), 492 /
+// 381 for 24, 537 / 539 for 40, 996 / 873 for 64 (a second round), 1065 / 671 for 19 poses
+// of 32^3; first layer, 512- against 128-row tiles: 110 / 51 us for one pose, 120 / 75 for four.
+const Variant &fit_tile(const Variant &V, const ConvLayer &L, int D_in, int n_poses) {
+  const int Do = (D_in + 2 * ((L.k - 1) / 2) - L.k) / L.stride + 1;
+  const Variant *best = &V;
+  double cost = 0.9 * tile_cost(V, L, Do, n_poses);
+  auto consider = [&](const Variant &C) {
+    if (C.pairs != V.pairs || !tap_kernel_ok(C, L)) return;
+    const double t = tile_cost(C, L, Do, n_poses);
+    if (t < cost) {
+      cost = t;
+      best = &C;
+    }
+  };
+  for (const Variant &C : kFineTiles) consider(C);
+  for (const Variant &C : kVariants) consider(C);
+  return *best;
+}
+
 }  // namespace
 
 // one more variant id past the direct kernels: the frequency-domain path
@@ -943,8 +1166,7 @@ bool conv_variant_ok(int v, const ConvLayer &L, int bf16, int D_in) {
   if (v == kFftVariant) return (bf16 ? !L.spec_f32 : L.spec_f32) && fft_conv_ok(L, D_in);
   if (v < 0 || v >= kNumVariants) return false;
   const Variant &V = kVariants[v];
-  if (V.pairs == 2) return bf16 && L.wpk4 && V.ks == L.k && V.s == L.stride && L.cout_pad32 % V.nt == 0 && L.cin_pad % 4 == 0;
-  if (V.pairs) return bf16 && L.wpk8 && V.ks == L.k && V.s == L.stride && L.cout_pad32 % V.nt == 0 && L.cin_pad % 8 == 0;
+  if (V.pairs) return bf16 && tap_kernel_ok(V, L);
   const int cc = bf16 ? 16 : 8;
   return V.ks == L.k && V.s == L.stride && L.cout_pad32 % V.nt == 0 && L.cin_pad % cc == 0;
 }
@@ -996,10 +1218,11 @@ hipError_t launch_fill_random(void *p, int64_t bytes, int bf16, uint64_t seed, h
 }
 
 hipError_t launch_conv(int variant, const ConvLayer &L, int bf16, const void *in, const void *res,
-                       void *out, int n_poses, int D_in, void *work, hipStream_t s) {
+                       void *out, int n_poses, int D_in, void *work, hipStream_t s, bool fit) {
   if (!conv_variant_ok(variant, L, bf16, D_in)) return hipErrorInvalidValue;
   if (variant == kFftVariant) return launch_fft_conv(L, in, res, out, n_poses, D_in, work, s);
-  const Variant &V = kVariants[variant];
+  const Variant &V = fit && bf16 && kVariants[variant].pairs ? fit_tile(kVariants[variant], L, D_in, n_poses)
+                                                             : kVariants[variant];
   return bf16 ? V.launch_bf16(L, in, res, out, n_poses, D_in, s) : V.launch_f32(L, in, res, out, n_poses, D_in, s);
 }
 

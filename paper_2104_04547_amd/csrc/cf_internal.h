@@ -69,6 +69,20 @@ __device__ inline void xcd_order(int &x, int &y, int &z) {
   y = l / (gz * gx);
 }
 
+// The same renumbering with z slowest: an XCD works on one z (for the conv kernels: one
+// block of output channels, whose weights then stay in its L2).
+__device__ inline void xcd_order_by_z(int &x, int &y, int &z) {
+  constexpr int kXcd = 8;
+  const int gx = gridDim.x, gy = gridDim.y, gz = gridDim.z;
+  const int n = gx * gy * gz;
+  const int L = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
+  const int q = n / kXcd, r = n % kXcd, xcd = L % kXcd, k = L / kXcd;
+  const int l = (xcd < r ? xcd * (q + 1) : r * (q + 1) + (xcd - r) * q) + k;
+  x = l % gx;
+  y = (l / gx) % gy;
+  z = l / (gx * gy);
+}
+
 // Blocks of `rows` atoms given to each pose of a batch whose poses have `mean_atoms`
 // atoms on average (host): enough for poses up to twice the mean, and never more than
 // the largest possible pose has.  Workgroups of a larger pose take several blocks.
@@ -127,8 +141,10 @@ bool conv_variant_ok(int v, const ConvLayer &L, int bf16, int D_in);
 int conv_default_variant(const ConvLayer &L, int D_in, int bf16);
 // device scratch a variant needs for n_poses (0 for the direct kernels)
 int64_t conv_work_bytes(int v, const ConvLayer &L, int D_in, int n_poses);
+// fit: a batch too small for the variant's tile may take a finer tile of the same kernel
+// (the same sums in the same order)
 hipError_t launch_conv(int variant, const ConvLayer &L, int bf16, const void *in, const void *res,
-                       void *out, int n_poses, int D_in, void *work, hipStream_t s);
+                       void *out, int n_poses, int D_in, void *work, hipStream_t s, bool fit = false);
 // seeded values uniform in [0, 0.5) over `bytes` of bf16 or fp32 elements
 hipError_t launch_fill_random(void *p, int64_t bytes, int bf16, uint64_t seed, hipStream_t s);
 
