@@ -13,11 +13,8 @@
 //     entry over a row of the weight matrix;
 //   * weight gradients sum_i U[i][a] V[i][b] over atoms / poses / voxels: row
 //     chunks into partial sums, then one pass adding the partials in order;
-//   * conv weight gradient: LDS-tiled (32 output channels x 64 (tap, channel)
-//     columns) over 16-voxel steps of one pose, partial per pose;
-//   * conv data gradient: LDS-tiled (64 voxels x 64 channels) over taps and
-//     16-channel steps, the transposed conv as a gather (stride 2 reads only the
-//     output voxels a tap reaches).
+//   * conv weight and data gradients: products on the float32 matrix instruction
+//     (32x32x2), see k_conv_wgrad and k_conv_dgrad.
 #include <algorithm>
 #include <cmath>
 
@@ -253,141 +250,247 @@ __global__ __launch_bounds__(kT) void k_relu_grad_rows(float *__restrict__ d, co
     d[e] = pre[e] > 0.0f ? d[e] : 0.0f;
 }
 
-// Folded weights transposed for the data gradient: WT[t][co][ci] = W[co][ci][t] * a[co],
-// a = gamma / sqrt(var + eps) with BatchNorm, else 1.
+// Folded weights for the data gradient, as MFMA B fragments: W[co][ci][t] * a[co],
+// a = gamma / sqrt(var + eps) with BatchNorm, else 1, at
+// WT[((t * nch + co / 8) * cpad + ci) * 8 + (co & 1) * 4 + (co % 8) / 2], nch chunks of 8
+// output channels and cpad input channels (zero past the layer's): the four K values of
+// a lane (one parity of eight channels) are one 16-byte load.
 __global__ __launch_bounds__(kT) void k_fold_wt(const float *__restrict__ W, const float *__restrict__ gamma,
-                                                const float *__restrict__ var, int cout, int cin, int taps,
-                                                float *__restrict__ WT) {
-  const int64_t n = (int64_t)cout * cin * taps;
+                                                const float *__restrict__ var, int cout, int cin, int taps, int nch,
+                                                int cpad, float *__restrict__ WT) {
+  const int64_t n = (int64_t)taps * nch * cpad * 8;
   for (int64_t e = blockIdx.x * (int64_t)kT + threadIdx.x; e < n; e += (int64_t)gridDim.x * kT) {
-    const int t = (int)(e % taps), ci = (int)((e / taps) % cin), co = (int)(e / ((int64_t)taps * cin));
-    const float a = gamma ? (float)((double)gamma[co] / sqrt((double)var[co] + 1e-5)) : 1.0f;
-    WT[((int64_t)t * cout + co) * cin + ci] = W[e] * a;
+    const int q = (int)(e % 8), ci = (int)((e / 8) % cpad);
+    const int64_t tc = e / (8 * (int64_t)cpad);
+    const int co = (int)(tc % nch) * 8 + 2 * (q & 3) + (q >> 2), t = (int)(tc / nch);
+    float v = 0.0f;
+    if (co < cout && ci < cin) {
+      const float a = gamma ? (float)((double)gamma[co] / sqrt((double)var[co] + 1e-5)) : 1.0f;
+      v = W[((int64_t)co * cin + ci) * taps + t] * a;
+    }
+    WT[e] = v;
   }
 }
 
-// Weight gradient of one conv layer w.r.t. its folded weights, per pose:
+typedef float f32x16b __attribute__((ext_vector_type(16)));
+
+// Weight gradient of one conv layer w.r.t. its folded weights, per pose (and, with
+// few poses, per row subset):
 //   part[p][co][t * cin + ci] = sum_o dY[p][o][co] * X[p][s o + t - P][ci]
-// Workgroup: 32 output channels x 64 (tap, channel) columns of pose p; 16 output
-// voxels per step, both operands staged in LDS; 8 accumulators per thread.
-__global__ __launch_bounds__(kT) void k_conv_wgrad(const float *__restrict__ X, int D, int xstride, int cin,
-                                                   const float *__restrict__ dY, int Do, int ystride, int cout,
-                                                   int KS, int S, float *__restrict__ part) {
-  __shared__ float sa[16][33];
-  __shared__ float sb[16][65];
-  const int q0 = blockIdx.x * 64, c0 = blockIdx.y * 32, p = blockIdx.z;
-  const int taps = KS * KS * KS, Q = taps * cin, P = (KS - 1) / 2;
-  const int tid = threadIdx.x;
-  const int tc = tid / 16, tq = tid % 16;  // thread: channels c0 + 2 tc + {0, 1}, columns q0 + tq + 16 {0..3}
-  float acc[2][4] = {};
-  const int64_t vo = (int64_t)Do * Do * Do;
+// A workgroup takes 32 MB output channels and 32 NB columns (tx, ci) of one (tz, ty);
+// its four waves take the output rows (oz, oy) in turn, each with all MB x NB blocks of
+// accumulators, and add up in order at the end.  Per row a wave stages its dY row and
+// the X row that (tz, ty) pairs with it in LDS of its own, in runs of up to kRun
+// output voxels (so no barrier inside): with the X row packed at cin floats per voxel,
+// column q = tx cin + ci at output voxel ox is float S ox cin + q, the same for every
+// tap of the row.
+// What bounds it: the float32 matrix instruction (64 cycles; MB NB of them per
+// MB + NB LDS reads), with two waves per SIMD to hide the staging.  The six layers of the
+// full model, 8 poses at 48^3: 25.4 ms, 55 TFLOP/s (LDS-tiled FMAs with an im2col division
+// per element: 62.0 ms).
+constexpr int kRun = 24;
+// floats of LDS per wave at a run of `run` voxels: dY run, X run, and zeros for the
+// columns past the row's last (at most 4 blocks of 32 and 31 more)
+inline int wgrad_wave_floats(int run, int KS, int S, int cin) {
+  const int f = run * 64 + (S * (run - 1) + KS) * cin + 160;
+  return (f < 1024 ? 1024 : f + 3) / 4 * 4;
+}
+
+template <int MB, int NB>
+__global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2))) void k_conv_wgrad(
+    const float *__restrict__ X, int D, int xstride, int cin, const float *__restrict__ dY, int Do, int ystride,
+    int cout, int KS, int S, int ncg, int nsplit, int run, int wave_floats, float *__restrict__ part) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  const int P = (KS - 1) / 2;
+  const int cg = blockIdx.x % ncg, tzy = blockIdx.x / ncg, tz = tzy / KS, ty = tzy % KS;
+  const int c0 = blockIdx.y * 32 * MB, q0 = cg * 32 * NB;
+  const int p = blockIdx.z / nsplit, split = blockIdx.z % nsplit;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, khalf = lane >> 5, lrow = lane & 31;
+  float *sA = lds + wave * wave_floats, *sB = sA + run * 64;
+  const int xw = S * (run - 1) + KS;           // X positions of a run
   const float *xp = X + (int64_t)p * D * D * D * xstride;
-  const float *yp = dY + (int64_t)p * vo * ystride;
-  for (int64_t o0 = 0; o0 < vo; o0 += 16) {
-    // A: dY[o0 + r][c0 + c], r < 16, c < 32
-    for (int e = tid; e < 16 * 32; e += kT) {
-      const int r = e / 32, c = e % 32;
-      const int64_t o = o0 + r;
-      sa[r][c] = (o < vo && c0 + c < cout) ? yp[o * ystride + c0 + c] : 0.0f;
-    }
-    // B: X at s o + t - P, r < 16, column q = t * cin + ci
-    for (int e = tid; e < 16 * 64; e += kT) {
-      const int r = e / 64, qq = e % 64, q = q0 + qq;
-      const int64_t o = o0 + r;
-      float v = 0.0f;
-      if (o < vo && q < Q) {
-        const int t = q / cin, ci = q % cin;
-        const int tz = t / (KS * KS), ty = (t / KS) % KS, tx = t % KS;
-        const int oz = (int)(o / (Do * Do)), oy = (int)((o / Do) % Do), ox = (int)(o % Do);
-        const int z = S * oz + tz - P, y = S * oy + ty - P, x = S * ox + tx - P;
-        if (z >= 0 && z < D && y >= 0 && y < D && x >= 0 && x < D)
-          v = xp[(((int64_t)z * D + y) * D + x) * xstride + ci];
-      }
-      sb[r][qq] = v;
-    }
-    __syncthreads();
+  const float *yp = dY + (int64_t)p * Do * Do * Do * ystride + c0;
+  const int nco = min(32 * MB, cout - c0);
+  f32x16b acc[MB][NB];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float a0 = sa[r][2 * tc], a1 = sa[r][2 * tc + 1];
+  for (int m = 0; m < MB; ++m)
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const float b = sb[r][tq + 16 * u];
-        acc[0][u] = fmaf(a0, b, acc[0][u]);
-        acc[1][u] = fmaf(a1, b, acc[1][u]);
+    for (int n = 0; n < NB; ++n) acc[m][n] = f32x16b{};
+  for (int e = lane; e < 160; e += 64) sB[xw * cin + e] = 0.0f;  // columns past the row's last
+  for (int r = split * 4 + wave; r < Do * Do; r += 4 * nsplit) {
+    const int oz = r / Do, oy = r % Do, z = S * oz + tz - P, y = S * oy + ty - P;
+    if (z < 0 || z >= D || y < 0 || y >= D) continue;
+    const float *xr = xp + ((int64_t)z * D + y) * D * xstride;
+    const float *yr = yp + (int64_t)r * Do * ystride;
+    for (int o0 = 0; o0 < Do; o0 += run) {
+      const int no = min(run, Do - o0);
+      // the wave's own LDS: its operations stay in order, only the compiler is held
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      // dY run: [voxel][64], odd voxels with their two 32-channel halves swapped, so that
+      // the two K halves of a fragment read fall on different banks
+      constexpr int CW = 32 * MB;              // channels staged
+      constexpr int VPL = 64 / CW;             // voxels per pass of the wave
+      const int ca = lane % CW;
+#pragma unroll 4
+      for (int v = lane / CW; v < run; v += VPL) {
+        const float a = v < no && ca < nco ? yr[(int64_t)(o0 + v) * ystride + ca] : 0.0f;
+        sA[v * 64 + (ca ^ ((v & 1) << 5))] = a;
+      }
+      // X run: positions S o0 - P + i, cin floats each; zero outside the grid and past the
+      // last one an output voxel of the run reaches
+      const int x0 = S * o0 - P, xe = min(D, x0 + S * (no - 1) + KS);
+      if ((cin & 3) == 0 && (xstride & 3) == 0) {
+        const int c4 = cin >> 2;
+#pragma unroll 4
+        for (int e = lane; e < xw * c4; e += 64) {
+          const int i = e / c4, c = e - i * c4, x = x0 + i;
+          reinterpret_cast<float4 *>(sB)[e] = x >= 0 && x < xe
+                                                  ? *reinterpret_cast<const float4 *>(xr + (int64_t)x * xstride + 4 * c)
+                                                  : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+      } else {
+#pragma unroll 4
+        for (int e = lane; e < xw * cin; e += 64) {
+          const int i = e / cin, c = e - i * cin, x = x0 + i;
+          sB[e] = x >= 0 && x < xe ? xr[(int64_t)x * xstride + c] : 0.0f;
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      const float *bp = sB + khalf * S * cin + q0 + lrow;
+      for (int k = 0; k < run; k += 2) {
+        const int v = k + khalf;
+        float a[MB], b[NB];
+#pragma unroll
+        for (int m = 0; m < MB; ++m) a[m] = sA[v * 64 + ((32 * m + lrow) ^ (khalf << 5))];
+#pragma unroll
+        for (int n = 0; n < NB; ++n) b[n] = bp[k * S * cin + 32 * n];
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+          for (int n = 0; n < NB; ++n)
+            acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[m], b[n], acc[m][n], 0, 0, 0);
       }
     }
-    __syncthreads();
   }
+  // the waves' sums in order, a block at a time
+  const int64_t Q = (int64_t)KS * KS * KS * cin;
+  const int qn = KS * cin;
+  float *out = part + (int64_t)blockIdx.z * cout * Q + (int64_t)tzy * qn;
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
+  for (int m = 0; m < MB; ++m)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int co = c0 + 2 * tc + h, q = q0 + tq + 16 * u;
-      if (co < cout && q < Q) part[((int64_t)p * cout + co) * Q + q] = acc[h][u];
+    for (int n = 0; n < NB; ++n) {
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < 16; ++j) lds[wave * 1024 + (8 * (j >> 2) + 4 * khalf + (j & 3)) * 32 + lrow] = acc[m][n][j];
+      __syncthreads();
+      for (int e = threadIdx.x; e < 1024; e += kT) {
+        const int co = c0 + 32 * m + e / 32, q = q0 + 32 * n + e % 32;
+        if (co < cout && q < qn) out[co * Q + q] = lds[e] + lds[1024 + e] + lds[2048 + e] + lds[3072 + e];
+      }
     }
 }
 
 // Data gradient of one conv layer (the transposed conv as a gather):
-//   dX[p][v][ci] += sum_{t, co} dY[p][o][co] * WT[t][co][ci],  s o = v + P - t
-// for the output voxels o (per axis) a tap reaches.  Workgroup: 64 input voxels
-// x 64 channels of pose p; per tap, 16-channel steps of co staged in LDS.
-__global__ __launch_bounds__(kT) void k_conv_dgrad(const float *__restrict__ dY, int Do, int ystride, int cout,
-                                                   const float *__restrict__ WT, int cin, int KS, int S, int D,
-                                                   int xstride, float *__restrict__ dX) {
-  __shared__ float sa[64][17];
-  __shared__ float sb[16][65];
-  const int v0 = blockIdx.x * 64, ci0 = blockIdx.y * 64, p = blockIdx.z;
-  const int taps = KS * KS * KS, P = (KS - 1) / 2;
-  const int tid = threadIdx.x;
-  const int tv = tid / 16, tcc = tid % 16;  // voxels v0 + 4 tv + {0..3}, channels ci0 + tcc + 16 {0..3}
-  const int64_t vin = (int64_t)D * D * D, vo = (int64_t)Do * Do * Do;
-  const float *yp = dY + (int64_t)p * vo * ystride;
-  float acc[4][4] = {};
-  for (int t = 0; t < taps; ++t) {
-    const int tz = t / (KS * KS), ty = (t / KS) % KS, tx = t % KS;
-    for (int c0 = 0; c0 < cout; c0 += 16) {
-      for (int e = tid; e < 64 * 16; e += kT) {
-        const int r = e / 16, c = e % 16;
-        const int64_t v = v0 + r;
-        float val = 0.0f;
-        if (v < vin && c0 + c < cout) {
-          const int z = (int)(v / (D * D)), y = (int)((v / D) % D), x = (int)(v % D);
-          const int nz = z + P - tz, ny = y + P - ty, nx = x + P - tx;
-          if (nz >= 0 && ny >= 0 && nx >= 0 && nz % S == 0 && ny % S == 0 && nx % S == 0) {
-            const int oz = nz / S, oy = ny / S, ox = nx / S;
-            if (oz < Do && oy < Do && ox < Do) val = yp[(((int64_t)oz * Do + oy) * Do + ox) * ystride + c0 + c];
-          }
-        }
-        sa[r][c] = val;
-      }
-      for (int e = tid; e < 16 * 64; e += kT) {
-        const int c = e / 64, cc = e % 64;
-        sb[c][cc] = (c0 + c < cout && ci0 + cc < cin) ? WT[((int64_t)t * cout + c0 + c) * cin + ci0 + cc] : 0.0f;
-      }
-      __syncthreads();
+//   dX[p][v][ci] += sum_{t, co} dY[p][o][co] * W'[co][ci][t],  s o = v + P - t
+// Input voxels of one parity per axis (v = s u + r) see the same taps t = t0 + s m, and
+// reach the output voxels o = u + c - m: per parity class this is a dense stride-1
+// correlation over dY.  A workgroup takes a 4 x 4 x 4 tile of u of one class and 64 input
+// channels, a wave 32 x 32 of them; K runs over 8-channel chunks of co (the tile's dY
+// halo in LDS, even and odd channels apart) and the class's taps (weight fragments from
+// L2, two taps ahead).
+// What bounds it: the float32 matrix instruction, four per row and weight load.
+// Five layers of the full model, 8 poses at 48^3: 13.0 ms, 101 TFLOP/s (LDS-tiled FMAs that
+// tested every tap for parity: 65.7 ms).
+constexpr int kDT = 4;                     // tile edge (class voxels)
+constexpr int kDHalo = kDT + 6;            // halo edge at most (k = 7, stride 1)
+
+__global__ __launch_bounds__(kT) void k_conv_dgrad(const float *__restrict__ dY, int Do, int ystride, int nch,
+                                                   const float *__restrict__ WT, int cin, int cpad, int KS, int S,
+                                                   int D, int xstride, float *__restrict__ dX) {
+  __shared__ __attribute__((aligned(16))) float halo[kDHalo * kDHalo * kDHalo * 8];
+  const int ncl = S * S * S, P = (KS - 1) / 2;
+  const int p = blockIdx.z / ncl, cl = blockIdx.z % ncl;
+  const int rr[3] = {cl / (S * S), (cl / S) % S, cl % S};
+  int t0[3], nt[3], nu[3], base[3];  // first tap, taps, class voxels, first halo voxel - u0
 #pragma unroll
-      for (int c = 0; c < 16; ++c) {
-        float b[4], a[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) b[u] = sb[c][tcc + 16 * u];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) a[r] = sa[4 * tv + r][c];
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int u = 0; u < 4; ++u) acc[r][u] = fmaf(a[r], b[u], acc[r][u]);
-      }
-      __syncthreads();
-    }
+  for (int d = 0; d < 3; ++d) {
+    t0[d] = (rr[d] + P) % S;
+    nt[d] = (KS - t0[d] + S - 1) / S;
+    nu[d] = (D - rr[d] + S - 1) / S;
+    base[d] = (rr[d] + P - t0[d]) / S - (nt[d] - 1);
   }
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t v = v0 + 4 * tv + r;
-      const int ci = ci0 + tcc + 16 * u;
-      if (v < vin && ci < cin) dX[((int64_t)p * vin + v) * xstride + ci] += acc[r][u];
+  const int Dc = (D + S - 1) / S, ntl = (Dc + kDT - 1) / kDT;
+  const int uz0 = (int)(blockIdx.x / (ntl * ntl)) * kDT, uy0 = (int)(blockIdx.x / ntl) % ntl * kDT,
+            ux0 = (int)(blockIdx.x % ntl) * kDT;
+  if (uz0 >= nu[0] || uy0 >= nu[1] || ux0 >= nu[2]) return;
+  const int hz = kDT + nt[0] - 1, hy = kDT + nt[1] - 1, hx = kDT + nt[2] - 1;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, khalf = lane >> 5, lrow = lane & 31;
+  const int m = (wave & 1) * 32 + lrow;                       // this lane's A row: tile voxel
+  const int ci = blockIdx.y * 64 + (wave >> 1) * 32 + lrow;   // ... and B column
+  const bool cols = blockIdx.y * 64 + (wave >> 1) * 32 < cin; // a wave past the channels only stages
+  const int lz = m / 16, ly = (m / 4) % 4, lx = m % 4;
+  const float *yp = dY + (int64_t)p * Do * Do * Do * ystride;
+  f32x16b acc = {};
+  for (int c = 0; c < nch; ++c) {
+    __syncthreads();
+    for (int e = threadIdx.x; e < hz * hy * hx; e += kT) {
+      const int x = e % hx, y = (e / hx) % hy, z = e / (hx * hy);
+      const int oz = uz0 + base[0] + z, oy = uy0 + base[1] + y, ox = ux0 + base[2] + x;
+      float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
+      if (oz >= 0 && oz < Do && oy >= 0 && oy < Do && ox >= 0 && ox < Do) {
+        const float *src = yp + (((int64_t)oz * Do + oy) * Do + ox) * ystride + c * 8;
+        a = *reinterpret_cast<const float4 *>(src);
+        b = *reinterpret_cast<const float4 *>(src + 4);
+      }
+      float4 *dst = reinterpret_cast<float4 *>(halo + e * 8);
+      dst[0] = make_float4(a.x, a.z, b.x, b.z);
+      dst[1] = make_float4(a.y, a.w, b.y, b.w);
     }
+    __syncthreads();
+    if (!cols) continue;
+    // weight fragments of the class's taps in turn (mx fastest; the last one again past
+    // the end)
+    const float *wb = WT + ((int64_t)c * cpad + ci) * 8 + khalf * 4;
+    int fx = 0, fy = 0, fz = 0;
+    auto next_frag = [&]() {
+      const int t = ((t0[0] + S * fz) * KS + t0[1] + S * fy) * KS + t0[2] + S * fx;
+      if (++fx == nt[2]) {
+        fx = 0;
+        if (++fy == nt[1]) {
+          fy = 0;
+          if (++fz == nt[0]) fx = nt[2] - 1, fy = nt[1] - 1, fz = nt[0] - 1;
+        }
+      }
+      return *reinterpret_cast<const float4 *>(wb + (int64_t)t * nch * cpad * 8);
+    };
+    float4 w0 = next_frag(), w1 = next_frag();
+    for (int mz = 0; mz < nt[0]; ++mz)
+      for (int my = 0; my < nt[1]; ++my) {
+        const float *row = halo + (((lz + nt[0] - 1 - mz) * hy + ly + nt[1] - 1 - my) * hx + lx) * 8 + khalf * 4;
+        for (int mx = 0; mx < nt[2]; ++mx) {
+          const float4 w = w0;
+          w0 = w1;
+          w1 = next_frag();
+          const float4 a = *reinterpret_cast<const float4 *>(row + (nt[2] - 1 - mx) * 8);
+          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, w.x, acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, w.y, acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, w.z, acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, w.w, acc, 0, 0, 0);
+        }
+      }
+  }
+  if (!cols || ci >= cin) return;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const int mm = (wave & 1) * 32 + 8 * (j >> 2) + 4 * khalf + (j & 3);
+    const int uz = uz0 + mm / 16, uy = uy0 + (mm / 4) % 4, ux = ux0 + mm % 4;
+    if (uz >= nu[0] || uy >= nu[1] || ux >= nu[2]) continue;
+    const int64_t v = ((int64_t)(S * uz + rr[0]) * D + S * uy + rr[1]) * D + S * ux + rr[2];
+    dX[((int64_t)p * D * D * D + v) * xstride + ci] += acc[j];
+  }
 }
 
 // Folded-weight gradients -> gradients of the blob's parameters, one workgroup
@@ -612,23 +715,60 @@ hipError_t bw_relu_grad_rows(float *d, const float *pre, int n, int J, hipStream
   if (n > 0) hipLaunchKernelGGL(k_relu_grad_rows, grid1((int64_t)n * J), dim3(kT), 0, s, d, pre, n, J);
   return hipGetLastError();
 }
+int64_t bw_fold_wt_floats(int cout, int cin, int taps) {
+  return (int64_t)taps * ((cout + 7) / 8) * ((cin + 31) / 32 * 32) * 8;
+}
 hipError_t bw_fold_wt(const float *W, const float *gamma, const float *var, int cout, int cin, int taps, float *WT,
                       hipStream_t s) {
-  hipLaunchKernelGGL(k_fold_wt, grid1((int64_t)cout * cin * taps), dim3(kT), 0, s, W, gamma, var, cout, cin, taps, WT);
+  hipLaunchKernelGGL(k_fold_wt, grid1(bw_fold_wt_floats(cout, cin, taps)), dim3(kT), 0, s, W, gamma, var, cout, cin,
+                     taps, (cout + 7) / 8, (cin + 31) / 32 * 32, WT);
   return hipGetLastError();
 }
+// row subsets per pose of the weight gradient: as many as nparts partials allow, while
+// the launch has fewer workgroups than two per CU
+int bw_conv_wgrad_split(int cin, int cout, int KS, int Do, int np, int nparts) {
+  const int nb = (KS * cin + 31) / 32, ncg = (nb + 4) / 5, mb = cout <= 32 ? 1 : 2;
+  const int64_t wg = (int64_t)KS * KS * ncg * ((cout + 32 * mb - 1) / (32 * mb)) * np;
+  int split = 1;
+  while (split < 8 && wg * split < 512 && (split * 2) * np <= nparts && split * 8 <= Do * Do) split *= 2;
+  return split;
+}
 hipError_t bw_conv_wgrad(const float *X, int D, int xstride, int cin, const float *dY, int Do, int ystride, int cout,
-                         int KS, int S, int np, float *part, hipStream_t s) {
-  const int Q = KS * KS * KS * cin;
-  hipLaunchKernelGGL(k_conv_wgrad, dim3((Q + 63) / 64, (cout + 31) / 32, np), dim3(kT), 0, s, X, D, xstride, cin, dY,
-                     Do, ystride, cout, KS, S, part);
+                         int KS, int S, int np, int nsplit, float *part, hipStream_t s) {
+  const int nb = (KS * cin + 31) / 32, ncg = (nb + 4) / 5, nbw = (nb + ncg - 1) / ncg;
+  // voxels per run: even, at most kRun, two workgroups per CU (one needs a run of at most
+  // two voxels and 256 channels to fit)
+  int run = std::min(kRun, (Do + 1) / 2 * 2);
+  while (run > 2 && wgrad_wave_floats(run, KS, S, cin) * 16 > 81920) run -= 2;
+  const int wf = wgrad_wave_floats(run, KS, S, cin);
+  const size_t lds = sizeof(float) * 4 * wf;
+  if (lds > 163840) return hipErrorInvalidValue;
+  const int mb = cout <= 32 ? 1 : 2;
+  const dim3 grid(KS * KS * ncg, (cout + 32 * mb - 1) / (32 * mb), np * nsplit);
+#define CF_WG(MB, NB)                                                                                              \
+  do {                                                                                                             \
+    if (lds > 65536) {                                                                                             \
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_conv_wgrad<MB, NB>),              \
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, 163840);                \
+      if (e != hipSuccess) return e;                                                                               \
+    }                                                                                                              \
+    hipLaunchKernelGGL((k_conv_wgrad<MB, NB>), grid, dim3(kT), lds, s, X, D, xstride, cin, dY, Do, ystride, cout,  \
+                       KS, S, ncg, nsplit, run, wf, part);                                                              \
+  } while (0)
+  if (mb == 1) {
+    if (nbw <= 3) CF_WG(1, 3); else CF_WG(1, 5);
+  } else {
+    if (nbw <= 3) CF_WG(2, 3); else CF_WG(2, 5);
+  }
+#undef CF_WG
   return hipGetLastError();
 }
 hipError_t bw_conv_dgrad(const float *dY, int Do, int ystride, int cout, const float *WT, int cin, int KS, int S, int D,
                          int xstride, int np, float *dX, hipStream_t s) {
-  const int64_t vin = (int64_t)D * D * D;
-  hipLaunchKernelGGL(k_conv_dgrad, dim3((unsigned)((vin + 63) / 64), (cin + 63) / 64, np), dim3(kT), 0, s, dY, Do,
-                     ystride, cout, WT, cin, KS, S, D, xstride, dX);
+  if (KS - 1 + kDT > kDHalo || ystride % 8) return hipErrorInvalidValue;
+  const int ntl = ((D + S - 1) / S + kDT - 1) / kDT;
+  hipLaunchKernelGGL(k_conv_dgrad, dim3(ntl * ntl * ntl, (cin + 63) / 64, np * S * S * S), dim3(kT), 0, s, dY, Do,
+                     ystride, (cout + 7) / 8, WT, cin, (cin + 31) / 32 * 32, KS, S, D, xstride, dX);
   return hipGetLastError();
 }
 hipError_t bw_fold_grad(const float *dWf, const float *dbf, const float *W, const float *b, const float *gamma,

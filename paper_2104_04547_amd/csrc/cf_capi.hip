@@ -1194,14 +1194,15 @@ int cf_backward(cf_ctx *c, const cf_pose_batch *b, int G, const float *dscore, f
   const int64_t nH = acap * H, n3 = acap * 3 * H;
   const int64_t sg_floats = (R + 1) * nH + R * nH + 2 * R * n3 + 9 * nH + 2 * n3;
   if ((rc = ensure(c, c->bw_sg, (size_t)sg_floats * sizeof(float)))) return rc;
-  // CNN scratch: per-pose weight-gradient partials, the pose sum, folded transposed
-  // weights, bias gradient; pool / dense rows
-  int64_t wq = 0;
-  for (int i = 0; i < L; ++i)
-    wq = std::max<int64_t>(wq, (int64_t)c->conv[i].cout * c->conv[i].cin * c->conv[i].k * c->conv[i].k * c->conv[i].k);
+  int64_t wq = 0, wt = 0;
+  for (int i = 0; i < L; ++i) {
+    const auto &Lr = c->conv[i];
+    const int taps = Lr.k * Lr.k * Lr.k;
+    wq = std::max<int64_t>(wq, (int64_t)Lr.cout * Lr.cin * taps);
+    if (i > 0) wt = std::max(wt, cf::bw_fold_wt_floats(Lr.cout, Lr.cin, taps));
+  }
+  wq = (wq + 3) / 4 * 4;  // the packed weights after the partials are read 16 bytes at a time
   const int dmax = 256;
-  const int64_t cnn_floats = (int64_t)chunk * wq + 2 * wq + 256 + 8 * (int64_t)chunk * dmax;
-  if ((rc = ensure(c, c->bw_cnn, (size_t)cnn_floats * sizeof(float)))) return rc;
   // head: per-pose parameter gradients and the latents' gradients
   const int64_t head_floats = (int64_t)chunk * c->tr.head_n + (int64_t)chunk * (c->lc + H) + 2 * (int64_t)chunk;
   if ((rc = ensure(c, c->bw_head, (size_t)head_floats * sizeof(float)))) return rc;
@@ -1213,6 +1214,15 @@ int cf_backward(cf_ctx *c, const cf_pose_batch *b, int G, const float *dscore, f
   part = std::max(part, cf::bw_outer_scratch(chunk, dmax, dmax));
   for (int i = 0; i < L; ++i) part = std::max(part, cf::bw_outer_scratch((int)(chunk * vox(i + 1)), c->conv[i].cout, 1));
   if ((rc = ensure(c, c->bw_part, (size_t)part * sizeof(float)))) return rc;
+  // CNN scratch: weight-gradient partials (one per pose, or several when few poses would
+  // leave the chip idle and the budget has room), their sum, folded weights packed for the
+  // data gradient, bias gradient; pool / dense rows
+  const int64_t cnn_rest = wq + wt + 256 + 8 * (int64_t)chunk * dmax;
+  int nparts = chunk;
+  if (nparts < 8 && c->scratch_bytes - (int64_t)c->bw_cnn.n + c->weight_bytes +
+                            (8 * wq + cnn_rest) * (int64_t)sizeof(float) <= c->budget)
+    nparts = 8;
+  if ((rc = ensure(c, c->bw_cnn, (size_t)(nparts * wq + cnn_rest) * sizeof(float)))) return rc;
 
   const float *P = c->raw;
   const TrainOffsets &T = c->tr;
@@ -1292,7 +1302,7 @@ int cf_backward(cf_ctx *c, const cf_pose_batch *b, int G, const float *dscore, f
     CF_HIP(cf::bw_outer(dH, H, x, CF_NCH, n, H, CF_NCH, grad + T.embed_w, CF_NCH, 1, pt, s));
     CF_HIP(cf::bw_outer(dH, H, nullptr, 0, n, H, 1, grad + T.embed_b, 1, 1, pt, s));
     // ---- 3D-CNN backward ----
-    float *part = (float *)c->bw_cnn.p, *dWf = part + (int64_t)chunk * wq, *WT = dWf + wq, *dbf = WT + wq;
+    float *part = (float *)c->bw_cnn.p, *dWf = part + (int64_t)nparts * wq, *WT = dWf + wq, *dbf = WT + wt;
     float *pool = dbf + 256, *pre1 = pool + (int64_t)chunk * dmax, *lat1 = pre1 + (int64_t)chunk * dmax;
     float *pre2 = lat1 + (int64_t)chunk * dmax, *dl2 = pre2 + (int64_t)chunk * dmax, *dl1 = dl2 + (int64_t)chunk * dmax;
     float *dpool = dl1 + (int64_t)chunk * dmax;
@@ -1335,9 +1345,10 @@ int cf_backward(cf_ctx *c, const cf_pose_batch *b, int G, const float *dscore, f
       const float *X = i == 0 ? (const float *)c->grid.p : (const float *)c->act[i - 1].p;
       const int xs = i == 0 ? grid_cpad(c) : c->conv[i - 1].cout_store;
       const int64_t Q = (int64_t)taps * Lr.cin;
+      const int nsplit = cf::bw_conv_wgrad_split(Lr.cin, Lr.cout, Lr.k, dims[i + 1], np, nparts);
       CF_HIP(cf::bw_conv_wgrad(X, dims[i], xs, Lr.cin, dY, dims[i + 1], Lr.cout_store, Lr.cout, Lr.k, Lr.stride, np,
-                               part, s));
-      CF_HIP(cf::bw_outer(part, (int)(Lr.cout * Q), nullptr, 0, np, (int)(Lr.cout * Q), 1, dWf, 1, 0, pt, s));
+                               nsplit, part, s));
+      CF_HIP(cf::bw_outer(part, (int)(Lr.cout * Q), nullptr, 0, np * nsplit, (int)(Lr.cout * Q), 1, dWf, 1, 0, pt, s));
       const bool bn = d.bn != 0;
       CF_HIP(cf::bw_fold_grad(dWf, dbf, P + T.conv_w[i], P + T.conv_b[i], bn ? P + T.bn_g[i] : nullptr,
                               bn ? P + T.bn_m[i] : nullptr, bn ? P + T.bn_v[i] : nullptr, Lr.cout, Lr.cin, taps,

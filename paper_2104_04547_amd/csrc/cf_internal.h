@@ -234,10 +234,16 @@ hipError_t bw_pool_seed(const float *dpool, int np, int64_t vox, int cstride, in
 hipError_t bw_relu_mask(float *d, const float *y, int64_t n, hipStream_t s);
 hipError_t bw_relu_rows(float *y, int n, int J, int ld, hipStream_t s);
 hipError_t bw_relu_grad_rows(float *d, const float *pre, int n, int J, hipStream_t s);
+// folded weights packed for the data gradient (bw_fold_wt_floats floats)
+int64_t bw_fold_wt_floats(int cout, int cin, int taps);
 hipError_t bw_fold_wt(const float *W, const float *gamma, const float *var, int cout, int cin, int taps, float *WT,
                       hipStream_t s);
+// np * nsplit partials [cout][taps * cin]; nsplit from bw_conv_wgrad_split (partials
+// available: nparts >= np)
+int bw_conv_wgrad_split(int cin, int cout, int KS, int Do, int np, int nparts);
 hipError_t bw_conv_wgrad(const float *X, int D, int xstride, int cin, const float *dY, int Do, int ystride, int cout,
-                         int KS, int S, int np, float *part, hipStream_t s);
+                         int KS, int S, int np, int nsplit, float *part, hipStream_t s);
+// dY rows of ystride (a multiple of 8) channels, zero past cout
 hipError_t bw_conv_dgrad(const float *dY, int Do, int ystride, int cout, const float *WT, int cin, int KS, int S, int D,
                          int xstride, int np, float *dX, hipStream_t s);
 hipError_t bw_fold_grad(const float *dWf, const float *dbf, const float *W, const float *b, const float *gamma,
