@@ -109,6 +109,9 @@ struct cf_ctx {
   std::vector<DevBuf> act;  // t_1 .. t_L
   std::vector<DevBuf> dact; // backward: gradients of t_1 .. t_L
   DevBuf bw_sg, bw_cnn, bw_part, bw_head;  // backward scratch
+  DevBuf bw_sum;                           // spectrum of one layer's weight gradient
+  std::vector<DevBuf> gspec_t;             // per layer: weight spectra of the data gradient,
+  std::vector<char> gspec_t_set;           // ... built by the first backward call that takes them
   DevBuf splatwork;                        // per-atom normalisers and per-tile atom lists
   DevBuf convwork;          // scratch of the frequency-domain conv (spectra)
   std::map<int, std::vector<int>> variants;  // per G
@@ -882,7 +885,9 @@ void free_ctx(cf_ctx *c) {
     if (b.p) (void)hipFree(b.p);
   for (auto &b : c->dact)
     if (b.p) (void)hipFree(b.p);
-  DevBuf *bw[] = {&c->bw_sg, &c->bw_cnn, &c->bw_part, &c->bw_head, &c->splatwork};
+  for (auto &b : c->gspec_t)
+    if (b.p) (void)hipFree(b.p);
+  DevBuf *bw[] = {&c->bw_sg, &c->bw_cnn, &c->bw_part, &c->bw_head, &c->bw_sum, &c->splatwork};
   for (DevBuf *b : bw)
     if (b->p) (void)hipFree(b->p);
   if (c->convwork.p) (void)hipFree(c->convwork.p);
@@ -1224,6 +1229,32 @@ int cf_backward(cf_ctx *c, const cf_pose_batch *b, int G, const float *dscore, f
     nparts = 8;
   if ((rc = ensure(c, c->bw_cnn, (size_t)(nparts * wq + cnn_rest) * sizeof(float)))) return rc;
 
+  // stride-1 layers in the frequency domain: weight spectra of the data gradient, the
+  // weight gradient's spectrum and the plane spectra, where they leave half the budget free
+  // (later calls of this context keep their room); the direct kernels otherwise
+  std::vector<char> spectral(L, 0);
+  {
+    int64_t keep = 0, sum = 0, work = 0;
+    auto more = [](const DevBuf &b, int64_t need) { return std::max<int64_t>(0, need - (int64_t)b.n); };
+    if ((int)c->gspec_t.size() != L) c->gspec_t.resize(L), c->gspec_t_set.assign(L, 0);
+    for (int i = 0; i < L; ++i) {
+      const auto &Lr = c->conv[i];
+      if (!cf::fft_grad_ok(Lr, dims[i], chunk)) continue;
+      const int64_t g = i > 0 ? more(c->gspec_t[i], cf::fft_grad_layer(Lr).gspec_bytes) : 0;
+      const int64_t sm = std::max(sum, cf::fft_grad_sum_bytes(Lr)), wk = std::max(work, cf::fft_grad_work_bytes(Lr, dims[i], chunk));
+      if (2 * (c->scratch_bytes + c->weight_bytes + keep + g + more(c->bw_sum, sm) + more(c->convwork, wk)) > c->budget)
+        continue;
+      keep += g;
+      sum = sm;
+      work = wk;
+      spectral[i] = 1;
+    }
+    if (sum && (rc = ensure(c, c->bw_sum, (size_t)sum))) return rc;
+    if (work && (rc = ensure(c, c->convwork, (size_t)work))) return rc;
+    for (int i = 1; i < L; ++i)
+      if (spectral[i] && (rc = ensure(c, c->gspec_t[i], (size_t)cf::fft_grad_layer(c->conv[i]).gspec_bytes))) return rc;
+  }
+
   const float *P = c->raw;
   const TrainOffsets &T = c->tr;
   float *pt = (float *)c->bw_part.p;
@@ -1345,17 +1376,30 @@ int cf_backward(cf_ctx *c, const cf_pose_batch *b, int G, const float *dscore, f
       const float *X = i == 0 ? (const float *)c->grid.p : (const float *)c->act[i - 1].p;
       const int xs = i == 0 ? grid_cpad(c) : c->conv[i - 1].cout_store;
       const int64_t Q = (int64_t)taps * Lr.cin;
-      const int nsplit = cf::bw_conv_wgrad_split(Lr.cin, Lr.cout, Lr.k, dims[i + 1], np, nparts);
-      CF_HIP(cf::bw_conv_wgrad(X, dims[i], xs, Lr.cin, dY, dims[i + 1], Lr.cout_store, Lr.cout, Lr.k, Lr.stride, np,
-                               nsplit, part, s));
-      CF_HIP(cf::bw_outer(part, (int)(Lr.cout * Q), nullptr, 0, np * nsplit, (int)(Lr.cout * Q), 1, dWf, 1, 0, pt, s));
+      const bool fft = spectral[i] != 0;
+      if (fft) {
+        CF_HIP(cf::launch_fft_wgrad(Lr, X, dY, np, dims[i], c->convwork.p, c->bw_sum.p, dWf, s));
+      } else {
+        const int nsplit = cf::bw_conv_wgrad_split(Lr.cin, Lr.cout, Lr.k, dims[i + 1], np, nparts);
+        CF_HIP(cf::bw_conv_wgrad(X, dims[i], xs, Lr.cin, dY, dims[i + 1], Lr.cout_store, Lr.cout, Lr.k, Lr.stride, np,
+                                 nsplit, part, s));
+        CF_HIP(cf::bw_outer(part, (int)(Lr.cout * Q), nullptr, 0, np * nsplit, (int)(Lr.cout * Q), 1, dWf, 1, 0, pt, s));
+      }
       const bool bn = d.bn != 0;
       CF_HIP(cf::bw_fold_grad(dWf, dbf, P + T.conv_w[i], P + T.conv_b[i], bn ? P + T.bn_g[i] : nullptr,
                               bn ? P + T.bn_m[i] : nullptr, bn ? P + T.bn_v[i] : nullptr, Lr.cout, Lr.cin, taps,
                               grad + T.conv_w[i], grad + T.conv_b[i], bn ? grad + T.bn_g[i] : nullptr,
                               bn ? grad + T.bn_b[i] : nullptr, bn ? grad + T.bn_m[i] : nullptr,
                               bn ? grad + T.bn_v[i] : nullptr, s));
-      if (i > 0) {
+      if (i > 0 && fft) {
+        cf::ConvLayer Lt = cf::fft_grad_layer(Lr);
+        Lt.gspec = c->gspec_t[i].p;
+        if (!c->gspec_t_set[i]) {
+          CF_HIP(cf::fft_grad_prepare(Lt, P + T.conv_w[i], bn ? P + T.bn_g[i] : nullptr, bn ? P + T.bn_v[i] : nullptr, WT, s));
+          c->gspec_t_set[i] = 1;
+        }
+        CF_HIP(cf::launch_fft_dgrad(Lt, np, dims[i], c->convwork.p, (float *)c->dact[i - 1].p, s));
+      } else if (i > 0) {
         CF_HIP(cf::bw_fold_wt(P + T.conv_w[i], bn ? P + T.bn_g[i] : nullptr, bn ? P + T.bn_v[i] : nullptr, Lr.cout,
                               Lr.cin, taps, WT, s));
         CF_HIP(cf::bw_conv_dgrad(dY, dims[i + 1], Lr.cout_store, Lr.cout, WT, Lr.cin, Lr.k, Lr.stride, dims[i], xs, np,

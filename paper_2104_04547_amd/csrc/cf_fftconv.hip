@@ -74,6 +74,7 @@ __host__ __device__ constexpr int plane_lds_bytes(int D, bool f32 = false) {
 constexpr int kZpBytes = 32 * 8 * 8;
 
 typedef float float2v __attribute__((ext_vector_type(2)));
+typedef float accv16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
 // two floats rounded to bf16 (nearest even) by one conversion, lo in the low half
 __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
@@ -553,8 +554,9 @@ __global__ __launch_bounds__(256) void k_fft_fwd2d(const void *__restrict__ in_v
 // layout [P][D][D][D][cout_store].  The spectrum's DC and Nyquist columns travel
 // packed, as in the fused transform.  NTL > 1 (overlap-save tiles): the plane of
 // edge NTL * D is NTL x NTL tiles of D x D outputs, each with its own spectrum;
-// grid (NTL * D, np * NTL^2, nco), np counting (pose, tile) planes.
-template <int DT, bool F32, int NTL = 1>
+// grid (NTL * D, np * NTL^2, nco), np counting (pose, tile) planes.  GRAD (a data
+// gradient, float32): no bias, residual or ReLU; the plane is added to out.
+template <int DT, bool F32, int NTL = 1, bool GRAD = false>
 __global__ __launch_bounds__(256) void k_fft_inv2d(const void *__restrict__ ys_v, const float *__restrict__ bias,
                                                     const void *__restrict__ res_v, void *__restrict__ out_v, int np,
                                                     int D_rt, int nco, int cout_store) {
@@ -602,7 +604,7 @@ __global__ __launch_bounds__(256) void k_fft_inv2d(const void *__restrict__ ys_v
   float *O = reinterpret_cast<float *>(T);  // [x][y (pitch D + 1)][8] conv result + bias
   if (roww) {
     constexpr float kScale = 1.0f / (kN * kN);
-    const float b0 = bias[chunk * 8 + c0], b1 = bias[chunk * 8 + c0 + 1];
+    const float b0 = GRAD ? 0.0f : bias[chunk * 8 + c0], b1 = GRAD ? 0.0f : bias[chunk * 8 + c0 + 1];
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
       const int x = 16 * h + j;
@@ -619,13 +621,14 @@ __global__ __launch_bounds__(256) void k_fft_inv2d(const void *__restrict__ ys_v
     const float4 f1 = *reinterpret_cast<const float4 *>(O + (xx * DP + yy) * 8 + 4);
     f[0] = f0.x; f[1] = f0.y; f[2] = f0.z; f[3] = f0.w; f[4] = f1.x; f[5] = f1.y; f[6] = f1.z; f[7] = f1.w;
     if constexpr (F32) {
-      if (res) {
-        const float4 r0 = *reinterpret_cast<const float4 *>(res + base + v * cout_store);
-        const float4 r1 = *reinterpret_cast<const float4 *>(res + base + v * cout_store + 4);
+      if (GRAD || res) {
+        const float *add = GRAD ? (const float *)out : (const float *)res;
+        const float4 r0 = *reinterpret_cast<const float4 *>(add + base + v * cout_store);
+        const float4 r1 = *reinterpret_cast<const float4 *>(add + base + v * cout_store + 4);
         f[0] += r0.x; f[1] += r0.y; f[2] += r0.z; f[3] += r0.w; f[4] += r1.x; f[5] += r1.y; f[6] += r1.z; f[7] += r1.w;
       }
 #pragma unroll
-      for (int qq = 0; qq < 8; ++qq) f[qq] = f[qq] > 0.0f ? f[qq] : 0.0f;
+      for (int qq = 0; qq < 8; ++qq) f[qq] = GRAD || f[qq] > 0.0f ? f[qq] : 0.0f;
       float4 *dst = reinterpret_cast<float4 *>(out + base + v * cout_store);
       dst[0] = make_float4(f[0], f[1], f[2], f[3]);
       dst[1] = make_float4(f[4], f[5], f[6], f[7]);
@@ -1132,6 +1135,174 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void k
   }
 }
 
+// ---------------------------------------------------------------- gradients (float32)
+
+// Weight gradient per frequency column.  dW(co, ci, dz, dy, dx) is a correlation of the
+// layer's input X with the output gradient dY; in the plane spectra it is, per column,
+//   S(dz, ci, co) = sum_{pose, z} X(z + dz - p, ci) conj(dY(z, co)),
+// a complex product with K = (pose, z): one workgroup per column, a wave per 32 x 32 block
+// of (ci, co) with all KS shifts in accumulators (real and imaginary part), so that a step
+// of two z rows takes 4 KS matrix instructions for two dY fragments and two new X rows
+// (the other shifts' rows move down in registers).  Rows of the poses in turn through LDS.
+// What bounds it: the float32 matrix instruction (3.0 GFLOP per pose at 24^3, 64 -> 64, k 7,
+// against 38.8 for the direct sum): 315 us for 8 poses, 76 TFLOP/s.  With the transforms,
+// the taps below and the data gradient's z-correlation a layer's two gradients take 0.8 ms
+// against 7.5 in the direct kernels.
+// S: [col][re | im][dz][ci][co].
+template <int KS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_fft_zwgrad(
+    const float *__restrict__ xs, const float *__restrict__ ysp, float *__restrict__ S, int np, int D, int cin,
+    int cout) {
+  extern __shared__ __attribute__((aligned(16))) float zlds[];
+  constexpr int P = (KS - 1) / 2;
+  const int col = blockIdx.x;
+  const int xrow = 2 * cin, yrow = 2 * cout, xp = xrow + 8, yp = yrow + 8;  // floats, LDS pitches
+  const int De = (D + 1) / 2 * 2;
+  float *sx = zlds, *sy = zlds + (De + KS - 1) * xp;
+  const int tid = threadIdx.x, nth = blockDim.x, lane = tid & 63, wave = tid >> 6;
+  const int khalf = lane >> 5, lrow = lane & 31;
+  const int nbi = cin / 32, ib = wave % nbi, ob = wave / nbi;
+  auto at = [](int c) { return (c >> 3) * 16 + (c & 7); };  // re of channel c in a spectrum row
+  const int xo = at(ib * 32 + lrow), yo = at(ob * 32 + lrow);
+  accv16 re[KS], im[KS];
+#pragma unroll
+  for (int d = 0; d < KS; ++d) re[d] = im[d] = accv16{};
+  for (int p = 0; p < np; ++p) {
+    __syncthreads();
+    // X rows z = -P .. De + P - 1 and dY rows 0 .. De - 1, zero outside the grid
+    const float *xg = xs + ((int64_t)col * np + p) * D * xrow, *yg = ysp + ((int64_t)col * np + p) * D * yrow;
+    for (int e = tid; e < (De + KS - 1) * (xrow / 4); e += nth) {
+      const int r = e / (xrow / 4), q = e % (xrow / 4), z = r - P;
+      *reinterpret_cast<float4 *>(sx + r * xp + 4 * q) =
+          z >= 0 && z < D ? *reinterpret_cast<const float4 *>(xg + z * xrow + 4 * q) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    for (int e = tid; e < De * (yrow / 4); e += nth) {
+      const int r = e / (yrow / 4), q = e % (yrow / 4);
+      *reinterpret_cast<float4 *>(sy + r * yp + 4 * q) =
+          r < D ? *reinterpret_cast<const float4 *>(yg + r * yrow + 4 * q) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    __syncthreads();
+    float xr[KS], xi[KS];  // rows z + khalf + d of this lane's ci
+#pragma unroll
+    for (int d = 0; d < KS; ++d) {
+      xr[d] = sx[(khalf + d) * xp + xo];
+      xi[d] = sx[(khalf + d) * xp + xo + 8];
+    }
+    for (int z = 0; z < De; z += 2) {
+      const float yr = sy[(z + khalf) * yp + yo], yi = sy[(z + khalf) * yp + yo + 8], ny = -yi;
+#pragma unroll
+      for (int d = 0; d < KS; ++d) {
+        re[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(xr[d], yr, re[d], 0, 0, 0);
+        im[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(xi[d], yr, im[d], 0, 0, 0);
+        re[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(xi[d], yi, re[d], 0, 0, 0);
+        im[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(xr[d], ny, im[d], 0, 0, 0);
+      }
+      if (z + 2 < De) {
+#pragma unroll
+        for (int d = 0; d < KS; ++d) {
+          xr[d] = d + 2 < KS ? xr[(d + 2) % KS] : sx[(z + 2 + khalf + d) * xp + xo];
+          xi[d] = d + 2 < KS ? xi[(d + 2) % KS] : sx[(z + 2 + khalf + d) * xp + xo + 8];
+        }
+      }
+    }
+  }
+  float *o = S + (int64_t)col * 2 * KS * cin * cout;
+#pragma unroll
+  for (int d = 0; d < KS; ++d)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int ci = ib * 32 + 8 * (j >> 2) + 4 * khalf + (j & 3);
+      const int64_t w = ((int64_t)d * cin + ci) * cout + ob * 32 + lrow;
+      o[w] = re[d][j];
+      o[(int64_t)KS * cin * cout + w] = im[d][j];
+    }
+}
+
+// The k x k taps of every (dz, ci, co) from its 544 columns:
+//   dW(dy, dx) = 1/1024 sum_{ky, kx} w_kx Re(S e^{2 pi i ((dy - p) ky + (dx - p) kx) / 32}),
+// w = 1 at kx 0 and 16, else 2 (the Hermitian half).  Wave g of a workgroup takes the kx = g
+// mod 4 of 64 elements, ky first into KS partial sums, and the waves' taps are added in
+// order.  Reads S once (125 MB at 64 -> 64, k 7: 73 us).  dWf: [co][t * cin + ci].
+template <int KS>
+__global__ __launch_bounds__(256) void k_fft_wgrad_taps(const float *__restrict__ S, float *__restrict__ dWf, int cin,
+                                                       int cout) {
+  constexpr int P = (KS - 1) / 2;
+  __shared__ float red[4][KS * KS][64];
+  const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+  const int64_t plane = (int64_t)KS * cin * cout, e = (int64_t)blockIdx.x * 64 + lane;
+  float out[KS][KS];
+#pragma unroll
+  for (int a = 0; a < KS; ++a)
+#pragma unroll
+    for (int b = 0; b < KS; ++b) out[a][b] = 0.0f;
+  for (int kx = g; kx < kNX; kx += 4) {
+    // sums over ky of Sr, Si against cos and sin of m ky: the taps p + m and p - m share them
+    float rc[P + 1], rs[P + 1], ic[P + 1], is[P + 1];
+#pragma unroll
+    for (int m = 0; m <= P; ++m) rc[m] = rs[m] = ic[m] = is[m] = 0.0f;
+    const float *s0 = S + (int64_t)kx * 2 * plane + e;
+#pragma unroll
+    for (int ky = 0; ky < kN; ++ky) {
+      const float a = s0[(int64_t)ky * kNX * 2 * plane], b = s0[((int64_t)ky * kNX * 2 + 1) * plane];
+      rc[0] += a;
+      ic[0] += b;
+#pragma unroll
+      for (int m = 1; m <= P; ++m) {
+        const int ph = (m * ky) % 32;
+        const float c = ph < 16 ? kFftCos32[ph & 15] : -kFftCos32[ph & 15];
+        const float s = ph < 16 ? kFftSin32[ph & 15] : -kFftSin32[ph & 15];
+        rc[m] = fmaf(a, c, rc[m]);
+        rs[m] = fmaf(b, s, rs[m]);
+        ic[m] = fmaf(b, c, ic[m]);
+        is[m] = fmaf(a, s, is[m]);
+      }
+    }
+    const float w = (kx == 0 || kx == kNX - 1 ? 1.0f : 2.0f) / (kN * kN);
+    float cx[P + 1], sx[P + 1];
+#pragma unroll
+    for (int m = 0; m <= P; ++m) {
+      const int ph = (m * kx) % 32;
+      cx[m] = w * (ph < 16 ? kFftCos32[ph & 15] : -kFftCos32[ph & 15]);
+      sx[m] = w * (ph < 16 ? kFftSin32[ph & 15] : -kFftSin32[ph & 15]);
+    }
+#pragma unroll
+    for (int a = 0; a < KS; ++a) {
+      const int m = a < P ? P - a : a - P;
+      const float pr = a < P ? rc[m] + rs[m] : rc[m] - rs[m], pi = a < P ? ic[m] - is[m] : ic[m] + is[m];
+#pragma unroll
+      for (int b = 0; b < KS; ++b) {
+        const int n = b < P ? P - b : b - P;
+        out[a][b] = fmaf(pr, cx[n], out[a][b]);
+        out[a][b] = fmaf(b < P ? pi : -pi, sx[n], out[a][b]);
+      }
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < KS; ++a)
+#pragma unroll
+    for (int b = 0; b < KS; ++b) red[g][a * KS + b][lane] = out[a][b];
+  __syncthreads();
+  for (int i = threadIdx.x; i < KS * KS * 64; i += 256) {
+    const int l = i & 63, t = i >> 6;
+    const int64_t el = (int64_t)blockIdx.x * 64 + l;
+    const int co = (int)(el % cout), ci = (int)((el / cout) % cin), dz = (int)(el / ((int64_t)cout * cin));
+    dWf[((int64_t)co * KS * KS * KS + dz * KS * KS + t) * cin + ci] = red[0][t][l] + red[1][t][l] + red[2][t][l] + red[3][t][l];
+  }
+}
+
+// W'[ci][co][flipped tap] = W[co][ci][tap] a[co] (a = gamma / sqrt(var + eps) with
+// BatchNorm, else 1): the data gradient's correlation as a conv layer of its own
+__global__ __launch_bounds__(256) void k_fft_flip(const float *__restrict__ W, const float *__restrict__ gamma,
+                                                  const float *__restrict__ var, int cout, int cin, int taps,
+                                                  float *__restrict__ out) {
+  const int64_t n = (int64_t)cout * cin * taps;
+  for (int64_t e = blockIdx.x * (int64_t)256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) {
+    const int t = (int)(e % taps), co = (int)((e / taps) % cout), ci = (int)(e / ((int64_t)taps * cout));
+    const float a = gamma ? (float)((double)gamma[co] / sqrt((double)var[co] + 1e-5)) : 1.0f;
+    out[e] = W[((int64_t)co * cin + ci) * taps + taps - 1 - t] * a;
+  }
+}
+
 // ---------------------------------------------------------------- weights
 
 // One thread per (col, chunk, dz, 32-column block, lane): the 8 values of one MFMA
@@ -1183,6 +1354,18 @@ int nch_of(const ConvLayer &L) { return (L.cin + 7) / 8; }
 size_t fft_lds_bytes(int D, bool f32) { return (size_t)plane_lds_bytes(D, f32) + kZpBytes; }
 int nbt_of(const ConvLayer &L) { return L.cout * 2 / 32; }
 int esz_of(const ConvLayer &L) { return L.spec_f32 ? 4 : 2; }
+
+void launch_fwd2d(const void *in, void *xs, int np, int D, int cin_pad, int nch, bool f32, hipStream_t s) {
+#define CF_FWD(DT, F)                                                                               \
+  hipLaunchKernelGGL((k_fft_fwd2d<DT, F>), dim3(D, np, nch), dim3(256), fft_lds_bytes(D, F), s, in, xs, np, D, \
+                     cin_pad, nch)
+  if (f32) {
+    if (D == 24) CF_FWD(24, true); else if (D == 16) CF_FWD(16, true); else if (D == 12) CF_FWD(12, true); else CF_FWD(0, true);
+  } else {
+    if (D == 24) CF_FWD(24, false); else if (D == 16) CF_FWD(16, false); else if (D == 12) CF_FWD(12, false); else CF_FWD(0, false);
+  }
+#undef CF_FWD
+}
 
 // overlap-save tiling for the grids of edge 32 (2 x 2 tiles of 16 x 16 outputs per
 // plane, each through a window of 16 + k - 1 <= 32 positions)
@@ -1307,15 +1490,7 @@ hipError_t launch_fft_conv(const ConvLayer &L, const void *in, const void *res, 
     }
 #undef CF_FWDT
   } else if (stage < 0 || stage == 0) {
-#define CF_FWD(DT, F)                                                                               \
-  hipLaunchKernelGGL((k_fft_fwd2d<DT, F>), dim3(D, np, nch), dim3(256), fft_lds_bytes(D, F), s, in, xs, np, D, \
-                     L.cin_pad, nch)
-    if (f32) {
-      if (D == 24) CF_FWD(24, true); else if (D == 16) CF_FWD(16, true); else if (D == 12) CF_FWD(12, true); else CF_FWD(0, true);
-    } else {
-      if (D == 24) CF_FWD(24, false); else if (D == 16) CF_FWD(16, false); else if (D == 12) CF_FWD(12, false); else CF_FWD(0, false);
-    }
-#undef CF_FWD
+    launch_fwd2d(in, xs, np, D, L.cin_pad, nch, f32, s);
   }
   if ((stage < 0 || stage == 1) && f32) {
     const int ppb = kRowsZH / D;
@@ -1381,6 +1556,78 @@ hipError_t launch_fft_conv(const ConvLayer &L, const void *in, const void *res, 
     }
 #undef CF_INV
   }
+  return hipGetLastError();
+}
+
+
+// ---- gradients ----
+
+ConvLayer fft_grad_layer(const ConvLayer &L) {
+  ConvLayer G = L;
+  G.cin = L.cout;
+  G.cin_pad = L.cout_store;
+  G.cout = L.cin;
+  G.cout_store = L.cin_pad;
+  G.res_src = -1;
+  G.gspec = nullptr;
+  G.gspec_bytes = 0;
+  if (fft_conv_layer_ok(G)) G.gspec_bytes = fft_conv_gspec_bytes(G);
+  return G;
+}
+
+bool fft_grad_ok(const ConvLayer &L, int D, int np) {
+  if (!L.spec_f32 || !fft_conv_ok(L, D) || fft_tiled(L, D) || (L.cin != 32 && L.cin != 64)) return false;
+  ConvLayer G = fft_grad_layer(L);
+  if (!fft_conv_layer_ok(G)) return false;
+  G.gspec = L.gspec;  // shape test only
+  if (!fft_conv_ok(G, D)) return false;
+  // The spectra of the weights and of their gradient cost the same for any batch (64 -> 64,
+  // k 7: ~0.2 ms), the direct kernels k^3 D^3 per pose: level near k^2 D^3 np = 10^5.
+  return (int64_t)L.k * L.k * D * D * D * np >= 200000;
+}
+
+int64_t fft_grad_work_bytes(const ConvLayer &L, int D, int np) {
+  return (fft_spec_in_elems(D, np) + (int64_t)kCols * np * D * (std::max(L.cin, L.cout) / 8) * 16) * 4;
+}
+int64_t fft_grad_sum_bytes(const ConvLayer &L) { return (int64_t)kCols * 2 * L.k * L.cin * L.cout * 4; }
+
+hipError_t fft_grad_prepare(ConvLayer &G, const float *W, const float *gamma, const float *var, float *staging,
+                            hipStream_t s) {
+  const int64_t n = (int64_t)G.cin * G.cout * G.k * G.k * G.k;
+  hipLaunchKernelGGL(k_fft_flip, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 65536)), dim3(256), 0, s, W, gamma,
+                     var, G.cin, G.cout, G.k * G.k * G.k, staging);
+  return fft_conv_prepare(G, staging, s);
+}
+
+hipError_t launch_fft_wgrad(const ConvLayer &L, const float *X, const float *dY, int np, int D, void *work, void *sum,
+                            float *dWf, hipStream_t s) {
+  float *ysp = reinterpret_cast<float *>(work), *xsp = ysp + fft_spec_in_elems(D, np);
+  launch_fwd2d(dY, ysp, np, D, L.cout_store, L.cout / 8, true, s);
+  launch_fwd2d(X, xsp, np, D, L.cin_pad, L.cin / 8, true, s);
+  const int De = (D + 1) / 2 * 2;
+  const size_t lds = sizeof(float) * ((size_t)(De + L.k - 1) * (2 * L.cin + 8) + (size_t)De * (2 * L.cout + 8));
+  const dim3 blk(64 * (L.cin / 32) * (L.cout / 32)), taps((unsigned)(L.k * L.cin * L.cout / 64));
+  float *S = reinterpret_cast<float *>(sum);
+#define CF_ZW(KS)                                                                                             \
+  do {                                                                                                        \
+    hipLaunchKernelGGL(k_fft_zwgrad<KS>, dim3(kCols), blk, lds, s, xsp, ysp, S, np, D, L.cin, L.cout);        \
+    hipLaunchKernelGGL(k_fft_wgrad_taps<KS>, taps, dim3(256), 0, s, S, dWf, L.cin, L.cout);                   \
+  } while (0)
+  if (L.k == 7) CF_ZW(7); else if (L.k == 5) CF_ZW(5); else CF_ZW(3);
+#undef CF_ZW
+  return hipGetLastError();
+}
+
+hipError_t launch_fft_dgrad(const ConvLayer &G, int np, int D, void *work, float *dX, hipStream_t s) {
+  hipError_t e = launch_fft_conv(G, nullptr, nullptr, nullptr, np, D, work, s, 1);
+  if (e != hipSuccess) return e;
+  const float *ys = reinterpret_cast<const float *>(work) + fft_spec_in_elems(D, np);
+  const int nco = G.cout / 8;
+#define CF_INVG(DT)                                                                                               \
+  hipLaunchKernelGGL((k_fft_inv2d<DT, true, 1, true>), dim3(D, np, nco), dim3(256), fft_lds_bytes(D, true), s, ys, \
+                     nullptr, nullptr, dX, np, D, nco, G.cout_store)
+  if (D == 24) CF_INVG(24); else if (D == 16) CF_INVG(16); else if (D == 12) CF_INVG(12); else CF_INVG(0);
+#undef CF_INVG
   return hipGetLastError();
 }
 

@@ -167,6 +167,21 @@ hipError_t launch_fft_mid(const ConvLayer &L, const ConvLayer &Ln, const void *r
 // algorithmic FLOP and HBM bytes of one stage for n_poses
 void fft_conv_stage_cost(int stage, const ConvLayer &L, int D, int n_poses, double *flop, double *bytes);
 bool conv_variant_is_fft(int v);
+// gradients of stride-1 layers in the frequency domain (float32): the layer whose forward
+// correlation is L's data gradient (weights flipped and transposed, gspec to be set by the
+// caller and filled by fft_grad_prepare), and whether the path applies to a batch
+ConvLayer fft_grad_layer(const ConvLayer &L);
+bool fft_grad_ok(const ConvLayer &L, int D, int n_poses);
+int64_t fft_grad_work_bytes(const ConvLayer &L, int D, int n_poses);  // spectra of dY and X
+int64_t fft_grad_sum_bytes(const ConvLayer &L);                       // spectrum of the weight gradient
+// staging: cin * cout * k^3 floats
+hipError_t fft_grad_prepare(ConvLayer &G, const float *W, const float *gamma, const float *var, float *staging,
+                            hipStream_t s);
+// weight gradient summed over the poses, [co][tap * cin + ci]; leaves dY's spectrum in work
+// for launch_fft_dgrad, which adds the data gradient to dX
+hipError_t launch_fft_wgrad(const ConvLayer &L, const float *X, const float *dY, int n_poses, int D, void *work,
+                            void *sum, float *dWf, hipStream_t s);
+hipError_t launch_fft_dgrad(const ConvLayer &G, int n_poses, int D, void *work, float *dX, hipStream_t s);
 
 hipError_t launch_pool_dense(const void *act, int bf16, int n_poses, int vox, int cstride, int c,
                              const float *dense_w, const float *dense_b, int n_dense, const float *dense2_w,

@@ -18,6 +18,11 @@ SHAPES = {
     "wide": (((19, 100, 7, 2, -1), (100, 100, 3, 1, -1), (100, 100, 3, 1, 1), (100, 34, 5, 2, -1)), 12, 2),
     # stride 1 on the grid: rows of 28 voxels
     "long": (((19, 40, 3, 1, -1), (40, 8, 5, 1, -1)), 28, 3),
+    # the frequency-domain gradients: 7^3 at 16^3 with a residual add; 3^3 and 5^3 at 24^3
+    # between 32 and 64 channels; 7^3 on an odd 13^3 grid
+    "spectral7": (((19, 64, 5, 2, -1), (64, 64, 7, 1, -1), (64, 64, 7, 1, 1)), 32, 2),
+    "spectral35": (((19, 32, 5, 2, -1), (32, 64, 3, 1, -1), (64, 32, 5, 1, -1)), 48, 2),
+    "spectral_odd": (((19, 32, 5, 2, -1), (32, 32, 5, 2, -1), (32, 32, 7, 1, -1)), 52, 2),
 }
 
 
