@@ -6,13 +6,15 @@
 // one upstream gradient per pose g_p = dL/ds_p, the vector-Jacobian product
 // sum_p g_p ds_p/dtheta for every parameter theta, in float32.
 //
-// Design: plain kernels, one output element per thread, every reduction in a
-// fixed order (row chunks, then partial sums in order), so gradients are
-// reproducible bit for bit and independent of the launch shape.
-//   * per-atom matrix products of the SG-CNN (H <= 64): one thread per output
-//     entry over a row of the weight matrix;
-//   * weight gradients sum_i U[i][a] V[i][b] over atoms / poses / voxels: row
-//     chunks into partial sums, then one pass adding the partials in order;
+// Design: every reduction in a fixed order (row chunks, then partial sums in order),
+// so gradients are reproducible bit for bit and independent of the launch shape.
+//   * per-atom matrix products of the SG-CNN and their weight gradients
+//     sum_i U[i][a] V[i][b]: 32 x 32 blocks on the float32 matrix instruction
+//     (32x32x2) straight from memory -- a few thousand atoms at widths up to 192 are
+//     cache-resident, so a product is a few microseconds of latency (one thread per
+//     output entry, each walking its row, took 97 us for 5500 atoms x 64 -> 192, the
+//     weight gradients 38 + 32 us); weight gradients into partial sums per 128 rows, then
+//     one pass adding the partials in order;
 //   * conv weight and data gradients: products on the float32 matrix instruction
 //     (32x32x2), see k_conv_wgrad and k_conv_dgrad.
 #include <algorithm>
@@ -36,31 +38,66 @@ __global__ __launch_bounds__(kT) void k_add(float *dst, const float *src, int64_
   for (int64_t i = blockIdx.x * (int64_t)kT + threadIdx.x; i < n; i += (int64_t)gridDim.x * kT) dst[i] += src[i];
 }
 
-// Y[i][j] (+)= b[j] + sum_k W[j][k] X[i][k]
+typedef float f32x16b __attribute__((ext_vector_type(16)));
+
+// Four consecutive floats from p, of which `left` exist (zero past them)
+__device__ inline float4 take4(const float *p, int left, bool aligned) {
+  if (left >= 4 && aligned) return *reinterpret_cast<const float4 *>(p);
+  return make_float4(left > 0 ? p[0] : 0.0f, left > 1 ? p[1] : 0.0f, left > 2 ? p[2] : 0.0f, left > 3 ? p[3] : 0.0f);
+}
+
+// TRANS = false: Y[i][j] (+)= b[j] + sum_k W[j][k] X[i][k], i < n, j < J, k < K
+// TRANS = true:  Y[i][j] (+)= sum_k W[k][j] X[i][k]  (the transposed product dX = dY W)
+// A wave takes 32 rows x 32 columns, a workgroup 64 x 64.  The matrix instruction adds its
+// two products one after the other like two fused multiply-adds, so with k in ascending
+// order an entry is bit for bit the plain sum (the SG-CNN's states are large sums that
+// amplify rounding: taking k out of order doubled the gradient's distance from 64 bits).
+template <bool TRANS>
 __global__ __launch_bounds__(kT) void k_rowmat(const float *__restrict__ X, int ldx, int n, int K,
                                                const float *__restrict__ W, int ldw, const float *__restrict__ b,
                                                int J, float *__restrict__ Y, int ldy, int accumulate) {
-  for (int64_t e = blockIdx.x * (int64_t)kT + threadIdx.x; e < (int64_t)n * J; e += (int64_t)gridDim.x * kT) {
-    const int i = (int)(e / J), j = (int)(e % J);
-    const float *x = X + (int64_t)i * ldx, *w = W + (int64_t)j * ldw;
-    float acc = b ? b[j] : 0.0f;
-    for (int k = 0; k < K; ++k) acc = fmaf(w[k], x[k], acc);
-    float *y = Y + (int64_t)i * ldy + j;
-    *y = accumulate ? *y + acc : acc;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, khalf = lane >> 5, lrow = lane & 31;
+  const int i0 = blockIdx.x * 64 + (wave & 1) * 32, j0 = blockIdx.y * 64 + (wave >> 1) * 32;
+  if (i0 >= n || j0 >= J) return;
+  const int i = min(i0 + lrow, n - 1), j = min(j0 + lrow, J - 1);  // rows past the end: read, not stored
+  const float *x = X + (int64_t)i * ldx, *w = TRANS ? W + j : W + (int64_t)j * ldw;
+  const bool xa = ldx % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
+  const bool wa = !TRANS && ldw % 4 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0;
+  const float bj = b ? b[j] : 0.0f;
+  f32x16b acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = bj;
+#pragma unroll 2
+  for (int k = 0; k < K; k += 8) {
+    float a[4], v[4];  // k + 2 s + khalf
+    const float4 a0 = take4(x + k, K - k, xa), a1 = take4(x + k + 4, K - k - 4, xa);
+    a[0] = khalf ? a0.y : a0.x;
+    a[1] = khalf ? a0.w : a0.z;
+    a[2] = khalf ? a1.y : a1.x;
+    a[3] = khalf ? a1.w : a1.z;
+    if (TRANS) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int kk = k + 2 * q + khalf;
+        v[q] = kk < K ? w[(int64_t)kk * ldw] : 0.0f;
+      }
+    } else {
+      const float4 w0 = take4(w + k, K - k, wa), w1 = take4(w + k + 4, K - k - 4, wa);
+      v[0] = khalf ? w0.y : w0.x;
+      v[1] = khalf ? w0.w : w0.z;
+      v[2] = khalf ? w1.y : w1.x;
+      v[3] = khalf ? w1.w : w1.z;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], v[q], acc, 0, 0, 0);
   }
-}
-
-// Y[i][k] (+)= sum_j W[j][k] X[i][j]   (the transposed product: dX = dY W)
-__global__ __launch_bounds__(kT) void k_rowmat_t(const float *__restrict__ X, int ldx, int n, int J,
-                                                 const float *__restrict__ W, int ldw, int K, float *__restrict__ Y,
-                                                 int ldy, int accumulate) {
-  for (int64_t e = blockIdx.x * (int64_t)kT + threadIdx.x; e < (int64_t)n * K; e += (int64_t)gridDim.x * kT) {
-    const int i = (int)(e / K), k = (int)(e % K);
-    const float *x = X + (int64_t)i * ldx;
-    float acc = 0.0f;
-    for (int j = 0; j < J; ++j) acc = fmaf(W[(int64_t)j * ldw + k], x[j], acc);
-    float *y = Y + (int64_t)i * ldy + k;
-    *y = accumulate ? *y + acc : acc;
+  if (j0 + lrow >= J) return;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int row = i0 + 8 * (r >> 2) + 4 * khalf + (r & 3);
+    if (row >= n) continue;
+    float *y = Y + (int64_t)row * ldy + j;
+    *y = accumulate ? *y + acc[r] : acc[r];
   }
 }
 
@@ -175,23 +212,46 @@ __global__ __launch_bounds__(kT) void k_readout_bwd(const float *__restrict__ Gp
   }
 }
 
-// C[a][b] (+)= sum_{i < n} U[i][a] V[i][b] (V = null: the column sums of U).
-// Pass 1: chunk s of kRowsPerChunk rows -> partial[s][a][b]; pass 2 adds the
-// partials in chunk order.
+// C[a][b] (+)= sum_{i < n} U[i][a] V[i][b] (V = null: the column sums of U, B = 1).
+// Pass 1: chunk s of kRowsPerChunk rows -> partial[s][a][b] (column sums here, products
+// below); pass 2 adds the partials in chunk order.
 constexpr int kRowsPerChunk = 128;
 
-__global__ __launch_bounds__(kT) void k_outer_partial(const float *__restrict__ U, int ldu,
-                                                      const float *__restrict__ V, int ldv, int n, int A, int B,
+__global__ __launch_bounds__(kT) void k_outer_partial(const float *__restrict__ U, int ldu, int n, int A,
                                                       float *__restrict__ part) {
-  const int64_t ab = (int64_t)A * B;
-  const int64_t e = blockIdx.x * (int64_t)kT + threadIdx.x;
+  const int64_t a = blockIdx.x * (int64_t)kT + threadIdx.x;
   const int s = blockIdx.y;
-  if (e >= ab) return;
-  const int a = (int)(e / B), b = (int)(e % B);
+  if (a >= A) return;
   const int i0 = s * kRowsPerChunk, i1 = min(n, i0 + kRowsPerChunk);
   float acc = 0.0f;
-  for (int i = i0; i < i1; ++i) acc = fmaf(U[(int64_t)i * ldu + a], V ? V[(int64_t)i * ldv + b] : 1.0f, acc);
-  part[(int64_t)s * ab + e] = acc;
+#pragma unroll 16
+  for (int i = i0; i < i1; ++i) acc += U[(int64_t)i * ldu + a];
+  part[(int64_t)s * A + a] = acc;
+}
+
+// The same partials by matrix instruction (V given): a wave takes 32 x 32 entries (a, b) of
+// one chunk, two rows a step.
+__global__ __launch_bounds__(kT) void k_outer_mfma(const float *__restrict__ U, int ldu, const float *__restrict__ V,
+                                                   int ldv, int n, int A, int B, float *__restrict__ part) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, khalf = lane >> 5, lrow = lane & 31;
+  const int nbb = (B + 31) / 32;
+  const int blk = blockIdx.x * 4 + wave, a0 = blk / nbb * 32, b0 = blk % nbb * 32, s = blockIdx.y;
+  if (a0 >= A) return;
+  const int a = min(a0 + lrow, A - 1), b = min(b0 + lrow, B - 1);
+  const int i0 = s * kRowsPerChunk, i1 = min(n, i0 + kRowsPerChunk);
+  f32x16b acc = {};
+#pragma unroll 8
+  for (int i = i0; i < i1; i += 2) {
+    const int r = i + khalf;
+    const float u = r < i1 ? U[(int64_t)r * ldu + a] : 0.0f, v = r < i1 ? V[(int64_t)r * ldv + b] : 0.0f;
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(u, v, acc, 0, 0, 0);
+  }
+  if (b0 + lrow >= B) return;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int row = a0 + 8 * (r >> 2) + 4 * khalf + (r & 3);
+    if (row < A) part[(int64_t)s * A * B + (int64_t)row * B + b] = acc[r];
+  }
 }
 
 __global__ __launch_bounds__(kT) void k_outer_sum(const float *__restrict__ part, int nchunk, int A, int B,
@@ -200,23 +260,50 @@ __global__ __launch_bounds__(kT) void k_outer_sum(const float *__restrict__ part
   const int64_t e = blockIdx.x * (int64_t)kT + threadIdx.x;
   if (e >= ab) return;
   float acc = 0.0f;
+#pragma unroll 16
   for (int s = 0; s < nchunk; ++s) acc += part[(int64_t)s * ab + e];
   float *c = C + (e / B) * ldc + (e % B);
   *c = accumulate ? *c + acc : acc;
 }
 
+// ... for few entries and many chunks (a layer's bias gradient: 64 entries, hundreds of
+// chunks): a wave per entry, lane q the chunks q, q + 64, ..., then the lanes in a fixed tree
+__global__ __launch_bounds__(kT) void k_outer_sum_wave(const float *__restrict__ part, int nchunk, int A, int B,
+                                                       float *__restrict__ C, int ldc, int accumulate) {
+  const int64_t ab = (int64_t)A * B;
+  const int64_t e = blockIdx.x * (int64_t)(kT / 64) + (threadIdx.x >> 6);
+  if (e >= ab) return;
+  const int lane = threadIdx.x & 63;
+  float acc = 0.0f;
+#pragma unroll 4
+  for (int s = lane; s < nchunk; s += 64) acc += part[(int64_t)s * ab + e];
+  for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o, 64);
+  float *c = C + (e / B) * ldc + (e % B);
+  if (lane == 0) *c = accumulate ? *c + acc : acc;
+}
+
 // ---- 3D-CNN ----
 
-// pool[p][c] = mean over the voxels of act[p][v][c] (voxels in order)
-__global__ __launch_bounds__(kT) void k_pool_mean(const float *__restrict__ act, int np, int64_t vox, int cstride,
-                                                  int C, float *__restrict__ pool) {
-  const int64_t e = blockIdx.x * (int64_t)kT + threadIdx.x;
-  if (e >= (int64_t)np * C) return;
-  const int p = (int)(e / C), c = (int)(e % C);
-  const float *a = act + (int64_t)p * vox * cstride + c;
+// pool[p][c] = mean over the voxels of act[p][v][c]: a workgroup takes 32 channels of a
+// pose, its 32 groups of threads every 32nd voxel in order, and the groups are added in order
+constexpr int kPoolT = 1024;
+__global__ __launch_bounds__(kPoolT) void k_pool_mean(const float *__restrict__ act, int64_t vox, int cstride, int C,
+                                                     float *__restrict__ pool) {
+  __shared__ float sum[kPoolT];
+  const int p = blockIdx.y, c = blockIdx.x * 32 + (threadIdx.x & 31), g = threadIdx.x >> 5;
   float acc = 0.0f;
-  for (int64_t v = 0; v < vox; ++v) acc += a[v * cstride];
-  pool[e] = acc / (float)vox;
+  if (c < C) {
+    const float *a = act + (int64_t)p * vox * cstride + c;
+#pragma unroll 8
+    for (int64_t v = g; v < vox; v += kPoolT / 32) acc += a[v * cstride];
+  }
+  sum[threadIdx.x] = acc;
+  __syncthreads();
+  if (g == 0 && c < C) {
+    float m = 0.0f;
+    for (int q = 0; q < kPoolT / 32; ++q) m += sum[q * 32 + threadIdx.x];
+    pool[(int64_t)p * C + c] = m / (float)vox;
+  }
 }
 
 // dact[p][v][c] = dpool[p][c] / vox (channels past C zero)
@@ -271,8 +358,6 @@ __global__ __launch_bounds__(kT) void k_fold_wt(const float *__restrict__ W, con
     WT[e] = v;
   }
 }
-
-typedef float f32x16b __attribute__((ext_vector_type(16)));
 
 // Weight gradient of one conv layer w.r.t. its folded weights, per pose (and, with
 // few poses, per row subset):
@@ -645,12 +730,16 @@ hipError_t bw_add(float *dst, const float *src, int64_t n, hipStream_t s) {
 }
 hipError_t bw_rowmat(const float *X, int ldx, int n, int K, const float *W, int ldw, const float *b, int J, float *Y,
                      int ldy, int accumulate, hipStream_t s) {
-  if (n > 0) hipLaunchKernelGGL(k_rowmat, grid1((int64_t)n * J), dim3(kT), 0, s, X, ldx, n, K, W, ldw, b, J, Y, ldy, accumulate);
+  if (n > 0 && J > 0)
+    hipLaunchKernelGGL(k_rowmat<false>, dim3((n + 63) / 64, (J + 63) / 64), dim3(kT), 0, s, X, ldx, n, K, W, ldw, b, J, Y,
+                       ldy, accumulate);
   return hipGetLastError();
 }
 hipError_t bw_rowmat_t(const float *X, int ldx, int n, int J, const float *W, int ldw, int K, float *Y, int ldy,
                        int accumulate, hipStream_t s) {
-  if (n > 0) hipLaunchKernelGGL(k_rowmat_t, grid1((int64_t)n * K), dim3(kT), 0, s, X, ldx, n, J, W, ldw, K, Y, ldy, accumulate);
+  if (n > 0 && K > 0)
+    hipLaunchKernelGGL(k_rowmat<true>, dim3((n + 63) / 64, (K + 63) / 64), dim3(kT), 0, s, X, ldx, n, J, W, ldw, nullptr,
+                       K, Y, ldy, accumulate);
   return hipGetLastError();
 }
 hipError_t bw_agg(const int32_t *rowp, const int32_t *col, int64_t cap, const float *S, int n, int F, float *A,
@@ -686,17 +775,24 @@ hipError_t bw_outer(const float *U, int ldu, const float *V, int ldv, int n, int
                     int accumulate, float *part, hipStream_t s) {
   const int nchunk = std::max(1, (n + kRowsPerChunk - 1) / kRowsPerChunk);
   const int64_t ab = (int64_t)A * B;
-  if (n > 0)
-    hipLaunchKernelGGL(k_outer_partial, dim3((unsigned)((ab + kT - 1) / kT), nchunk), dim3(kT), 0, s, U, ldu, V, ldv,
-                       n, A, B, part);
+  if (n > 0 && V)
+    hipLaunchKernelGGL(k_outer_mfma, dim3((unsigned)((((A + 31) / 32) * ((B + 31) / 32) + 3) / 4), nchunk), dim3(kT), 0, s,
+                       U, ldu, V, ldv, n, A, B, part);
+  else if (n > 0)
+    hipLaunchKernelGGL(k_outer_partial, dim3((unsigned)((ab + kT - 1) / kT), nchunk), dim3(kT), 0, s, U, ldu, n, A,
+                       part);
   else
     hipLaunchKernelGGL(k_fill, grid1(ab), dim3(kT), 0, s, part, ab, 0.0f);
-  hipLaunchKernelGGL(k_outer_sum, dim3((unsigned)((ab + kT - 1) / kT)), dim3(kT), 0, s, part, n > 0 ? nchunk : 1, A, B,
-                     C, ldc, accumulate);
+  if (nchunk >= 64 && ab <= 4096)
+    hipLaunchKernelGGL(k_outer_sum_wave, dim3((unsigned)((ab + kT / 64 - 1) / (kT / 64))), dim3(kT), 0, s, part, nchunk, A,
+                       B, C, ldc, accumulate);
+  else
+    hipLaunchKernelGGL(k_outer_sum, dim3((unsigned)((ab + kT - 1) / kT)), dim3(kT), 0, s, part, n > 0 ? nchunk : 1, A, B,
+                       C, ldc, accumulate);
   return hipGetLastError();
 }
 hipError_t bw_pool_mean(const float *act, int np, int64_t vox, int cstride, int C, float *pool, hipStream_t s) {
-  hipLaunchKernelGGL(k_pool_mean, grid1((int64_t)np * C), dim3(kT), 0, s, act, np, vox, cstride, C, pool);
+  hipLaunchKernelGGL(k_pool_mean, dim3((C + 31) / 32, np), dim3(kPoolT), 0, s, act, vox, cstride, C, pool);
   return hipGetLastError();
 }
 hipError_t bw_pool_seed(const float *dpool, int np, int64_t vox, int cstride, int C, float *dact, hipStream_t s) {
