@@ -395,7 +395,11 @@ __device__ inline f32x16v mm_row(const float *arow, const bf16_t *bhi, const bf1
 // One round of one stage at width H for the atoms [blk, blk + BLK) of a pose:
 // neighbour sums of the current states (cur), the round's message product, the
 // stage's GRU, the new states of those atoms written to nxt (row stride H).
-template <int H, bool F32>
+// SEP (plain form without staging): the gates' input and hidden parts in accumulators of
+// their own that start at the biases -- with k in ascending order and the matrix
+// instruction adding its two products in turn, bit for bit the sums of plain fused
+// multiply-adds, which sit closer to the 64-bit states than the merged accumulators.
+template <int H, bool F32, bool SEP>
 __device__ void sg_block(const SgWeights &W, int stage, int r, const int32_t *__restrict__ rowp,
                          const int32_t *__restrict__ colp, int64_t cap, int csr_global, int a0, int base, int64_t lb,
                          int n, int blk, const float *cur, float *nxt, float *lds, int64_t *status) {
@@ -429,14 +433,27 @@ __device__ void sg_block(const SgWeights &W, int stage, int r, const int32_t *__
     // input and hidden products in one accumulator each; the candidate keeps them
     // apart (the reset gate scales only the hidden part)
     {
-      f32x16v gr = {}, gz = {}, gin = {}, ghn = {};
+      f32x16v gr = {}, gz = {}, gin = {}, ghn = {}, hr = {}, hz = {};
       const float *mrow = &M[(mb * 32 + lrow) * LD], *hrow = &Hc[(mb * 32 + lrow) * LD];
       if constexpr (F32) {
         const float *wi = W.w_ihT[stage], *wh = W.w_hhT[stage];
+        if constexpr (SEP) {
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            gr[j] = bir;
+            gz[j] = biz;
+            gin[j] = bin;
+            hr[j] = bhr;
+            hz[j] = bhz;
+            ghn[j] = bhn;
+          }
+          hr = mm_row<H, true>(hrow, nullptr, nullptr, wh, 3 * H, ocol, khalf, hr);
+          hz = mm_row<H, true>(hrow, nullptr, nullptr, wh, 3 * H, H + ocol, khalf, hz);
+        }
         gr = mm_row<H, true>(mrow, nullptr, nullptr, wi, 3 * H, ocol, khalf, gr);
-        gr = mm_row<H, true>(hrow, nullptr, nullptr, wh, 3 * H, ocol, khalf, gr);
+        if constexpr (!SEP) gr = mm_row<H, true>(hrow, nullptr, nullptr, wh, 3 * H, ocol, khalf, gr);
         gz = mm_row<H, true>(mrow, nullptr, nullptr, wi, 3 * H, H + ocol, khalf, gz);
-        gz = mm_row<H, true>(hrow, nullptr, nullptr, wh, 3 * H, H + ocol, khalf, gz);
+        if constexpr (!SEP) gz = mm_row<H, true>(hrow, nullptr, nullptr, wh, 3 * H, H + ocol, khalf, gz);
         gin = mm_row<H, true>(mrow, nullptr, nullptr, wi, 3 * H, 2 * H + ocol, khalf, gin);
         ghn = mm_row<H, true>(hrow, nullptr, nullptr, wh, 3 * H, 2 * H + ocol, khalf, ghn);
       } else {
@@ -462,9 +479,9 @@ __device__ void sg_block(const SgWeights &W, int stage, int r, const int32_t *__
         const int row = mb * 32 + 8 * (j >> 2) + 4 * khalf + (j & 3);
         const int i = blk + row;
         if (i < n) {
-          const float rr = sigm(gr[j] + (bir + bhr));
-          const float zz = sigm(gz[j] + (biz + bhz));
-          const float nn = tanhf(gin[j] + bin + rr * (ghn[j] + bhn));
+          const float rr = SEP ? sigm(gr[j] + hr[j]) : sigm(gr[j] + (bir + bhr));
+          const float zz = SEP ? sigm(gz[j] + hz[j]) : sigm(gz[j] + (biz + bhz));
+          const float nn = SEP ? tanhf(gin[j] + rr * ghn[j]) : tanhf(gin[j] + bin + rr * (ghn[j] + bhn));
           nxt[(lb + i) * H + ocol] = (1.0f - zz) * nn + zz * Hc[row * LD + ocol];
         }
       }
@@ -508,7 +525,7 @@ __global__ __launch_bounds__(kThreads) void k_sg_embed(SgWeights W, const int32_
 }
 
 // One round: the states of cur advanced into nxt.
-template <int H, bool F32>
+template <int H, bool F32, bool SEP>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(H == 128 || F32 ? 2 : 3))) void k_sg_round(
     SgWeights W, int stage, int r, const int32_t *__restrict__ atom_off, int n_atoms, int p0, int nbx,
     const int32_t *__restrict__ rowp, const int32_t *__restrict__ colp, int64_t cap, int csr_global,
@@ -518,7 +535,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(H == 1
   int64_t lb;
   if (!sg_item(atom_off, n_atoms, p0, nbx, hcap, false, pl, b0, a0, n, base, lb, status)) return;
   for (int blk = b0 * SgTile<H>::BLK; blk < n; blk += nbx * SgTile<H>::BLK)
-    sg_block<H, F32>(W, stage, r, rowp, colp, cap, csr_global, a0, base, lb, n, blk, cur, nxt, lds, status);
+    sg_block<H, F32, SEP>(W, stage, r, rowp, colp, cap, csr_global, a0, base, lb, n, blk, cur, nxt, lds, status);
 }
 
 // ---- PotentialNet staging: the covalent stage at width HC closes with a per-atom
@@ -683,18 +700,18 @@ struct SgCall {
 };
 
 // rounds r0 .. r0 + K - 1 of a stage; cur and nxt are swapped after each
-template <int H, bool F32>
+template <int H, bool F32, bool SEP>
 hipError_t launch_rounds(const SgWeights &W, const SgCall &c, int stage, int r0, int K, float *&cur, float *&nxt,
                          hipStream_t s) {
   const size_t lds = sizeof(float) * SgTile<H>::FLOATS;
   static bool attr = false;
   if (!attr) {
-    set_lds_attr(&k_sg_round<H, F32>, lds);
+    set_lds_attr(&k_sg_round<H, F32, SEP>, lds);
     attr = true;
   }
   const int nbx = pose_blocks(c.n_atoms, c.mean_atoms, SgTile<H>::BLK);
   for (int r = r0; r < r0 + K; ++r) {
-    hipLaunchKernelGGL((k_sg_round<H, F32>), dim3((unsigned)c.n_poses * nbx), dim3(kThreads), lds, s, W, stage, r,
+    hipLaunchKernelGGL((k_sg_round<H, F32, SEP>), dim3((unsigned)c.n_poses * nbx), dim3(kThreads), lds, s, W, stage, r,
                        c.atom_off, c.n_atoms, c.p0, nbx, c.row[stage], c.col[stage], c.cap[stage], c.csr_global, cur,
                        nxt, c.hcap, c.status);
     std::swap(cur, nxt);
@@ -714,8 +731,8 @@ template <int H, bool F32>
 hipError_t launch_flat(const SgWeights &W, const SgCall &c, hipStream_t s) {
   float *cur = c.hbuf, *nxt = c.hbuf + c.hcap * H;
   hipError_t e = launch_embed<H>(W, c, cur, s);
-  if (e == hipSuccess) e = launch_rounds<H, F32>(W, c, 0, 0, W.K_c, cur, nxt, s);
-  if (e == hipSuccess) e = launch_rounds<H, F32>(W, c, 1, W.K_c, W.K_n, cur, nxt, s);
+  if (e == hipSuccess) e = launch_rounds<H, F32, F32>(W, c, 0, 0, W.K_c, cur, nxt, s);
+  if (e == hipSuccess) e = launch_rounds<H, F32, F32>(W, c, 1, W.K_c, W.K_n, cur, nxt, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_sg_readout<H, CF_NCH>), dim3(c.n_poses), dim3(kThreads), 0, s, W, c.atom_off, c.n_atoms, cur,
                      c.feat, 0, c.is_lig, c.p0, c.hcap, c.latent);
@@ -730,12 +747,12 @@ hipError_t launch_staged(const SgWeights &W, const SgCall &c, hipStream_t s) {
   float *cur = c.hbuf, *nxt = c.hbuf + c.hcap * HC, *gb = c.hbuf + 2 * c.hcap * HC;
   float *cur2 = gb + c.hcap * HC, *nxt2 = cur2 + c.hcap * HN;
   hipError_t e = launch_embed<HC>(W, c, cur, s);
-  if (e == hipSuccess) e = launch_rounds<HC, F32>(W, c, 0, 0, W.K_c, cur, nxt, s);
+  if (e == hipSuccess) e = launch_rounds<HC, F32, false>(W, c, 0, 0, W.K_c, cur, nxt, s);
   if (e != hipSuccess) return e;
   const int nbx = pose_blocks(c.n_atoms, c.mean_atoms, kEmbedRows);
   hipLaunchKernelGGL((k_sg_mid<HC, HN>), dim3((unsigned)c.n_poses * nbx), dim3(kThreads), 0, s, W, c.atom_off,
                      c.n_atoms, c.feat, c.p0, nbx, cur, gb, cur2, c.hcap, c.status);
-  e = launch_rounds<HN, F32>(W, c, 1, W.K_c, W.K_n, cur2, nxt2, s);
+  e = launch_rounds<HN, F32, false>(W, c, 1, W.K_c, W.K_n, cur2, nxt2, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_sg_readout<HN, HC>), dim3(c.n_poses), dim3(kThreads), 0, s, W, c.atom_off, c.n_atoms, cur2, gb,
                      1, c.is_lig, c.p0, c.hcap, c.latent);
