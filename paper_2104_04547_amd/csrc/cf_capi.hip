@@ -1002,7 +1002,7 @@ int cf_voxelize(cf_ctx *c, const cf_pose_batch *b, int G, void *grid_out, void *
   }
   if ((rc = ensure(c, c->splatwork, (size_t)cf::splat_work_bytes(b->n_poses, b->n_atoms, G)))) return rc;
   CF_HIP(cf::launch_splat(b->atom_off, b->n_atoms, b->xyz, b->feat, cen, 0, b->n_poses, G, grid_out, c->bf16 ? 1 : 0, 0,
-                          c->splatwork.p, b->n_atoms, c->status, s));
+                          c->splatwork.p, b->n_atoms, mean_atoms(b), c->status, s));
   return CF_OK;
 }
 
@@ -1107,7 +1107,7 @@ int cf_score_poses(cf_ctx *c, const cf_pose_batch *b, int G, float *scores, void
     {
       Range r(c, "cf.splat");
       CF_HIP(cf::launch_splat(b->atom_off, b->n_atoms, b->xyz, b->feat, cen, p0, np, G, c->grid.p, c->bf16 ? 4 : 2,
-                              grid_cpad(c), c->splatwork.p, acap, c->status, s));
+                              grid_cpad(c), c->splatwork.p, acap, mean_atoms(b), c->status, s));
     }
     tend(c, s, e, "splat", 0.0, atoms * (12.0 + 4.0 * CF_NCH) + (double)np * G * G * G * CF_NCH * elem_size(c));
     {
@@ -1268,7 +1268,7 @@ int cf_backward(cf_ctx *c, const cf_pose_batch *b, int G, const float *dscore, f
     if (!b->center)
       CF_HIP(cf::launch_centers(b->atom_off, b->n_atoms, b->xyz, b->is_lig, p0, np, (int32_t *)c->centers.p, c->status, s));
     CF_HIP(cf::launch_splat(b->atom_off, b->n_atoms, b->xyz, b->feat, cen, p0, np, G, c->grid.p, 2, grid_cpad(c),
-                            c->splatwork.p, acap, c->status, s));
+                            c->splatwork.p, acap, mean_atoms(b), c->status, s));
     if ((rc = run_cnn(c, G, np, (float *)c->cnn_lat.p, s, nullptr, true))) return rc;
     CF_HIP(cf::launch_graph(b->atom_off, b->n_atoms, b->xyz, p0, np, mean_atoms(b), d.r_cov_u, d.r_nc_u, (int32_t *)c->cov_row.p,
                             (int32_t *)c->cov_col.p, acap * 16, (int32_t *)c->nc_row.p, (int32_t *)c->nc_col.p,

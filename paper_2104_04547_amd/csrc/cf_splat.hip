@@ -6,18 +6,24 @@
 // sigma = 0.5 A truncated at 3 sigma, normalised per atom over its whole support.
 //
 // Design: a binning pass, then one workgroup per (pose, 2 x 4 x G tile).
-//   * k_splat_bin (one workgroup per pose): each atom's support box (at most 4
-//     voxels per axis) reaches at most 3 x 2 tiles; the atoms are counted per tile,
+//   * k_splat_bin, first n_poses workgroups (one per pose): each atom's support box (at
+//     most 4 voxels per axis) reaches at most 3 x 2 tiles; the atoms are counted per tile,
 //     the counts scanned and the atoms listed per tile (the order inside a list
-//     does not matter, see below), and each atom's normaliser -- the sum of its
-//     weights over the whole (unclipped) support -- is computed once, by one wave
-//     per atom, one candidate voxel per lane, as an exact integer reduction.
+//     does not matter, see below).
+//   * k_splat_bin, the other workgroups (blocks of 64 atoms): each atom's normaliser --
+//     the sum of its weights over the whole (unclipped) support -- as an exact integer
+//     sum, four lanes per atom.  (A wave per atom inside the pose's workgroup was a
+//     chain of 172 atoms per wave: 105 us for one 690-atom pose, 190 us for 1500 atoms.)
 //   * k_splat: the tile's accumulators sit in LDS as 2^20 fixed-point int32, so
 //     the atomics are exact and the result does not depend on the order in which
 //     waves add contributions.  The list is dealt to the four waves in turn (one
 //     atom per lane) and each wave sweeps its atoms one after another: an atom's candidate
 //     voxels form at most a 4 x 4 x 4 box, one per lane, and the adds are
-//     wavefront-wide LDS atomics.  The finished tile is streamed to HBM once.
+//     wavefront-wide LDS atomics.  The finished tile is streamed to HBM once; a tile
+//     that no atom reaches (two thirds of a 48^3 grid, four fifths of a 64^3 one) is
+//     written as zeros without touching LDS.
+// What bounds it: the write of the grid, and for tiles with atoms the chain list -> atom ->
+// coordinates and features.
 // Results are bitwise independent of launch shape, list order and atom
 // scheduling, so a 90 degree rotation of a pose permutes its grid exactly.
 #include "cf_internal.h"
@@ -40,12 +46,6 @@ __device__ inline int rdlane(int v, int b) { return __builtin_amdgcn_readlane(v,
 __device__ inline int64_t rdlane64(int64_t v, int b) {
   const uint32_t lo = (uint32_t)rdlane((int)(uint32_t)v, b), hi = (uint32_t)rdlane((int)(uint32_t)(v >> 32), b);
   return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-__device__ inline int64_t wave_sum_i64(int64_t v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
 }
 
 __global__ __launch_bounds__(64) void k_centers(const int32_t *__restrict__ atom_off, int n_atoms,
@@ -86,36 +86,41 @@ __global__ __launch_bounds__(64) void k_centers(const int32_t *__restrict__ atom
 }
 
 // Support box of an atom (voxel index ranges per axis, from 3 sigma) relative to
-// the grid of edge G centred on (c0, c1, c2); X* receive the atom's offsets from
-// the centre.
+// the grid of edge G centred on (c0, c1, c2); d* = the atom's offset from voxel lo on each
+// axis, in (kRcut - 1024, kRcut] whatever the coordinates.
 struct AtomBox {
-  int64_t X0, X1, X2;
+  int d0, d1, d2;
   int lo0, lo1, lo2, hi0, hi1, hi2;
 };
 __device__ inline AtomBox atom_box(const int32_t *xyz, int a, int64_t c0, int64_t c1, int64_t c2, int G) {
   const int64_t off = 512LL * (G - 1);
+  const int64_t x0 = xyz[3 * (int64_t)a] - c0 + off, x1 = xyz[3 * (int64_t)a + 1] - c1 + off,
+                x2 = xyz[3 * (int64_t)a + 2] - c2 + off;  // from the centre of voxel 0
+  // arithmetic shifts: floor division by 1024
+  const int64_t l0 = (x0 - kRcut + 1023) >> 10, l1 = (x1 - kRcut + 1023) >> 10, l2 = (x2 - kRcut + 1023) >> 10;
   AtomBox b;
-  b.X0 = xyz[3 * a] - c0;
-  b.X1 = xyz[3 * a + 1] - c1;
-  b.X2 = xyz[3 * a + 2] - c2;
-  b.lo0 = (int)floordiv(b.X0 + off - kRcut + 1023, 1024);
-  b.lo1 = (int)floordiv(b.X1 + off - kRcut + 1023, 1024);
-  b.lo2 = (int)floordiv(b.X2 + off - kRcut + 1023, 1024);
-  b.hi0 = (int)floordiv(b.X0 + off + kRcut, 1024);
-  b.hi1 = (int)floordiv(b.X1 + off + kRcut, 1024);
-  b.hi2 = (int)floordiv(b.X2 + off + kRcut, 1024);
+  b.lo0 = (int)l0;
+  b.lo1 = (int)l1;
+  b.lo2 = (int)l2;
+  b.d0 = (int)(x0 - l0 * 1024);
+  b.d1 = (int)(x1 - l1 * 1024);
+  b.d2 = (int)(x2 - l2 * 1024);
+  b.hi0 = (int)((x0 + kRcut) >> 10);
+  b.hi1 = (int)((x1 + kRcut) >> 10);
+  b.hi2 = (int)((x2 + kRcut) >> 10);
   return b;
 }
 
-// Weight of candidate voxel (v0, v1, v2) for an atom at offset X from the centre
-// (0 outside the 3 sigma support).
-__device__ inline float splat_weight(int64_t X0, int64_t X1, int64_t X2, int v0, int v1, int v2, int G, bool &in) {
-  const int64_t d0 = X0 - 512LL * (2 * v0 - G + 1);
-  const int64_t d1 = X1 - 512LL * (2 * v1 - G + 1);
-  const int64_t d2 = X2 - 512LL * (2 * v2 - G + 1);
-  const int64_t D = d0 * d0 + d1 * d1 + d2 * d2;
-  in = D <= (int64_t)kRcut * kRcut;
+// Weight of candidate voxel lo + (q0, q1, q2), q < 4, for an atom at offset d from voxel lo
+// (0 outside the 3 sigma support); squares stay below 3 * 2560^2.
+__device__ inline float splat_weight(int d0, int d1, int d2, int q0, int q1, int q2, bool &in) {
+  const int e0 = d0 - 1024 * q0, e1 = d1 - 1024 * q1, e2 = d2 - 1024 * q2;
+  const int D = e0 * e0 + e1 * e1 + e2 * e2;
+  in = D <= kRcut * kRcut;
   return in ? expf(-(float)D * kInv2s2) : 0.0f;
+}
+__device__ inline float splat_weight(const AtomBox &b, int q0, int q1, int q2, bool &in) {
+  return splat_weight(b.d0, b.d1, b.d2, q0, q1, q2, in);
 }
 
 constexpr int kBinThreads = 256;
@@ -125,15 +130,50 @@ constexpr int kMaxTiles = (96 / kTA) * (96 / kTB);   // G <= 96
 constexpr int tiles_spanned(int T) { return (T + 2) / T + 1; }
 constexpr int kMaxTilesPerAtom = tiles_spanned(kTA) * tiles_spanned(kTB);
 
-// One workgroup per pose.  Zs[a - base] = the atom's normaliser; bin_off[pl][t]
-// (ntiles + 1 entries per pose) = where tile t's list starts in bin_atoms (local
-// atom ids a - base), the pose's lists occupying bin_atoms[kMaxTilesPerAtom (a0 - base) ...].
+constexpr int kNormRows = kBinThreads / 4;   // atoms per workgroup of the normaliser part
+
+// Workgroups past the first n_poses: Zs[a - base] = the normaliser of atom a.  Every w >=
+// exp(-4.5) > 2^-7 is an exact multiple of 2^-31, so w * 2^40 is an exact integer and the
+// integer sum is the exact sum of the float weights, in any order.
+__device__ void splat_norm(const int32_t *__restrict__ atom_off, int n_atoms, const int32_t *__restrict__ xyz,
+                           const int32_t *__restrict__ centers, int p0, int item, int nbx, int G, int64_t atoms_cap,
+                           double *__restrict__ Zs) {
+  const int pl = item / nbx, tid = threadIdx.x;
+  int a0, a1;
+  pose_range(atom_off, p0 + pl, n_atoms, a0, a1);
+  const int base = min(max(atom_off[p0], 0), n_atoms);
+  if (a0 < base || (int64_t)a1 - base > atoms_cap) return;
+  const int64_t c0 = centers[3 * pl], c1 = centers[3 * pl + 1], c2 = centers[3 * pl + 2];
+  for (int r0 = (item % nbx) * kNormRows; r0 < a1 - a0; r0 += nbx * kNormRows) {
+    const int a = a0 + r0 + (tid >> 2);
+    const bool live = a < a1;
+    const AtomBox b = atom_box(xyz, live ? a : a0, c0, c1, c2, G);
+    int64_t sum = 0;
+#pragma unroll 4
+    for (int v = 0; v < 16; ++v) {
+      bool in;
+      const float w = splat_weight(b, tid & 3, v >> 2, v & 3, in);
+      sum += (int64_t)((double)w * 1099511627776.0);
+    }
+    sum += __shfl_xor(sum, 1, 64);
+    sum += __shfl_xor(sum, 2, 64);
+    if (live && (tid & 3) == 0) Zs[a - base] = (double)sum * (1.0 / 1099511627776.0);
+  }
+}
+
+// The first n_poses workgroups: bin_off[pl][t] (ntiles + 1 entries per pose) = where tile t's
+// list starts in bin_atoms (local atom ids a - base), the pose's lists occupying
+// bin_atoms[kMaxTilesPerAtom (a0 - base) ...].
 __global__ __launch_bounds__(kBinThreads) void k_splat_bin(const int32_t *__restrict__ atom_off, int n_atoms,
                                                           const int32_t *__restrict__ xyz,
-                                                          const int32_t *__restrict__ centers, int p0, int G,
-                                                          int64_t atoms_cap, double *__restrict__ Zs,
+                                                          const int32_t *__restrict__ centers, int p0, int n_poses,
+                                                          int nbx, int G, int64_t atoms_cap, double *__restrict__ Zs,
                                                           int32_t *__restrict__ bin_off,
                                                           int32_t *__restrict__ bin_atoms) {
+  if ((int)blockIdx.x >= n_poses) {
+    splat_norm(atom_off, n_atoms, xyz, centers, p0, blockIdx.x - n_poses, nbx, G, atoms_cap, Zs);
+    return;
+  }
   __shared__ int cnt[kMaxTiles];
   __shared__ int part[kBinThreads];
   const int pl = blockIdx.x, p = p0 + pl, tid = threadIdx.x;
@@ -193,23 +233,87 @@ __global__ __launch_bounds__(kBinThreads) void k_splat_bin(const int32_t *__rest
     for (int i = t0a; i <= t0b; ++i)
       for (int j = t1a; j <= t1b; ++j) bin_atoms[atomicAdd(&cnt[i * ntb + j], 1)] = a - base;
   }
-  // normalisers: one wave per atom, candidate voxel per lane.  Every w >=
-  // exp(-4.5) > 2^-7 is an exact multiple of 2^-31, so w * 2^40 is an exact
-  // integer and the integer wave sum is the exact sum of the float weights.
-  const int lane = tid & 63, wave = tid >> 6;
-  for (int a = a0 + wave; a < a1; a += kBinThreads / 64) {
-    const AtomBox b = atom_box(xyz, a, c0, c1, c2, G);
-    bool in;
-    const float w = splat_weight(b.X0, b.X1, b.X2, b.lo0 + (lane >> 4), b.lo1 + ((lane >> 2) & 3), b.lo2 + (lane & 3), G, in);
-    const int64_t wq = (int64_t)((double)w * 1099511627776.0);
-    const double Z = (double)wave_sum_i64(wq) * (1.0 / 1099511627776.0);
-    if (lane == 0) Zs[a - base] = Z;
-  }
 }
 
 // MODE 0: float [19]; 1: bf16 [19]; 2: float [cpad]; 3: bf16 [cpad] (channels >= 19 zero);
 // 4: bf16 in 4-channel chunks, chunk-major per pose: [P][cpad / 4][G^3][4]
-template <int MODE>
+// WIDE (modes 0 and 1): four consecutive channels-last values per store, 16 or 8 bytes
+// (the tile's rows along axis 2 are G * 19 values, a multiple of four, and the
+// accumulators lie in the same order); the grid is aligned to that.
+template <int MODE, bool WIDE, bool ZERO>
+__device__ inline void store_tile(const int *acc, void *__restrict__ grid, int pl, int i0, int j0, int G, int cpad) {
+  const int nvox = kTA * kTB * G;
+  if ((MODE == 0 || MODE == 1) && WIDE) {
+    const int row4 = G * CF_NCH / 4;  // stores per row
+    for (int r = 0; r < kTA * kTB; ++r) {
+      const int64_t g0 = (((int64_t)pl * G + (i0 + r / kTB)) * G + (j0 + r % kTB)) * row4;
+      for (int e = threadIdx.x; e < row4; e += blockDim.x) {
+        const int4 a = ZERO ? make_int4(0, 0, 0, 0) : reinterpret_cast<const int4 *>(acc)[r * row4 + e];
+        const float v[4] = {(float)a.x * kSplatInvScale, (float)a.y * kSplatInvScale, (float)a.z * kSplatInvScale,
+                            (float)a.w * kSplatInvScale};
+        if (MODE == 0) {
+          reinterpret_cast<float4 *>(grid)[g0 + e] = make_float4(v[0], v[1], v[2], v[3]);
+        } else {
+          bf16_t h[4] = {(bf16_t)v[0], (bf16_t)v[1], (bf16_t)v[2], (bf16_t)v[3]};
+          reinterpret_cast<uint2 *>(grid)[g0 + e] = __builtin_bit_cast(uint2, h);
+        }
+      }
+    }
+  } else if (MODE == 0 || MODE == 1) {
+    for (int e = threadIdx.x; e < nvox * CF_NCH; e += blockDim.x) {
+      const int v = e / CF_NCH, ch = e - v * CF_NCH;
+      const int k = v % G, jj = (v / G) % kTB, ii = v / (G * kTB);
+      const int64_t gv = (((int64_t)pl * G + (i0 + ii)) * G + (j0 + jj)) * G + k;
+      const float val = ZERO ? 0.0f : (float)acc[e] * kSplatInvScale;
+      if (MODE == 0)
+        reinterpret_cast<float *>(grid)[gv * CF_NCH + ch] = val;
+      else
+        reinterpret_cast<bf16_t *>(grid)[gv * CF_NCH + ch] = (bf16_t)val;
+    }
+  } else if (MODE == 4) {
+    // chunk slowest, voxel fastest: a thread writes two consecutive 8-byte voxels (G is even)
+    const int ng = cpad / 4, nv2 = nvox / 2, g2 = G / 2;
+    const int64_t g3 = (int64_t)G * G * G;
+    for (int e = threadIdx.x; e < nv2 * ng; e += blockDim.x) {
+      const int g = e / nv2, v = (e - g * nv2) * 2;
+      const int k = v % G, jj = (v / G) % kTB, ii = v / (G * kTB);
+      const int64_t vloc = ((int64_t)(i0 + ii) * G + (j0 + jj)) * G + k;
+      bf16_t h[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int ch = g * 4 + (q & 3);
+        h[q] = (bf16_t)(!ZERO && ch < CF_NCH ? (float)acc[(v + (q >> 2)) * CF_NCH + ch] * kSplatInvScale : 0.0f);
+      }
+      *reinterpret_cast<uint4 *>(reinterpret_cast<bf16_t *>(grid) + (((int64_t)pl * ng + g) * g3 + vloc) * 4) =
+          __builtin_bit_cast(uint4, h);
+    }
+  } else {
+    const int ng = cpad / 8;
+    for (int e = threadIdx.x; e < nvox * ng; e += blockDim.x) {
+      const int v = e / ng, g = e - v * ng;
+      const int k = v % G, jj = (v / G) % kTB, ii = v / (G * kTB);
+      const int64_t gv = (((int64_t)pl * G + (i0 + ii)) * G + (j0 + jj)) * G + k;
+      float val[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int ch = g * 8 + q;
+        val[q] = !ZERO && ch < CF_NCH ? (float)acc[v * CF_NCH + ch] * kSplatInvScale : 0.0f;
+      }
+      if (MODE == 2) {
+        float4 *dst = reinterpret_cast<float4 *>(reinterpret_cast<float *>(grid) + gv * cpad + g * 8);
+        dst[0] = make_float4(val[0], val[1], val[2], val[3]);
+        dst[1] = make_float4(val[4], val[5], val[6], val[7]);
+      } else {
+        bf16x8 pk;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) pk[q] = (bf16_t)val[q];
+        *reinterpret_cast<bf16x8 *>(reinterpret_cast<bf16_t *>(grid) + gv * cpad + g * 8) = pk;
+      }
+    }
+  }
+}
+
+template <int MODE, bool WIDE>
 __global__ __launch_bounds__(256) void k_splat(const int32_t *__restrict__ atom_off, int n_atoms,
                                                const int32_t *__restrict__ xyz,
                                                const float *__restrict__ feat,
@@ -227,14 +331,18 @@ __global__ __launch_bounds__(256) void k_splat(const int32_t *__restrict__ atom_
   const int i0 = (blockIdx.x / ntb) * kTA, j0 = (blockIdx.x % ntb) * kTB;
   const int nacc = kTA * kTB * G * CF_NCH;  // a multiple of 4 (kTA * kTB is)
   static_assert((kTA * kTB) % 4 == 0, "accumulators cleared 16 bytes at a time");
-  for (int e = threadIdx.x; e < nacc / 4; e += blockDim.x) reinterpret_cast<int4 *>(acc)[e] = make_int4(0, 0, 0, 0);
-  if (threadIdx.x == 0) budget = 0;
   int a0, a1;
   if (!pose_range(atom_off, p, n_atoms, a0, a1) && blockIdx.x == 0 && threadIdx.x == 0)
     dev_fail(status, kDevBadOffsets);
   const int base = min(max(atom_off[p0], 0), n_atoms);
   const int64_t c0 = centers[3 * pl], c1 = centers[3 * pl + 1], c2 = centers[3 * pl + 2];
   const int l0 = bin_off[(int64_t)pl * (ntiles + 1) + blockIdx.x], l1 = bin_off[(int64_t)pl * (ntiles + 1) + blockIdx.x + 1];
+  if (l0 == l1) {  // no atom reaches the tile
+    store_tile<MODE, WIDE, true>(acc, grid, pl, i0, j0, G, cpad);
+    return;
+  }
+  for (int e = threadIdx.x; e < nacc / 4; e += blockDim.x) reinterpret_cast<int4 *>(acc)[e] = make_int4(0, 0, 0, 0);
+  if (threadIdx.x == 0) budget = 0;
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   // the tile's list is dealt to the waves in turn (entry q0 + 4 k to lane k of wave
@@ -282,7 +390,8 @@ __global__ __launch_bounds__(256) void k_splat(const int32_t *__restrict__ atom_
       const int v0 = rdlane(bx.lo0, b) + (lane >> 4), v1 = rdlane(bx.lo1, b) + ((lane >> 2) & 3),
                 v2 = rdlane(bx.lo2, b) + (lane & 3);
       bool in;
-      const float w = splat_weight(rdlane64(bx.X0, b), rdlane64(bx.X1, b), rdlane64(bx.X2, b), v0, v1, v2, G, in);
+      const float w = splat_weight(rdlane(bx.d0, b), rdlane(bx.d1, b), rdlane(bx.d2, b), lane >> 4, (lane >> 2) & 3,
+                                   lane & 3, in);
       const double Z = __longlong_as_double(rdlane64(__double_as_longlong(Za), b));
       const float f = (float)((double)w / Z);
       const bool tile = in && v0 >= i0 && v0 < i0 + kTA && v1 >= j0 && v1 < j0 + kTB && v2 >= 0 && v2 < G;
@@ -308,64 +417,7 @@ __global__ __launch_bounds__(256) void k_splat(const int32_t *__restrict__ atom_
   }
   __syncthreads();
   if (threadIdx.x == 0 && budget > kSplatBudget) dev_fail(status, kDevGridRange);
-  // stream the tile out
-  const int nvox = kTA * kTB * G;
-  if (MODE == 0 || MODE == 1) {
-    for (int e = threadIdx.x; e < nvox * CF_NCH; e += blockDim.x) {
-      const int v = e / CF_NCH, ch = e - v * CF_NCH;
-      const int k = v % G, jj = (v / G) % kTB, ii = v / (G * kTB);
-      const int64_t gv = (((int64_t)pl * G + (i0 + ii)) * G + (j0 + jj)) * G + k;
-      const float val = (float)acc[e] * kSplatInvScale;
-      if (MODE == 0)
-        reinterpret_cast<float *>(grid)[gv * CF_NCH + ch] = val;
-      else
-        reinterpret_cast<bf16_t *>(grid)[gv * CF_NCH + ch] = (bf16_t)val;
-    }
-  } else if (MODE == 4) {
-    // chunk slowest, voxel fastest: consecutive threads write consecutive 8-byte voxels
-    const int ng = cpad / 4;
-    const int64_t g3 = (int64_t)G * G * G;
-    for (int e = threadIdx.x; e < nvox * ng; e += blockDim.x) {
-      const int g = e / nvox, v = e - g * nvox;
-      const int k = v % G, jj = (v / G) % kTB, ii = v / (G * kTB);
-      const int64_t vloc = ((int64_t)(i0 + ii) * G + (j0 + jj)) * G + k;
-      float val[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int ch = g * 4 + q;
-        val[q] = ch < CF_NCH ? (float)acc[v * CF_NCH + ch] * kSplatInvScale : 0.0f;
-      }
-      const uint32_t lo = (uint32_t)__builtin_bit_cast(uint16_t, (bf16_t)val[0]) |
-                          ((uint32_t)__builtin_bit_cast(uint16_t, (bf16_t)val[1]) << 16);
-      const uint32_t hi = (uint32_t)__builtin_bit_cast(uint16_t, (bf16_t)val[2]) |
-                          ((uint32_t)__builtin_bit_cast(uint16_t, (bf16_t)val[3]) << 16);
-      *reinterpret_cast<uint2 *>(reinterpret_cast<bf16_t *>(grid) + (((int64_t)pl * ng + g) * g3 + vloc) * 4) =
-          make_uint2(lo, hi);
-    }
-  } else {
-    const int ng = cpad / 8;
-    for (int e = threadIdx.x; e < nvox * ng; e += blockDim.x) {
-      const int v = e / ng, g = e - v * ng;
-      const int k = v % G, jj = (v / G) % kTB, ii = v / (G * kTB);
-      const int64_t gv = (((int64_t)pl * G + (i0 + ii)) * G + (j0 + jj)) * G + k;
-      float val[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int ch = g * 8 + q;
-        val[q] = ch < CF_NCH ? (float)acc[v * CF_NCH + ch] * kSplatInvScale : 0.0f;
-      }
-      if (MODE == 2) {
-        float4 *dst = reinterpret_cast<float4 *>(reinterpret_cast<float *>(grid) + gv * cpad + g * 8);
-        dst[0] = make_float4(val[0], val[1], val[2], val[3]);
-        dst[1] = make_float4(val[4], val[5], val[6], val[7]);
-      } else {
-        bf16x8 pk;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) pk[q] = (bf16_t)val[q];
-        *reinterpret_cast<bf16x8 *>(reinterpret_cast<bf16_t *>(grid) + gv * cpad + g * 8) = pk;
-      }
-    }
-  }
+  store_tile<MODE, WIDE, false>(acc, grid, pl, i0, j0, G, cpad);
 }
 
 // Public [19]-channel grid -> the internal layout (conversion between precisions
@@ -446,26 +498,29 @@ int64_t splat_work_bytes(int n_poses, int64_t atoms, int G) {
 
 hipError_t launch_splat(const int32_t *atom_off, int n_atoms, const int32_t *xyz, const float *feat,
                         const int32_t *centers, int p0, int n_poses, int G, void *grid, int out_mode,
-                        int cpad, void *work, int64_t atoms_cap, int64_t *status, hipStream_t s) {
+                        int cpad, void *work, int64_t atoms_cap, int mean_atoms, int64_t *status, hipStream_t s) {
   if (n_poses <= 0) return hipSuccess;
   if (!work || G > 96) return hipErrorInvalidValue;
   const int ntiles = (G / kTA) * (G / kTB);
   double *Zs = reinterpret_cast<double *>(work);
   int32_t *bin_off = reinterpret_cast<int32_t *>(Zs + atoms_cap);
   int32_t *bin_atoms = bin_off + (int64_t)n_poses * (ntiles + 1);
-  hipLaunchKernelGGL(k_splat_bin, dim3(n_poses), dim3(kBinThreads), 0, s, atom_off, n_atoms, xyz, centers, p0, G,
-                     atoms_cap, Zs, bin_off, bin_atoms);
+  const int nbx = pose_blocks(n_atoms, mean_atoms, kNormRows);
+  hipLaunchKernelGGL(k_splat_bin, dim3((unsigned)n_poses * (1 + nbx)), dim3(kBinThreads), 0, s, atom_off, n_atoms, xyz,
+                     centers, p0, n_poses, nbx, G, atoms_cap, Zs, bin_off, bin_atoms);
+  // a caller's grid need not be aligned to the wide stores
+  const bool wide = reinterpret_cast<uintptr_t>(grid) % (out_mode == 0 ? 16 : 8) == 0;
   const dim3 grd(ntiles, n_poses);
   const size_t lds = sizeof(int) * kTA * kTB * G * CF_NCH;
-#define CF_SPLAT(M)                                                                                          \
-  hipLaunchKernelGGL(k_splat<M>, grd, dim3(256), lds, s, atom_off, n_atoms, xyz, feat, centers, p0, G, grid, cpad, \
+#define CF_SPLAT(M, W)                                                                                       \
+  hipLaunchKernelGGL((k_splat<M, W>), grd, dim3(256), lds, s, atom_off, n_atoms, xyz, feat, centers, p0, G, grid, cpad, \
                      Zs, bin_off, bin_atoms, status)
   switch (out_mode) {
-    case 0: CF_SPLAT(0); break;
-    case 1: CF_SPLAT(1); break;
-    case 2: CF_SPLAT(2); break;
-    case 3: CF_SPLAT(3); break;
-    case 4: CF_SPLAT(4); break;
+    case 0: if (wide) CF_SPLAT(0, true); else CF_SPLAT(0, false); break;
+    case 1: if (wide) CF_SPLAT(1, true); else CF_SPLAT(1, false); break;
+    case 2: CF_SPLAT(2, true); break;
+    case 3: CF_SPLAT(3, true); break;
+    case 4: CF_SPLAT(4, true); break;
     default: return hipErrorInvalidValue;
   }
 #undef CF_SPLAT
