@@ -24,6 +24,7 @@
 //     contiguous).  Accumulation is fp32 in both.
 //   * epilogue: + folded bias, + residual tensor, ReLU, convert, store.
 #include <algorithm>
+#include <type_traits>
 
 #include "cf_internal.h"
 
@@ -954,6 +955,146 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(Conv4Cf
   }
 }
 
+// ---- fp32, small tiles ------------------------------------------------------------
+//
+// The fp32 form of k_conv (8-channel chunks, four 32x32x2 MFMAs per block and tap, the same
+// sums in the same order) with tiles small enough for two workgroups per CU: a stride-2
+// 7^3 halo at 32 bytes per voxel leaves one 4 x 4 x 8 tile per CU, one wave per SIMD, whose
+// LDS row read, weight loads and staging were exposed (53 % of what a float32 matrix product
+// reaches here).  A wave takes one 32 x 32 block; the four waves are RW row groups x 4 / RW
+// column groups.  Row fragments are read a tap ahead, weight fragments four taps ahead, and
+// the next chunk's halo is loaded during the walk.  Measured at 48^3: first layer of the full
+// model 501 -> 142 us for one pose, 4002 -> 2266 for 24, 37.6 -> 22.9 ms for 256; its last layer
+// 1866 -> 357, 3502 -> 1968, 29.2 -> 17.7 ms; 5^3 stride-1 layers of 32 channels 247 -> 72 us for
+// one pose, 6295 -> 6205 for 256.  The MFMA steps of a last chunk's absent
+// channels (5 of the 19-channel grid's 24) are left out: their products are zeros.
+template <int KS, int S, int TZ, int TY, int TX, int RW>
+struct ConvFCfg {
+  static constexpr int PAD = (KS - 1) / 2;
+  static constexpr int HZ = TZ * S + KS - S, HY = TY * S + KS - S, HX = TX * S + KS - S;
+  static constexpr int ROW = HX * 32 + 16, SLAB = HY * ROW, LDS = HZ * SLAB;
+  static constexpr int NV = HZ * HY * HX, HITER = (NV + 255) / 256, NT = 4 / RW * 32;
+  static_assert(TZ * TY * TX == 32 * RW, "a wave per 32 rows");
+  static_assert(LDS <= 81920, "two workgroups per CU");
+};
+
+template <int KS, int S, int TZ, int TY, int TX, int RW>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv_f32(
+    const float *__restrict__ in, const float *__restrict__ wpk, const float *__restrict__ bias,
+    const float *__restrict__ res, float *__restrict__ out, int D, int Do, int cin, int cin_pad, int cout_pad32, int cout,
+    int cout_store, int nty, int ntx, int wbytes) {
+  using C = ConvFCfg<KS, S, TZ, TY, TX, RW>;
+  __shared__ __attribute__((aligned(16))) char lds[C::LDS];
+  int tile, pose, nblk;
+  xcd_order(tile, pose, nblk);
+  const int tz0 = (tile / (nty * ntx)) * TZ, ty0 = ((tile / ntx) % nty) * TY, tx0 = (tile % ntx) * TX;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, khalf = lane >> 5, lrow = lane & 31;
+  const int rg = wave % RW, n0 = nblk * C::NT + wave / RW * 32;
+  const int nchunks = cin_pad / 8;
+  constexpr int HZ2 = S == 1 ? 0 : (C::HZ + 1) / 2, HY2 = S == 1 ? 0 : (C::HY + 1) / 2, HX2 = S == 1 ? 0 : (C::HX + 1) / 2;
+  int rowoff;
+  {
+    const int m = rg * 32 + lrow, z = m / (TY * TX), y = (m / TX) % TY, x = m % TX;
+    rowoff = z * C::SLAB + y * C::ROW + x * 32 + khalf * 16;
+  }
+  // this thread's halo voxels: element offset in a pose's chunk (-1: outside) and LDS offset
+  int hsrc[C::HITER], hdst[C::HITER];
+#pragma unroll
+  for (int it = 0; it < C::HITER; ++it) {
+    const int v = it * 256 + (int)threadIdx.x;
+    const int hx = v % C::HX, hy = (v / C::HX) % C::HY, hz = v / (C::HX * C::HY);
+    const int gz = tz0 * S - C::PAD + hz, gy = ty0 * S - C::PAD + hy, gx = tx0 * S - C::PAD + hx;
+    const bool inside = (unsigned)gz < (unsigned)D && (unsigned)gy < (unsigned)D && (unsigned)gx < (unsigned)D;
+    hsrc[it] = v < C::NV && inside ? ((gz * D + gy) * D + gx) * cin_pad : -1;
+    hdst[it] = v < C::NV ? stored_index(hz, C::HZ, S) * C::SLAB + stored_index(hy, C::HY, S) * C::ROW +
+                               stored_index(hx, C::HX, S) * 32
+                         : -1;
+  }
+  const float *src = in + (int64_t)pose * D * D * D * cin_pad;
+  float4 hl[C::HITER], hh[C::HITER];
+  auto fetch = [&](int chunk) {
+#pragma unroll
+    for (int it = 0; it < C::HITER; ++it) {
+      hl[it] = hh[it] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (hsrc[it] >= 0) {
+        const float4 *q = reinterpret_cast<const float4 *>(src + hsrc[it] + chunk * 8);
+        hl[it] = q[0];
+        hh[it] = q[1];
+      }
+    }
+  };
+  typedef float accv __attribute__((ext_vector_type(16)));
+  accv acc = {};
+  const int tap_bytes = nchunks * cout_pad32 * 32;
+  const __amdgpu_buffer_rsrc_t wrs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(wpk), (short)0, wbytes, 0x00020000);
+  // one chunk's taps, STEPS channel pairs of eight channels
+  auto walk = [&](auto steps_c, int chunk) {
+    constexpr int STEPS = decltype(steps_c)::value;
+    const int vb = ((chunk * cout_pad32 + n0 + lrow) * 8 + khalf * 4) * 4;
+    constexpr int PF = 4;
+    float4 b[PF];
+#pragma unroll
+    for (int q = 0; q < PF; ++q)
+      b[q] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(wrs, vb, q * tap_bytes, 0));
+    int soff = PF * tap_bytes;
+    float4 a = *reinterpret_cast<const float4 *>(lds + rowoff);
+    for (int dz = 0; dz < KS; ++dz)
+      for (int dy = 0; dy < KS; ++dy) {
+        const int row = (S == 1 ? dz : (dz & 1) * HZ2 + (dz >> 1)) * C::SLAB + (S == 1 ? dy : (dy & 1) * HY2 + (dy >> 1)) * C::ROW;
+        // first tap of the next (dz, dy); the last one reads its own row again
+        const int ny = dy + 1 < KS ? dy + 1 : 0, nz = dy + 1 < KS ? dz : (dz + 1 < KS ? dz + 1 : dz);
+        const int nrow = (S == 1 ? nz : (nz & 1) * HZ2 + (nz >> 1)) * C::SLAB + (S == 1 ? ny : (ny & 1) * HY2 + (ny >> 1)) * C::ROW;
+#pragma unroll
+        for (int dx = 0; dx < KS; ++dx) {
+          const float4 an = *reinterpret_cast<const float4 *>(
+              lds + rowoff + (dx + 1 < KS ? row + (S == 1 ? dx + 1 : ((dx + 1) & 1) * HX2 + ((dx + 1) >> 1)) * 32 : nrow));
+          __builtin_amdgcn_sched_barrier(0);
+          const float4 w = b[0];
+#pragma unroll
+          for (int q = 0; q + 1 < PF; ++q) b[q] = b[q + 1];
+          b[PF - 1] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(wrs, vb, soff, 0));
+          soff += tap_bytes;
+          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, w.x, acc, 0, 0, 0);
+          if constexpr (STEPS > 1) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, w.y, acc, 0, 0, 0);
+          if constexpr (STEPS > 2) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, w.z, acc, 0, 0, 0);
+          if constexpr (STEPS > 2) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, w.w, acc, 0, 0, 0);
+          a = an;
+        }
+      }
+  };
+  fetch(0);
+  for (int chunk = 0; chunk < nchunks; ++chunk) {
+    if (chunk) __syncthreads();
+#pragma unroll
+    for (int it = 0; it < C::HITER; ++it)
+      if (hdst[it] >= 0) {  // channels (0 .. 7) -> (0, 2, 4, 6 | 1, 3, 5, 7)
+        float4 *dst = reinterpret_cast<float4 *>(lds + hdst[it]);
+        dst[0] = make_float4(hl[it].x, hl[it].z, hh[it].x, hh[it].z);
+        dst[1] = make_float4(hl[it].y, hl[it].w, hh[it].y, hh[it].w);
+      }
+    __syncthreads();
+    if (chunk + 1 < nchunks) fetch(chunk + 1);
+    if (cin - chunk * 8 > 4)
+      walk(std::integral_constant<int, 4>{}, chunk);
+    else
+      walk(std::integral_constant<int, 2>{}, chunk);
+  }
+  const int n = n0 + lrow;
+  if (n >= cout) return;
+  const float bn = bias[n];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int m = rg * 32 + 8 * (r >> 2) + 4 * khalf + (r & 3);
+    const int z = tz0 + m / (TY * TX), y = ty0 + (m / TX) % TY, x = tx0 + m % TX;
+    if (z >= Do || y >= Do || x >= Do) continue;
+    const int64_t o = (((int64_t)pose * Do + z) * Do * Do + (int64_t)y * Do + x) * cout_store + n;
+    float v = acc[r] + bn;
+    if (res) v += res[o];
+    out[o] = v > 0.0f ? v : 0.0f;
+  }
+}
+
 template <int KS, int S, int TZ, int TY, int TX, int NW, int NT>
 hipError_t launch_q(const ConvLayer &L, const void *in, const void *res, void *out, int n_poses, int D,
                     hipStream_t s) {
@@ -964,6 +1105,18 @@ hipError_t launch_q(const ConvLayer &L, const void *in, const void *res, void *o
                      reinterpret_cast<const bf16_t *>(in), reinterpret_cast<const bf16_t *>(L.wpk4), L.bias,
                      reinterpret_cast<const bf16_t *>(res), reinterpret_cast<bf16_t *>(out), D, Do, L.cin_pad,
                      (L.cin + 3) / 4, L.cout_pad32, L.cout_store, nty, ntx, (int)L.wbytes4, L.in_cm4);
+  return hipGetLastError();
+}
+
+template <int KS, int S, int TZ, int TY, int TX, int RW>
+hipError_t launch_f(const ConvLayer &L, const void *in, const void *res, void *out, int n_poses, int D, hipStream_t s) {
+  const int Do = (D + 2 * ((KS - 1) / 2) - KS) / S + 1;
+  const int ntz = (Do + TZ - 1) / TZ, nty = (Do + TY - 1) / TY, ntx = (Do + TX - 1) / TX;
+  const dim3 grid(ntz * nty * ntx, n_poses, L.cout_pad32 / ConvFCfg<KS, S, TZ, TY, TX, RW>::NT);
+  hipLaunchKernelGGL((k_conv_f32<KS, S, TZ, TY, TX, RW>), grid, dim3(256), 0, s, reinterpret_cast<const float *>(in),
+                     reinterpret_cast<const float *>(L.wpk), L.bias, reinterpret_cast<const float *>(res),
+                     reinterpret_cast<float *>(out), D, Do, L.cin, L.cin_pad, L.cout_pad32, L.cout, L.cout_store, nty,
+                     ntx, (int)L.wbytes);
   return hipGetLastError();
 }
 
@@ -1221,6 +1374,28 @@ hipError_t launch_conv(int variant, const ConvLayer &L, int bf16, const void *in
                        void *out, int n_poses, int D_in, void *work, hipStream_t s, bool fit) {
   if (!conv_variant_ok(variant, L, bf16, D_in)) return hipErrorInvalidValue;
   if (variant == kFftVariant) return launch_fft_conv(L, in, res, out, n_poses, D_in, work, s);
+  // the plain form's small tiles are the faster ones at every batch size measured (1 .. 256
+  // poses, see k_conv_f32); the variants themselves run when the caller sets them
+  if (fit && !bf16) {
+#define CF_F(KS, S)                                                                                          \
+  if (L.k == KS && L.stride == S && L.cout_pad32 % 64 == 0)                                                  \
+    return launch_f<KS, S, 4, 4, 4, 2>(L, in, res, out, n_poses, D_in, s);
+#define CF_F32(KS, S)                                                                                        \
+  if (L.k == KS && L.stride == S) return launch_f<KS, S, 4, 4, 8, 4>(L, in, res, out, n_poses, D_in, s);
+    CF_F(7, 2)
+    CF_F(5, 2)
+    CF_F(3, 2)
+    CF_F(7, 1)
+    CF_F(5, 1)
+    CF_F(3, 1)
+    CF_F32(5, 2)
+    CF_F32(3, 2)
+    CF_F32(7, 1)
+    CF_F32(5, 1)
+    CF_F32(3, 1)
+#undef CF_F
+#undef CF_F32
+  }
   const Variant &V = fit && bf16 && kVariants[variant].pairs ? fit_tile(kVariants[variant], L, D_in, n_poses)
                                                              : kVariants[variant];
   return bf16 ? V.launch_bf16(L, in, res, out, n_poses, D_in, s) : V.launch_f32(L, in, res, out, n_poses, D_in, s);
