@@ -987,7 +987,9 @@ __global__ __launch_bounds__(128 * RG) __attribute__((amdgpu_waves_per_eu(3))) v
 // over two waves.  One K step (chunk, dz) is 16 deep (8 channels x re, im) and
 // takes eight MFMAs; MFMA j reads K indices j and 8 + j, so a lane's A fragment
 // is 8 contiguous floats of its row (khalf 0: re of the 8 channels, khalf 1: im)
-// and its B fragment the 8 matching weight values, both two 16-byte loads.
+// and its B fragment the 8 matching weight values, both two 16-byte loads.  The panel
+// (39 KB) allows four workgroups per CU, two waves on every SIMD: staging the epilogue's 96
+// rows at once (51 KB, three workgroups) left half of the SIMDs with one wave.
 template <int KS, int NB>
 __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void k_fft_zconv_f32(
     const float *__restrict__ xs, const float *__restrict__ gp, float *__restrict__ ys, int np, int D, int nch,
@@ -995,7 +997,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void k
   constexpr int P = (KS - 1) / 2, NT = 64 * NB, MB = 3, NBT = NT / 32, NTH = 128;
   constexpr int PH = 4 * 64 + 16;                // panel row pitch (bytes): 4 chunks x 16 floats
   constexpr int HALF = NT / 2, orow = HALF * 8, opitch = orow + 16;
-  constexpr int kLds = kRowsZH * opitch > kPanelRowsH * PH ? kRowsZH * opitch : kPanelRowsH * PH;
+  constexpr int kLds = 32 * opitch > kPanelRowsH * PH ? 32 * opitch : kPanelRowsH * PH;
   __shared__ __attribute__((aligned(16))) char lds[kLds];
   int pblk, col, zero;
   xcd_order(pblk, col, zero);
@@ -1110,14 +1112,17 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
   }
 
-  // epilogue through LDS: rows of NT floats in the spectrum layout, then contiguous stores
-  __syncthreads();
+  // epilogue through LDS, 32 rows at a time: rows of NT floats in the spectrum layout, then
+  // contiguous stores
   float *ot = reinterpret_cast<float *>(lds);
+  constexpr int q16 = orow / 16;
+  float *dst = ys + ((int64_t)col * np + p0) * D * (orow / 4);
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
+  for (int mb = 0; mb < MB; ++mb) {
+    __syncthreads();
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int row = mb * 32 + 8 * (r >> 2) + 4 * khalf + (r & 3);
+      const int row = 8 * (r >> 2) + 4 * khalf + (r & 3);
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         const int n = (wave_n * NB + nb) * 32 + lrow;
@@ -1125,13 +1130,13 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void k
         ot[(row * opitch) / 4 + (co >> 3) * 16 + part * 8 + (co & 7)] = acc[mb][nb][r];
       }
     }
-  __syncthreads();
-  constexpr int q16 = orow / 16;
-  float *dst = ys + ((int64_t)col * np + p0) * D * (orow / 4);
-  for (int e = tid; e < nvalid * D * q16; e += NTH) {
-    const int q = e % q16, row = e / q16;
-    *reinterpret_cast<uint4 *>(dst + (int64_t)row * (orow / 4) + q * 4) =
-        *reinterpret_cast<const uint4 *>(lds + row * opitch + q * 16);
+    __syncthreads();
+    for (int e = tid; e < 32 * q16; e += NTH) {
+      const int q = e % q16, row = e / q16;
+      if (mb * 32 + row < nvalid * D)
+        *reinterpret_cast<uint4 *>(dst + (int64_t)(mb * 32 + row) * (orow / 4) + q * 4) =
+            *reinterpret_cast<const uint4 *>(lds + row * opitch + q * 16);
+    }
   }
 }
 
