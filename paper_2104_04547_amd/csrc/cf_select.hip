@@ -5,13 +5,22 @@
 // maximum Coherent Fusion pK over its poses (Sec. 5.2); compounds are then ranked
 // and the best few purchased for assays (the 100-of-1,000,000 example, Sec. 3.4).
 //
-// cf_compound_max: one thread per segment (segments are short), NaN scores are
+// cf_compound_max: a group of 8 lanes per segment (64 for long segments), NaN scores are
 // ignored, ties go to the lowest pose index.
-// cf_top_k: exact radix select on 64-bit keys (order-preserving 32-bit image of
+// cf_top_k: exact selection on 64-bit keys (order-preserving 32-bit image of
 // the value, then the complemented index, so every key is distinct and the
-// ranking is "value descending, index ascending"): 8 passes of an 8-bit digit
-// histogram find the k-th key, one pass collects the keys at or above it, and a
-// single workgroup sorts those k keys.  Results are deterministic.
+// ranking is "value descending, index ascending").
+//   * up to 65,536 values: one workgroup with every value in registers.  The k-th largest
+//     of its 1024 threads' maxima bounds the k-th largest value from below; the few values
+//     at or above it are sorted.  Where too many are (large k, or values in an order that
+//     defeats the bound), a binary search over the value and then the index finds the
+//     k-th key exactly.
+//   * more: radix select, 8 passes of an 8-bit digit histogram (the last workgroup of a pass
+//     picks the digit; passes after the key is certain return at once), one pass collects
+//     the keys at or above the k-th, and a single workgroup sorts those k keys.
+// What bounds it: launches, and latency on one CU.  For 50,000 values 19 launches took 75 us
+// (102 us with the maxima of 50,000 segments of 10^6 scores before them), one takes 26
+// (30).  Results are deterministic.
 #include <algorithm>
 #include <cfloat>
 #include <climits>
@@ -35,77 +44,241 @@ __device__ inline uint64_t topk_key(float v, int i) {
   return ((uint64_t)k << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i);
 }
 
+// LPS lanes per segment; lane q takes the scores q, q + LPS, ... and the lanes' maxima are
+// merged (the lowest index wins a tie)
+template <int LPS>
 __global__ __launch_bounds__(kSelThreads) void k_segmax(const float *__restrict__ scores, int n_scores,
                                                         const int32_t *__restrict__ off, int n_seg,
                                                         float *__restrict__ best, int32_t *__restrict__ best_idx,
                                                         int64_t *status) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= n_seg) return;
+  const int64_t t = blockIdx.x * (int64_t)kSelThreads + threadIdx.x;
+  const int c = (int)(t / LPS), q = (int)(t % LPS);
+  if (c >= n_seg) return;  // whole groups
   int a = off[c], b = off[c + 1];
   if (a < 0 || b < a || b > n_scores) {
-    dev_fail(status, kDevBadOffsets);
+    if (q == 0) dev_fail(status, kDevBadOffsets);
     a = b = 0;
   }
   float m = -FLT_MAX;
   int idx = -1;
-  for (int p = a; p < b; ++p) {
-    const float v = scores[p];
-    if (v == v && (idx < 0 || v > m)) {
-      m = v;
-      idx = p;
+  for (int p0 = a; p0 < b; p0 += 4 * LPS) {
+    float v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int p = p0 + u * LPS + q;
+      v[u] = p < b ? scores[p] : __builtin_nanf("");
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (v[u] == v[u] && (idx < 0 || v[u] > m)) {
+        m = v[u];
+        idx = p0 + u * LPS + q;
+      }
+  }
+#pragma unroll
+  for (int o = LPS / 2; o >= 1; o >>= 1) {
+    const float mo = __shfl_xor(m, o, LPS);
+    const int io = __shfl_xor(idx, o, LPS);
+    if (io >= 0 && (idx < 0 || mo > m || (mo == m && io < idx))) {
+      m = mo;
+      idx = io;
     }
   }
-  best[c] = idx < 0 ? -INFINITY : m;
-  best_idx[c] = idx;
-}
-
-// state: [0] prefix (uint64), [1] mask of decided bits, [2] k remaining
-__global__ void k_topk_init(uint32_t *hist, uint64_t *state, int k) {
-  for (int i = threadIdx.x; i < 256; i += blockDim.x) hist[i] = 0;
-  if (threadIdx.x == 0) {
-    state[0] = 0;
-    state[1] = 0;
-    state[2] = (uint64_t)k;
-    state[3] = 0;  // collected count
+  if (q == 0) {
+    best[c] = idx < 0 ? -INFINITY : m;
+    best_idx[c] = idx;
   }
 }
 
-__global__ __launch_bounds__(kSelThreads) void k_topk_hist(const float *__restrict__ v, int n, int shift,
-                                                           uint32_t *hist, const uint64_t *state) {
+// bitonic sort of m (a power of two) keys in LDS by nth threads, descending
+__device__ inline void sort_keys(uint64_t *s, int m, int nth) {
+  for (int size = 2; size <= m; size <<= 1)
+    for (int stride = size >> 1; stride > 0; stride >>= 1) {
+      for (int i = threadIdx.x; i < m; i += nth) {
+        const int j = i ^ stride;
+        if (j > i) {
+          const bool desc = (i & size) == 0;
+          const uint64_t a = s[i], b = s[j];
+          if (desc ? (a < b) : (a > b)) {
+            s[i] = b;
+            s[j] = a;
+          }
+        }
+      }
+      __syncthreads();
+    }
+}
+
+// ---- up to kSmallN values: one workgroup ----
+
+constexpr int kSmallT = 1024, kSmallN = 64 * kSmallT, kSmallCap = 8192;
+
+// E values per thread, n <= E * 1024, 1 <= k <= min(n, 1024)
+template <int E>
+__global__ __launch_bounds__(kSmallT) void k_topk_small(const float *__restrict__ v, int n, int k,
+                                                       int32_t *__restrict__ idx_out, float *__restrict__ val_out) {
+  __shared__ uint64_t cand[kSmallCap];
+  __shared__ uint32_t thr;
+  __shared__ int cnt, total[2];
+  const int tid = threadIdx.x, lane = tid & 63;
+  uint32_t key[E];  // images of the values e * 1024 + tid; 0 past the end (as a NaN's, but never counted)
+  uint32_t mx = 0;
+  // buffer loads: one offset register for all of them (past the end they return zero)
+  const __amdgpu_buffer_rsrc_t rs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(v), (short)0, n * 4, 0x00020000);
+#pragma unroll
+  for (int e = 0; e < E; ++e) key[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, tid * 4, e * kSmallT * 4, 0);
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    key[e] = e * kSmallT + tid < n ? (uint32_t)(topk_key(__uint_as_float(key[e]), 0) >> 32) : 0u;
+    mx = key[e] > mx ? key[e] : mx;
+  }
+  uint32_t *maxima = reinterpret_cast<uint32_t *>(cand);
+  maxima[tid] = mx;
+  if (tid == 0) cnt = 0;
+  __syncthreads();
+  if (tid < 64) {  // the k-th largest of the maxima: the largest t that at least k of them reach
+    uint32_t q[kSmallT / 64];
+#pragma unroll
+    for (int u = 0; u < kSmallT / 64; ++u) q[u] = maxima[u * 64 + lane];
+    uint32_t t = 0;
+    for (int bit = 31; bit >= 0; --bit) {
+      const uint32_t c = t | 1u << bit;
+      int have = 0;
+#pragma unroll
+      for (int u = 0; u < kSmallT / 64; ++u) have += __popcll(__ballot(q[u] >= c));
+      if (have >= k) t = c;
+    }
+    if (lane == 0) thr = t;
+  }
+  __syncthreads();
+  const uint32_t lo = thr;
+  // keys at or above the bound (each key's slot is arbitrary: they are sorted)
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int i = e * kSmallT + tid;
+    if (i < n && key[e] >= lo) {
+      const int slot = atomicAdd(&cnt, 1);
+      if (slot < kSmallCap) cand[slot] = ((uint64_t)key[e] << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i);
+    }
+  }
+  __syncthreads();
+  int m = cnt;
+  if (m > kSmallCap) {
+    // exact: the largest value image t that at least k values reach, then the smallest index
+    // bound x such that k keys are above t or at t with an index below x
+    auto count = [&](auto pred, int slot) {
+      int c = 0;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int i = e * kSmallT + tid;
+        c += i < n && pred(key[e], i) ? 1 : 0;
+      }
+      for (int o = 32; o >= 1; o >>= 1) c += __shfl_xor(c, o, 64);
+      if (lane == 0 && c) atomicAdd(&total[slot], c);
+    };
+    auto reach = [&](auto pred, int step) {  // number of keys for which pred holds
+      const int slot = step & 1;
+      if (tid == 0) total[slot] = 0;
+      __syncthreads();
+      count(pred, slot);
+      __syncthreads();
+      return total[slot];
+    };
+    uint32_t t = 0;
+    int step = 0;
+    for (int bit = 31; bit >= 0; --bit) {
+      const uint32_t c = t | 1u << bit;
+      if (reach([&](uint32_t y, int) { return y >= c; }, step++) >= k) t = c;
+    }
+    uint32_t below = 0;  // the largest x with fewer than k such keys; the k-th has index x
+    for (int bit = 16; bit >= 0; --bit) {
+      const uint32_t x = below | 1u << bit;
+      if (reach([&](uint32_t y, int i) { return y > t || (y == t && (uint32_t)i < x); }, step++) < k) below = x;
+    }
+    __syncthreads();
+    if (tid == 0) cnt = 0;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = e * kSmallT + tid;
+      if (i < n && (key[e] > t || (key[e] == t && (uint32_t)i <= below))) {
+        const int slot = atomicAdd(&cnt, 1);
+        if (slot < kSmallCap) cand[slot] = ((uint64_t)key[e] << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i);
+      }
+    }
+    __syncthreads();
+    m = cnt;
+  }
+  int p2 = 1;
+  while (p2 < m) p2 <<= 1;
+  for (int i = m + tid; i < p2; i += kSmallT) cand[i] = 0ull;
+  __syncthreads();
+  sort_keys(cand, p2, kSmallT);
+  for (int i = tid; i < k; i += kSmallT) {
+    const int j = (int)(0xFFFFFFFFu - (uint32_t)(cand[i] & 0xFFFFFFFFu));
+    idx_out[i] = j;
+    if (val_out) val_out[i] = v[j];
+  }
+}
+
+// ---- more values: radix select ----
+
+// state: [0] prefix (uint64), [1] mask of decided bits, [2] k remaining, [3] collected
+// count, [4] workgroups done with the pass, [5] 1 when the prefix already cuts off exactly k keys
+__global__ void k_topk_init(uint32_t *hist, uint64_t *state, int k) {
+  for (int i = threadIdx.x; i < 256; i += blockDim.x) hist[i] = 0;
+  if (threadIdx.x < 6) state[threadIdx.x] = threadIdx.x == 2 ? (uint64_t)k : 0;
+}
+
+// One digit: histogram of the keys under the prefix; the last workgroup chooses the digit
+// whose bucket holds the k-th largest key and clears the histogram for the next pass.
+__global__ __launch_bounds__(kSelThreads) void k_topk_digit(const float *__restrict__ v, int n, int shift,
+                                                            uint32_t *hist, uint64_t *state) {
   __shared__ uint32_t h[256];
-  for (int i = threadIdx.x; i < 256; i += blockDim.x) h[i] = 0;
+  __shared__ bool last;
+  if (state[5]) return;  // written by an earlier launch only: the same for all workgroups
+  h[threadIdx.x] = 0;
   __syncthreads();
   const uint64_t prefix = state[0], mask = state[1];
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    const uint64_t key = topk_key(v[i], i);
+  for (int64_t i = blockIdx.x * (int64_t)kSelThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kSelThreads) {
+    const uint64_t key = topk_key(v[i], (int)i);
     if ((key & mask) == prefix) atomicAdd(&h[(key >> shift) & 0xFF], 1u);
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < 256; i += blockDim.x)
-    if (h[i]) atomicAdd(&hist[i], h[i]);
-}
-
-// one thread: choose the digit whose bucket holds the k-th largest key, then
-// clear the histogram for the next pass
-__global__ void k_topk_pick(uint32_t *hist, uint64_t *state, int shift) {
-  if (threadIdx.x == 0) {
-    uint64_t krem = state[2];
-    int d = 255;
-    for (; d > 0; --d) {
-      if (hist[d] >= krem) break;
-      krem -= hist[d];
-    }
-    state[0] |= (uint64_t)d << shift;
-    state[1] |= (uint64_t)0xFF << shift;
-    state[2] = krem;
-  }
+  if (h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
+  __threadfence();
   __syncthreads();
-  for (int i = threadIdx.x; i < 256; i += blockDim.x) hist[i] = 0;
+  if (threadIdx.x == 0)
+    last = atomicAdd(reinterpret_cast<unsigned long long *>(&state[4]), 1ull) == (unsigned long long)gridDim.x - 1;
+  __syncthreads();
+  if (!last) return;
+  __threadfence();
+  // counts of all workgroups (read past the caches of this one), suffix sums over the digits
+  const uint32_t own = atomicAdd(&hist[threadIdx.x], 0u);
+  h[threadIdx.x] = own;
+  __syncthreads();
+  for (int o = 1; o < 256; o <<= 1) {
+    const uint32_t add = threadIdx.x + o < 256 ? h[threadIdx.x + o] : 0u;
+    __syncthreads();
+    h[threadIdx.x] += add;
+    __syncthreads();
+  }
+  const uint64_t krem = state[2];
+  const uint64_t at = h[threadIdx.x], above = at - own;  // keys with this digit or a larger one; a larger one
+  if (above < krem && at >= krem) {                      // exactly one digit
+    state[0] = prefix | (uint64_t)threadIdx.x << shift;
+    state[1] = mask | (uint64_t)0xFF << shift;
+    state[2] = krem - above;
+    state[4] = 0;
+    state[5] = krem - above == own ? 1 : 0;  // the whole bucket: no key below it has to be told apart
+  }
+  hist[threadIdx.x] = 0;
 }
 
 __global__ __launch_bounds__(kSelThreads) void k_topk_collect(const float *__restrict__ v, int n, uint64_t *state,
                                                               uint64_t *cand, int k) {
-  const uint64_t thr = state[0];  // the k-th largest key (all keys are distinct)
+  const uint64_t thr = state[0];  // exactly k keys are at or above it (all keys are distinct)
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     const uint64_t key = topk_key(v[i], i);
     if (key >= thr) {
@@ -123,22 +296,7 @@ __global__ __launch_bounds__(1024) void k_topk_sort(const uint64_t *cand, int k,
   while (m < k) m <<= 1;
   for (int i = threadIdx.x; i < m; i += blockDim.x) s[i] = i < k ? cand[i] : 0ull;
   __syncthreads();
-  for (int size = 2; size <= m; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int i = threadIdx.x; i < m; i += blockDim.x) {
-        const int j = i ^ stride;
-        if (j > i) {
-          const bool desc = (i & size) == 0;
-          const uint64_t a = s[i], b = s[j];
-          if (desc ? (a < b) : (a > b)) {
-            s[i] = b;
-            s[j] = a;
-          }
-        }
-      }
-      __syncthreads();
-    }
-  }
+  sort_keys(s, m, 1024);
   for (int i = threadIdx.x; i < k; i += blockDim.x) {
     const int idx = (int)(0xFFFFFFFFu - (uint32_t)(s[i] & 0xFFFFFFFFu));
     idx_out[i] = idx;
@@ -151,8 +309,13 @@ __global__ __launch_bounds__(1024) void k_topk_sort(const uint64_t *cand, int k,
 hipError_t launch_segmax(const float *scores, int n_scores, const int32_t *off, int n_seg, float *best,
                          int32_t *best_idx, int64_t *status, hipStream_t s) {
   if (n_seg <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_segmax, dim3((n_seg + kSelThreads - 1) / kSelThreads), dim3(kSelThreads), 0, s, scores,
-                     n_scores, off, n_seg, best, best_idx, status);
+  // 8 lanes per segment (a compound has up to 40 poses), a wave where segments are long
+  if ((int64_t)n_scores > 128 * (int64_t)n_seg)
+    hipLaunchKernelGGL(k_segmax<64>, dim3((unsigned)(((int64_t)n_seg * 64 + kSelThreads - 1) / kSelThreads)),
+                       dim3(kSelThreads), 0, s, scores, n_scores, off, n_seg, best, best_idx, status);
+  else
+    hipLaunchKernelGGL(k_segmax<8>, dim3((unsigned)(((int64_t)n_seg * 8 + kSelThreads - 1) / kSelThreads)),
+                       dim3(kSelThreads), 0, s, scores, n_scores, off, n_seg, best, best_idx, status);
   return hipGetLastError();
 }
 
@@ -188,15 +351,22 @@ hipError_t topk_static_scratch(void **out) {
 
 hipError_t launch_topk(const float *v, int n, int k, int32_t *idx_out, float *val_out, void *scratch,
                        hipStream_t s) {
+  if (n <= kSmallN && k <= kTopkMaxK) {
+    if (n <= 4 * kSmallT)
+      hipLaunchKernelGGL(k_topk_small<4>, dim3(1), dim3(kSmallT), 0, s, v, n, k, idx_out, val_out);
+    else if (n <= 16 * kSmallT)
+      hipLaunchKernelGGL(k_topk_small<16>, dim3(1), dim3(kSmallT), 0, s, v, n, k, idx_out, val_out);
+    else
+      hipLaunchKernelGGL(k_topk_small<64>, dim3(1), dim3(kSmallT), 0, s, v, n, k, idx_out, val_out);
+    return hipGetLastError();
+  }
   uint32_t *hist = reinterpret_cast<uint32_t *>(scratch);
   uint64_t *state = reinterpret_cast<uint64_t *>(reinterpret_cast<char *>(scratch) + 1024);
   uint64_t *cand = reinterpret_cast<uint64_t *>(reinterpret_cast<char *>(scratch) + 1024 + 64);
   const int blocks = (int)std::min<int64_t>(1024, ((int64_t)n + kSelThreads - 1) / kSelThreads);
   hipLaunchKernelGGL(k_topk_init, dim3(1), dim3(256), 0, s, hist, state, k);
-  for (int shift = 56; shift >= 0; shift -= 8) {
-    hipLaunchKernelGGL(k_topk_hist, dim3(blocks), dim3(kSelThreads), 0, s, v, n, shift, hist, state);
-    hipLaunchKernelGGL(k_topk_pick, dim3(1), dim3(256), 0, s, hist, state, shift);
-  }
+  for (int shift = 56; shift >= 0; shift -= 8)
+    hipLaunchKernelGGL(k_topk_digit, dim3(blocks), dim3(kSelThreads), 0, s, v, n, shift, hist, state);
   hipLaunchKernelGGL(k_topk_collect, dim3(blocks), dim3(kSelThreads), 0, s, v, n, state, cand, k);
   hipLaunchKernelGGL(k_topk_sort, dim3(1), dim3(1024), 0, s, cand, k, v, idx_out, val_out);
   return hipGetLastError();
