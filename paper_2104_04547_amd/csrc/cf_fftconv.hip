@@ -118,6 +118,25 @@ __device__ inline void spec_put(void *Ov, int col, int c, float r, float i) {
   O[(col * 8 + 4 + (c >> 1)) * 2 + (c & 1)] = (uint16_t)(two >> 16);
 }
 
+// A plane's spectrum into LDS, all 256 threads: src is column 0's chunk (64 bytes of fp32,
+// 32 of bf16), columns colstride elements apart.  All of a thread's loads are in flight
+// together.
+template <typename T>
+__device__ inline void spec_load(T *Y, const T *src, int64_t colstride, int tid) {
+  constexpr int kQ = sizeof(T), kE = 16 / sizeof(T), kU = (kCols * kQ + 255) / 256;  // kQ 16-byte pieces a column
+  const int hh = tid % kQ, col0 = tid / kQ;
+  uint4 raw[kU];
+#pragma unroll
+  for (int u = 0; u < kU; ++u) {
+    const int col = (u + 1) * (256 / kQ) <= kCols ? col0 + u * (256 / kQ) : min(col0 + u * (256 / kQ), kCols - 1);
+    raw[u] = *reinterpret_cast<const uint4 *>(src + col * colstride + hh * kE);
+  }
+#pragma unroll
+  for (int u = 0; u < kU; ++u)
+    if ((u + 1) * (256 / kQ) <= kCols || col0 + u * (256 / kQ) < kCols)
+      *reinterpret_cast<uint4 *>(Y + (col0 + u * (256 / kQ)) * 16 + hh * kE) = raw[u];
+}
+
 // inverse, all 256 threads (ky = tid >> 3, c = tid & 7): Zp[ky][c] = H(Y0)[ky] + i H(Y16)[ky]
 template <bool F32>
 __device__ inline void dc_nyquist_pack(const void *Y, float2 *Zp, int tid) {
@@ -144,16 +163,139 @@ __device__ inline void dc_nyquist_split(const float2 *Zp, void *O, int tid) {
 // ---------------------------------------------------------------- lane-pair transforms
 //
 // Every 32-point FFT of the plane kernels is shared by two adjacent lanes
-// (fft32_pair_dit / fft32_pair_dif): the column phases run on all 256 threads
+// (fft32_lanes_dit / fft32_lanes_dif): the column phases run on all 256 threads
 // (128 (column, channel) pairs) and the row phase on 8 D threads, each lane
 // holding 16 points instead of 32, so that all four waves work in every phase and
-// the register file holds half the transform state (at 24^3: 118 VGPRs for the
-// fused transform against 153 with one transform per lane, four waves per SIMD
-// instead of three).  Lane h = tid & 1 of a pair, partner tid ^ 1 (a quad
-// permutation, so the exchange is a DPP move).
+// the register file holds half the transform state (at 24^3: 82 VGPRs for the
+// fused transform, five workgroups per CU; 153 with one transform per lane).  Lane h = tid & 1 of a pair, partner tid ^ 1 (a quad
+// permutation, so the exchange is a DPP operand).
 
-__device__ inline float pair_swap(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));  // lanes 1,0,3,2
+// (r, i) times e^{-+2 pi i t / 32}, t = 0 .. 15 (NEG: times minus that), in place.  Which
+// product of each part is rounded by itself is written out: left to the compiler, it
+// depends on the code around the transform.
+template <bool INV, bool NEG = false>
+__device__ inline void lane_twiddle(float &r, float &i, int t) {
+  const float c = NEG ? -kFftCos32[t] : kFftCos32[t], s = NEG ? -kFftSin32[t] : kFftSin32[t];
+  if (t == 0) {
+    r *= c;
+    i *= c;
+  } else if (t == 8) {
+    const float is = INV ? i * -s : i * s;
+    i = INV ? r * s : r * -s;
+    r = is;
+  } else if (INV) {
+    const float is = i * -s, ic = i * c;
+    i = __builtin_fmaf(r, s, ic);
+    r = __builtin_fmaf(r, c, is);
+  } else if (NEG && t < 8 && t != 4) {
+    const float is = i * s, rs = r * -s;
+    i = __builtin_fmaf(i, c, rs);
+    r = __builtin_fmaf(r, c, is);
+  } else {
+    const float rs = r * -s, rc = r * c;
+    r = __builtin_fmaf(i, s, rc);
+    i = __builtin_fmaf(i, c, rs);
+  }
+}
+
+// fft16 with those multiplications
+template <bool INV>
+__device__ inline void lane_fft16(float (&re)[16], float (&im)[16]) {
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int j = ((i & 1) << 3) | ((i & 2) << 1) | ((i & 4) >> 1) | ((i & 8) >> 3);
+    if (j > i) {
+      const float tr = re[i], ti = im[i];
+      re[i] = re[j];
+      im[i] = im[j];
+      re[j] = tr;
+      im[j] = ti;
+    }
+  }
+#pragma unroll
+  for (int half = 1; half < 16; half <<= 1) {
+#pragma unroll
+    for (int a = 0; a < 16; ++a) {
+      if (a & half) continue;
+      const int b = a + half;
+      float br = re[b], bi = im[b];
+      lane_twiddle<INV>(br, bi, (a & (half - 1)) * (16 / half));
+      re[b] = re[a] - br;
+      im[b] = im[a] - bi;
+      re[a] = re[a] + br;
+      im[a] = im[a] + bi;
+    }
+  }
+}
+
+// v[k] += s * (the value of v[k] in the neighbouring lane, lane ^ 1), k = 0 .. 15: a
+// multiply-add that reads the other lane by itself (the compiler makes a move and a
+// multiply-add of it).  A lane reads registers that the instructions before have
+// written, which takes two wait states: the s_nop.
+__device__ inline void pair_fma(float (&v)[16], float s) {
+#define CF_PAIR_FMA(n) "v_fmac_f32_dpp %" #n ", %" #n ", %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+#pragma unroll
+  for (int o = 0; o < 16; o += 8)
+    asm volatile("s_nop 1\n\t" CF_PAIR_FMA(0) CF_PAIR_FMA(1) CF_PAIR_FMA(2) CF_PAIR_FMA(3) CF_PAIR_FMA(4)
+                     CF_PAIR_FMA(5) CF_PAIR_FMA(6) CF_PAIR_FMA(7)
+                 : "+v"(v[o]), "+v"(v[o + 1]), "+v"(v[o + 2]), "+v"(v[o + 3]), "+v"(v[o + 4]), "+v"(v[o + 5]),
+                   "+v"(v[o + 6]), "+v"(v[o + 7])
+                 : "v"(s));
+#undef CF_PAIR_FMA
+}
+
+// fft32_pair_dit and fft32_pair_dif on two neighbouring lanes.  The half h = 1 is held
+// negated across the exchange (by its twiddles, which is exact), so both lanes combine as
+// mine + s * theirs with a sign s = +-1 per lane, in place of an add, a subtract, a
+// select and a move for each value.
+template <bool INV>
+__device__ inline void fft32_lanes_dit(float (&re)[16], float (&im)[16], int h) {
+  lane_fft16<INV>(re, im);
+  if (h) {
+#pragma unroll
+    for (int k = 0; k < 16; ++k) lane_twiddle<INV, true>(re[k], im[k], k);
+  }
+  const float s = h ? 1.0f : -1.0f;
+  pair_fma(re, s);
+  pair_fma(im, s);
+}
+
+template <bool INV>
+__device__ inline void fft32_lanes_dif(float (&re)[16], float (&im)[16], int h) {
+  const float s = h ? -1.0f : 1.0f;
+  pair_fma(re, s);
+  pair_fma(im, s);
+  if (h) {
+#pragma unroll
+    for (int n = 0; n < 16; ++n) lane_twiddle<INV, true>(re[n], im[n], n);
+  }
+  lane_fft16<INV>(re, im);
+}
+
+// Calls in(n) for the n = 0 .. 15 with 16 h + n < D and out(n) for the others, with one
+// branch on the lane's half where D is a constant (a test per n costs a mask, a branch
+// and a wait each).
+template <int DT, typename In, typename Out>
+__device__ inline void by_half(int h, int D, In in, Out out) {
+  if constexpr (DT == 0) {
+#pragma unroll
+    for (int n = 0; n < 16; ++n)
+      if (16 * h + n < D) in(n);
+      else out(n);
+  } else {
+    constexpr int both = DT > 16 ? DT - 16 : 0, lower = DT < 16 ? DT : 16;
+#pragma unroll
+    for (int n = 0; n < both; ++n) in(n);
+    if (!h) {
+#pragma unroll
+      for (int n = both; n < lower; ++n) in(n);
+    } else {
+#pragma unroll
+      for (int n = both; n < lower; ++n) out(n);
+    }
+#pragma unroll
+    for (int n = lower; n < 16; ++n) out(n);
+  }
 }
 
 // inverse columns, decimation in time: lane h takes ky = 2n + h (columns 1 .. 15
@@ -171,13 +313,13 @@ __device__ inline void col_inv_load_dc2(const float2 *Zp, int c, int h, float (&
     im[n] = v.y;
   }
 }
-// after fft32_pair_dit<true>: lane h holds y = 16 h + k; rows y < D of T
+// after fft32_lanes_dit<true>: lane h holds y = 16 h + k; rows y < D of T
+template <int DT>
 __device__ inline void col_inv_store2(float2 *T, int kxp, int c, int h, int D, const float (&re)[16],
                                       const float (&im)[16]) {
   const int DP = D + 1;
-#pragma unroll
-  for (int k = 0; k < 16; ++k)
-    if (16 * h + k < D) T[(kxp * DP + 16 * h + k) * 8 + c] = make_float2(re[k], im[k]);
+  by_half<DT>(
+      h, D, [&](int k) { T[(kxp * DP + 16 * h + k) * 8 + c] = make_float2(re[k], im[k]); }, [](int) {});
 }
 // rows, inverse: lane h takes Z[2n + h] of the complex sequence A + i B of the two
 // channels' Hermitian halves (Z[0], Z[16] from the packed column)
@@ -201,7 +343,7 @@ __device__ inline void row_inv_load2(const float2 *T, int y, int c0, int h, int 
     }
   }
 }
-// rows, forward, after fft32_pair_dif<false> (lane h holds X[2m + h]): the row
+// rows, forward, after fft32_lanes_dif<false> (lane h holds X[2m + h]): the row
 // spectra of the two channels at the frequencies of this lane's parity
 __device__ inline void row_fwd_store2(float2 *T, int y, int c0, int h, int D, const float (&re)[16],
                                       const float (&im)[16]) {
@@ -210,24 +352,40 @@ __device__ inline void row_fwd_store2(float2 *T, int y, int c0, int h, int D, co
 #pragma unroll
   for (int m = 0; m < 8; ++m) {
     const int k = 2 * m + h;  // 1 .. 15 (k = 0 is the packed column)
-    if (k == 0) continue;
-    const int j = 16 - m - h;  // index of X[32 - k] in this lane
-    *reinterpret_cast<float4 *>(T + (k * DP + y) * 8 + c0) =
-        make_float4(0.5f * (re[m] + re[j]), 0.5f * (im[m] - im[j]), 0.5f * (im[m] + im[j]), -0.5f * (re[m] - re[j]));
+    // X[32 - k], value 16 - m - h of this lane (selected: an index that depends on the
+    // lane would search the sixteen registers)
+    const float r1 = re[15 - m], i1 = im[15 - m], r0 = re[(16 - m) & 15], i0 = im[(16 - m) & 15];
+    const float rj = h ? r1 : r0, ij = h ? i1 : i0;
+    if (m || h)
+      *reinterpret_cast<float4 *>(T + (k * DP + y) * 8 + c0) =
+          make_float4(0.5f * (re[m] + rj), 0.5f * (im[m] - ij), 0.5f * (im[m] + ij), -0.5f * (re[m] - rj));
   }
 }
 // forward columns, decimation in frequency: lane h takes y = 16 h + n (zero past D)
+template <int DT>
 __device__ inline void col_fwd_load2(const float2 *T, int kxp, int c, int h, int D, float (&re)[16], float (&im)[16]) {
   const int DP = D + 1;
+  constexpr int both = DT > 16 ? DT - 16 : 0;
 #pragma unroll
   for (int n = 0; n < 16; ++n) {
-    const int y = 16 * h + n;
-    const float2 v = y < D ? T[(kxp * DP + y) * 8 + c] : make_float2(0.0f, 0.0f);
-    re[n] = v.x;
-    im[n] = v.y;
+    re[n] = im[n] = 0.0f;
+    if (n < both) {
+      const float2 v = T[(kxp * DP + 16 * h + n) * 8 + c];
+      re[n] = v.x;
+      im[n] = v.y;
+    }
+  }
+  if (DT == 0 || !h) {
+#pragma unroll
+    for (int n = both; n < 16; ++n)
+      if (16 * h + n < D) {
+        const float2 v = T[(kxp * DP + 16 * h + n) * 8 + c];
+        re[n] = v.x;
+        im[n] = v.y;
+      }
   }
 }
-// after fft32_pair_dif<false>: lane h holds ky = 2m + h of column kxp (spectrum), or
+// after fft32_lanes_dif<false>: lane h holds ky = 2m + h of column kxp (spectrum), or
 // of the packed column (Zp)
 template <bool F32>
 __device__ inline void col_fwd_store2(void *O, float2 *Zp, int kxp, int c, int h, const float (&re)[16],
@@ -306,7 +464,7 @@ __global__ __launch_bounds__(256) void k_fft_fwd2d_t(const void *__restrict__ in
     }
     __syncthreads();  // the plane is in registers; its LDS becomes the row spectra
     if (roww) {
-      fft32_pair_dif<false>(re, im, h, pair_swap);
+      fft32_lanes_dif<false>(re, im, h);
       row_fwd_store2(T, wy, c0, h, W, re, im);
     }
   }
@@ -322,7 +480,7 @@ __global__ __launch_bounds__(256) void k_fft_fwd2d_t(const void *__restrict__ in
     re[n] = v.x;
     im[n] = v.y;
   }
-  fft32_pair_dif<false>(re, im, h, pair_swap);
+  fft32_lanes_dif<false>(re, im, h);
   __syncthreads();
   act_t *O = reinterpret_cast<act_t *>(T);  // [col][re | im][8]
   float2 *Zp = reinterpret_cast<float2 *>(dyn_lds + plane_lds_bytes(W, F32));
@@ -346,11 +504,21 @@ __global__ __launch_bounds__(256) void k_fft_fwd2d_t(const void *__restrict__ in
 // One workgroup per (z, pose, chunk), grid (D, np, nch) in XCD order; the chunking
 // of layer i's output is the chunking of layer i + 1's input.  LDS: the spectrum /
 // row spectra (fft_lds_bytes) and, with a residual or a stored output, the
-// activation plane [y][x][8].  The residual (RES) and the stored output (OUT) are
+// activation plane [y][x][8].
+//
+// Bound by vector arithmetic (its instructions fill 69 % of the SIMDs' cycles at 16^3),
+// then by memory: what counts is instructions per plane.  The exchange of a lane pair as
+// one multiply-add per value, the mirrored half of a row's spectrum by a select of two
+// registers (an index that depends on the lane cost 330 instructions), one branch per
+// half in place of one per value, and a plane's loads in flight together took 2230
+// instructions of a wave to 1630: 137 -> 118 us for 77 poses of 16^3 x 64, 1.65 -> 1.45 ms
+// for 512 of 24^3, with the same bits.
+//
+// The residual (RES) and the stored output (OUT) are
 // template arguments: as run-time tests they put a branch and a wait on each
 // value's residual read inside the epilogue of the row transforms.
 template <int DT, bool F32, bool RES, bool OUT>
-__global__ __launch_bounds__(256) void k_fft_mid(const void *__restrict__ ys_v, const float *__restrict__ bias,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(F32 || RES ? 4 : 5))) void k_fft_mid(const void *__restrict__ ys_v, const float *__restrict__ bias,
                                                   const void *__restrict__ res_v, void *__restrict__ out_v,
                                                   void *__restrict__ xs_v, int np, int D_rt, int nch, int cout_store,
                                                   int lds_spec) {
@@ -371,11 +539,7 @@ __global__ __launch_bounds__(256) void k_fft_mid(const void *__restrict__ ys_v, 
   const int tid = threadIdx.x, h = tid & 1, q = tid >> 1;
   const int64_t rowb = (int64_t)nch * 16;
   const int64_t base = (((int64_t)p * D + z) * D * D) * cout_store + chunk * 8;
-  for (int e = tid; e < kCols * kQ; e += 256) {
-    const int col = e / kQ, hh = e % kQ;
-    *reinterpret_cast<uint4 *>(Y + col * 16 + hh * (16 / kEsz)) = *reinterpret_cast<const uint4 *>(
-        ys + (((int64_t)col * np + p) * D + z) * rowb + chunk * 16 + hh * (16 / kEsz));
-  }
+  spec_load(Y, ys + ((int64_t)p * D + z) * rowb + chunk * 16, (int64_t)np * D * rowb, tid);
   if constexpr (RES)
     for (int v = tid; v < D * D; v += 256)
 #pragma unroll
@@ -387,11 +551,11 @@ __global__ __launch_bounds__(256) void k_fft_mid(const void *__restrict__ ys_v, 
   {
     float re[16], im[16];
     dc_nyquist_pack<F32>(Y, Zp, tid);
-    if (kxp) col_inv_load2<F32>(Y, kxp, c, h, re, im);
+    col_inv_load2<F32>(Y, kxp, c, h, re, im);
     __syncthreads();
     if (!kxp) col_inv_load_dc2(Zp, c, h, re, im);
-    fft32_pair_dit<true>(re, im, h, pair_swap);
-    col_inv_store2(T, kxp, c, h, D, re, im);
+    fft32_lanes_dit<true>(re, im, h);
+    col_inv_store2<DT>(T, kxp, c, h, D, re, im);
   }
   __syncthreads();
   // rows along x: inverse of two channels, epilogue (bf16 rounding in the bf16
@@ -402,44 +566,39 @@ __global__ __launch_bounds__(256) void k_fft_mid(const void *__restrict__ ys_v, 
     float re[16], im[16];
     if (roww) {
       row_inv_load2(T, y, c0, h, D, re, im);
-      fft32_pair_dit<true>(re, im, h, pair_swap);
+      fft32_lanes_dit<true>(re, im, h);
       constexpr float kScale = 1.0f / (kN * kN);
       const float b0 = bias[chunk * 8 + c0], b1 = bias[chunk * 8 + c0 + 1];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int x = 16 * h + j;
-        if (x < D) {
-          float v0 = re[j] * kScale + b0, v1 = im[j] * kScale + b1;
-          if constexpr (F32) {
-            if constexpr (RES) {
-              const float2 two = *reinterpret_cast<const float2 *>(R + (y * D + x) * 8 + c0);
-              v0 += two.x;
-              v1 += two.y;
+      by_half<DT>(
+          h, D,
+          [&](int j) {
+            const int x = 16 * h + j;
+            float v0 = re[j] * kScale + b0, v1 = im[j] * kScale + b1;
+            if constexpr (F32) {
+              if constexpr (RES) {
+                const float2 two = *reinterpret_cast<const float2 *>(R + (y * D + x) * 8 + c0);
+                v0 += two.x;
+                v1 += two.y;
+              }
+              v0 = v0 > 0.0f ? v0 : 0.0f;
+              v1 = v1 > 0.0f ? v1 : 0.0f;
+              if constexpr (OUT) *reinterpret_cast<float2 *>(R + (y * D + x) * 8 + c0) = make_float2(v0, v1);
+              re[j] = v0;
+              im[j] = v1;
+            } else {
+              if constexpr (RES) {
+                const uint32_t two = *reinterpret_cast<const uint32_t *>(R + (y * D + x) * 8 + c0);
+                v0 += __uint_as_float(two << 16);
+                v1 += __uint_as_float(two & 0xffff0000u);
+              }
+              const uint32_t two = pack_bf16x2(v0 > 0.0f ? v0 : 0.0f, v1 > 0.0f ? v1 : 0.0f);
+              if constexpr (OUT) *reinterpret_cast<uint32_t *>(R + (y * D + x) * 8 + c0) = two;
+              re[j] = __uint_as_float(two << 16);
+              im[j] = __uint_as_float(two & 0xffff0000u);
             }
-            v0 = v0 > 0.0f ? v0 : 0.0f;
-            v1 = v1 > 0.0f ? v1 : 0.0f;
-            if constexpr (OUT) *reinterpret_cast<float2 *>(R + (y * D + x) * 8 + c0) = make_float2(v0, v1);
-            re[j] = v0;
-            im[j] = v1;
-          } else {
-            if constexpr (RES) {
-              const uint32_t two = *reinterpret_cast<const uint32_t *>(R + (y * D + x) * 8 + c0);
-              v0 += __uint_as_float(two << 16);
-              v1 += __uint_as_float(two & 0xffff0000u);
-            }
-            const bf16_t h0 = (bf16_t)(v0 > 0.0f ? v0 : 0.0f), h1 = (bf16_t)(v1 > 0.0f ? v1 : 0.0f);
-            if constexpr (OUT)
-              *reinterpret_cast<uint32_t *>(R + (y * D + x) * 8 + c0) =
-                  (uint32_t)__builtin_bit_cast(uint16_t, h0) | ((uint32_t)__builtin_bit_cast(uint16_t, h1) << 16);
-            re[j] = (float)h0;
-            im[j] = (float)h1;
-          }
-        } else {
-          re[j] = 0.0f;
-          im[j] = 0.0f;
-        }
-      }
-      fft32_pair_dif<false>(re, im, h, pair_swap);
+          },
+          [&](int j) { re[j] = im[j] = 0.0f; });
+      fft32_lanes_dif<false>(re, im, h);
       // no barrier between reading and rewriting T: each lane reads the row spectra
       // at the frequencies of its own parity (the mirror 32 - k has the same parity)
       // and writes back exactly those slots; the partner's values came by DPP
@@ -454,8 +613,8 @@ __global__ __launch_bounds__(256) void k_fft_mid(const void *__restrict__ ys_v, 
         reinterpret_cast<uint4 *>(out + base + (int64_t)v * cout_store)[qq] = reinterpret_cast<const uint4 *>(R + v * 8)[qq];
   // forward columns along y
   float re[16], im[16];
-  col_fwd_load2(T, kxp, c, h, D, re, im);
-  fft32_pair_dif<false>(re, im, h, pair_swap);
+  col_fwd_load2<DT>(T, kxp, c, h, D, re, im);
+  fft32_lanes_dif<false>(re, im, h);
   __syncthreads();
   act_t *O = reinterpret_cast<act_t *>(T);
   col_fwd_store2<F32>(O, Zp, kxp, c, h, re, im);
@@ -525,7 +684,7 @@ __global__ __launch_bounds__(256) void k_fft_fwd2d(const void *__restrict__ in_v
     }
     __syncthreads();  // the plane is in registers; its LDS becomes the row spectra
     if (roww) {
-      fft32_pair_dif<false>(re, im, h, pair_swap);
+      fft32_lanes_dif<false>(re, im, h);
       row_fwd_store2(T, y, c0, h, D, re, im);
     }
   }
@@ -533,8 +692,8 @@ __global__ __launch_bounds__(256) void k_fft_fwd2d(const void *__restrict__ in_v
   // columns along y
   const int kxp = q >> 3, c = q & 7;
   float re[16], im[16];
-  col_fwd_load2(T, kxp, c, h, D, re, im);
-  fft32_pair_dif<false>(re, im, h, pair_swap);
+  col_fwd_load2<DT>(T, kxp, c, h, D, re, im);
+  fft32_lanes_dif<false>(re, im, h);
   __syncthreads();
   act_t *O = reinterpret_cast<act_t *>(T);  // [col][re | im][8]
   col_fwd_store2<F32>(O, Zp, kxp, c, h, re, im);
@@ -576,21 +735,17 @@ __global__ __launch_bounds__(256) void k_fft_inv2d(const void *__restrict__ ys_v
   float2 *Zp = reinterpret_cast<float2 *>(dyn_lds + plane_lds_bytes(D, F32));
   const int tid = threadIdx.x, h = tid & 1, q = tid >> 1, DP = D + 1;
   const int64_t rowb = (int64_t)nco * 16;
-  for (int e = tid; e < kCols * kQ; e += 256) {
-    const int col = e / kQ, hh = e % kQ;
-    *reinterpret_cast<uint4 *>(Y + col * 16 + hh * (16 / kEsz)) = *reinterpret_cast<const uint4 *>(
-        ys + (((int64_t)col * np + pv) * Dz + z) * rowb + chunk * 16 + hh * (16 / kEsz));
-  }
+  spec_load(Y, ys + ((int64_t)pv * Dz + z) * rowb + chunk * 16, (int64_t)np * Dz * rowb, tid);
   __syncthreads();
   const int kxp = q >> 3, c = q & 7;
   {
     float re[16], im[16];
     dc_nyquist_pack<F32>(Y, Zp, tid);
-    if (kxp) col_inv_load2<F32>(Y, kxp, c, h, re, im);
+    col_inv_load2<F32>(Y, kxp, c, h, re, im);
     __syncthreads();
     if (!kxp) col_inv_load_dc2(Zp, c, h, re, im);
-    fft32_pair_dit<true>(re, im, h, pair_swap);
-    col_inv_store2(T, kxp, c, h, D, re, im);
+    fft32_lanes_dit<true>(re, im, h);
+    col_inv_store2<DT>(T, kxp, c, h, D, re, im);
   }
   __syncthreads();
   const bool roww = tid < 8 * D;
@@ -598,18 +753,20 @@ __global__ __launch_bounds__(256) void k_fft_inv2d(const void *__restrict__ ys_v
   float re[16], im[16];
   if (roww) {
     row_inv_load2(T, y, c0, h, D, re, im);
-    fft32_pair_dit<true>(re, im, h, pair_swap);
+    fft32_lanes_dit<true>(re, im, h);
   }
   __syncthreads();  // the row spectra are read; T becomes the output plane
   float *O = reinterpret_cast<float *>(T);  // [x][y (pitch D + 1)][8] conv result + bias
   if (roww) {
     constexpr float kScale = 1.0f / (kN * kN);
     const float b0 = GRAD ? 0.0f : bias[chunk * 8 + c0], b1 = GRAD ? 0.0f : bias[chunk * 8 + c0 + 1];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const int x = 16 * h + j;
-      if (x < D) *reinterpret_cast<float2 *>(O + (x * DP + y) * 8 + c0) = make_float2(re[j] * kScale + b0, im[j] * kScale + b1);
-    }
+    by_half<DT>(
+        h, D,
+        [&](int j) {
+          *reinterpret_cast<float2 *>(O + ((16 * h + j) * DP + y) * 8 + c0) =
+              make_float2(re[j] * kScale + b0, im[j] * kScale + b1);
+        },
+        [](int) {});
   }
   __syncthreads();
   const int64_t base = (((int64_t)p * Dz + z) * Dz * Dz) * cout_store + chunk * 8;
