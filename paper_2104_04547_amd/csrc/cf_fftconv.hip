@@ -298,12 +298,42 @@ __device__ inline void by_half(int h, int D, In in, Out out) {
   }
 }
 
+// The same for a tile's window, whose positions lie at first + w * pitch: in(n, p) where
+// array position 16 h + n holds the window position at p (n + P + 16 h left of the wrap,
+// n + P - 16 h right of it).  One base a lane and constant offsets from it.
+template <int TS, int P, typename E, typename In>
+__device__ inline void by_window(int h, const E *first, int pitch, In in) {
+  static_assert(TS == 16, "the wrap falls into the upper half");
+  const E *left = first + 16 * h * pitch, *right = first - 16 * h * pitch;
+#pragma unroll
+  for (int n = 0; n < P; ++n) in(n, left + (n + P) * pitch);
+  if (!h) {
+#pragma unroll
+    for (int n = P; n < 16 - P; ++n) in(n, first + (n + P) * pitch);
+  }
+#pragma unroll
+  for (int n = 16 - P; n < 16; ++n) in(n, right + (n + P) * pitch);
+}
+
+// two neighbouring channels of an activation
+__device__ inline void two_channels(const float *v, float &a, float &b) {
+  const float2 two = *reinterpret_cast<const float2 *>(v);
+  a = two.x;
+  b = two.y;
+}
+__device__ inline void two_channels(const bf16_t *v, float &a, float &b) {
+  const uint32_t two = *reinterpret_cast<const uint32_t *>(v);
+  a = __uint_as_float(two << 16);
+  b = __uint_as_float(two & 0xffff0000u);
+}
+
 // inverse columns, decimation in time: lane h takes ky = 2n + h (columns 1 .. 15
 // from the spectrum; the packed DC / Nyquist column from Zp)
 template <bool F32>
 __device__ inline void col_inv_load2(const void *Y, int kxp, int c, int h, float (&re)[16], float (&im)[16]) {
+  const char *Yh = reinterpret_cast<const char *>(Y) + (h * kNX + kxp) * (F32 ? 64 : 32);
 #pragma unroll
-  for (int n = 0; n < 16; ++n) spec_get<F32>(Y, (2 * n + h) * kNX + kxp, c, re[n], im[n]);
+  for (int n = 0; n < 16; ++n) spec_get<F32>(Yh, 2 * n * kNX, c, re[n], im[n]);
 }
 __device__ inline void col_inv_load_dc2(const float2 *Zp, int c, int h, float (&re)[16], float (&im)[16]) {
 #pragma unroll
@@ -317,9 +347,8 @@ __device__ inline void col_inv_load_dc2(const float2 *Zp, int c, int h, float (&
 template <int DT>
 __device__ inline void col_inv_store2(float2 *T, int kxp, int c, int h, int D, const float (&re)[16],
                                       const float (&im)[16]) {
-  const int DP = D + 1;
-  by_half<DT>(
-      h, D, [&](int k) { T[(kxp * DP + 16 * h + k) * 8 + c] = make_float2(re[k], im[k]); }, [](int) {});
+  float2 *t = T + (kxp * (D + 1) + 16 * h) * 8 + c;
+  by_half<DT>(h, D, [&](int k) { t[k * 8] = make_float2(re[k], im[k]); }, [](int) {});
 }
 // rows, inverse: lane h takes Z[2n + h] of the complex sequence A + i B of the two
 // channels' Hermitian halves (Z[0], Z[16] from the packed column)
@@ -364,38 +393,30 @@ __device__ inline void row_fwd_store2(float2 *T, int y, int c0, int h, int D, co
 // forward columns, decimation in frequency: lane h takes y = 16 h + n (zero past D)
 template <int DT>
 __device__ inline void col_fwd_load2(const float2 *T, int kxp, int c, int h, int D, float (&re)[16], float (&im)[16]) {
-  const int DP = D + 1;
-  constexpr int both = DT > 16 ? DT - 16 : 0;
+  const float2 *t = T + (kxp * (D + 1) + 16 * h) * 8 + c;
 #pragma unroll
-  for (int n = 0; n < 16; ++n) {
-    re[n] = im[n] = 0.0f;
-    if (n < both) {
-      const float2 v = T[(kxp * DP + 16 * h + n) * 8 + c];
-      re[n] = v.x;
-      im[n] = v.y;
-    }
-  }
-  if (DT == 0 || !h) {
-#pragma unroll
-    for (int n = both; n < 16; ++n)
-      if (16 * h + n < D) {
-        const float2 v = T[(kxp * DP + 16 * h + n) * 8 + c];
-        re[n] = v.x;
-        im[n] = v.y;
-      }
-  }
+  for (int n = 0; n < 16; ++n) re[n] = im[n] = 0.0f;
+  by_half<DT>(
+      h, D,
+      [&](int n) {
+        re[n] = t[n * 8].x;
+        im[n] = t[n * 8].y;
+      },
+      [](int) {});
 }
 // after fft32_lanes_dif<false>: lane h holds ky = 2m + h of column kxp (spectrum), or
 // of the packed column (Zp)
 template <bool F32>
 __device__ inline void col_fwd_store2(void *O, float2 *Zp, int kxp, int c, int h, const float (&re)[16],
                                       const float (&im)[16]) {
+  char *Oh = reinterpret_cast<char *>(O) + (h * kNX + kxp) * (F32 ? 64 : 32);
+  float2 *z = Zp + h * 8 + c;
   if (kxp) {
 #pragma unroll
-    for (int m = 0; m < 16; ++m) spec_put<F32>(O, (2 * m + h) * kNX + kxp, c, re[m], im[m]);
+    for (int m = 0; m < 16; ++m) spec_put<F32>(Oh, 2 * m * kNX, c, re[m], im[m]);
   } else {
 #pragma unroll
-    for (int m = 0; m < 16; ++m) Zp[(2 * m + h) * 8 + c] = make_float2(re[m], im[m]);
+    for (int m = 0; m < 16; ++m) z[m * 16] = make_float2(re[m], im[m]);
   }
 }
 
@@ -427,14 +448,26 @@ __global__ __launch_bounds__(256) void k_fft_fwd2d_t(const void *__restrict__ in
   float2 *T = reinterpret_cast<float2 *>(dyn_lds);      // [kx][wy (pitch WP)][8]
   const int tid = threadIdx.x;
   const act_t *src = in + (((int64_t)p * Dz + z) * Dz * Dz) * cin_pad + chunk * 8;
-  for (int v = tid; v < W * W; v += 256) {
-    const int wy = v / W, wx = v - wy * W;
-    const int y = y0 + wy, x = x0 + wx;
-    const bool inside = y >= 0 && y < Dz && x >= 0 && x < Dz;
+  {
+    // a thread's loads in flight together
+    constexpr int kU = (W * W + 255) / 256;
+    uint4 raw[kU][kEsz / 2];
 #pragma unroll
-    for (int q = 0; q < kEsz / 2; ++q)
-      reinterpret_cast<uint4 *>(plane + (wx * WP + wy) * 8)[q] =
-          inside ? reinterpret_cast<const uint4 *>(src + ((int64_t)y * Dz + x) * cin_pad)[q] : make_uint4(0, 0, 0, 0);
+    for (int u = 0; u < kU; ++u) {
+      const int v = tid + u * 256, wy = v / W, wx = v - wy * W;
+      const int y = y0 + wy, x = x0 + wx;
+      const bool inside = v < W * W && y >= 0 && y < Dz && x >= 0 && x < Dz;
+#pragma unroll
+      for (int q = 0; q < kEsz / 2; ++q)
+        raw[u][q] = inside ? reinterpret_cast<const uint4 *>(src + ((int64_t)y * Dz + x) * cin_pad)[q] : make_uint4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int v = tid + u * 256, wy = v / W, wx = v - wy * W;
+      if (v < W * W)
+#pragma unroll
+        for (int q = 0; q < kEsz / 2; ++q) reinterpret_cast<uint4 *>(plane + (wx * WP + wy) * 8)[q] = raw[u][q];
+    }
   }
   __syncthreads();
   // rows along x (window rows wy) on 8 W threads, a lane pair per (wy, two channels),
@@ -444,24 +477,10 @@ __global__ __launch_bounds__(256) void k_fft_fwd2d_t(const void *__restrict__ in
     const bool roww = tid < 8 * W;
     const int wy = q >> 2, c0 = (q & 3) * 2;
     float re[16], im[16];
+    // (threads past the last row read rows of the plane region that they do not use)
 #pragma unroll
-    for (int n = 0; n < 16; ++n) {
-      const int a = 16 * h + n;
-      const int w = a < TS + P ? a + P : (a >= 32 - P ? a - 32 + P : -1);
-      re[n] = 0.0f;
-      im[n] = 0.0f;
-      if (roww && w >= 0) {
-        if constexpr (F32) {
-          const float2 two = *reinterpret_cast<const float2 *>(plane + (w * WP + wy) * 8 + c0);
-          re[n] = two.x;
-          im[n] = two.y;
-        } else {
-          const uint32_t two = *reinterpret_cast<const uint32_t *>(plane + (w * WP + wy) * 8 + c0);
-          re[n] = __uint_as_float(two << 16);
-          im[n] = __uint_as_float(two & 0xffff0000u);
-        }
-      }
-    }
+    for (int n = 0; n < 16; ++n) re[n] = im[n] = 0.0f;
+    by_window<TS, P>(h, plane + wy * 8 + c0, WP * 8, [&](int n, const act_t *v) { two_channels(v, re[n], im[n]); });
     __syncthreads();  // the plane is in registers; its LDS becomes the row spectra
     if (roww) {
       fft32_lanes_dif<false>(re, im, h);
@@ -473,13 +492,11 @@ __global__ __launch_bounds__(256) void k_fft_fwd2d_t(const void *__restrict__ in
   const int kxp = q >> 3, c = q & 7;
   float re[16], im[16];
 #pragma unroll
-  for (int n = 0; n < 16; ++n) {
-    const int a = 16 * h + n;
-    const int w = a < TS + P ? a + P : (a >= 32 - P ? a - 32 + P : -1);
-    const float2 v = w >= 0 ? T[(kxp * WP + w) * 8 + c] : make_float2(0.0f, 0.0f);
-    re[n] = v.x;
-    im[n] = v.y;
-  }
+  for (int n = 0; n < 16; ++n) re[n] = im[n] = 0.0f;
+  by_window<TS, P>(h, T + kxp * WP * 8 + c, 8, [&](int n, const float2 *v) {
+    re[n] = v->x;
+    im[n] = v->y;
+  });
   fft32_lanes_dif<false>(re, im, h);
   __syncthreads();
   act_t *O = reinterpret_cast<act_t *>(T);  // [col][re | im][8]
@@ -651,12 +668,30 @@ __global__ __launch_bounds__(256) void k_fft_fwd2d(const void *__restrict__ in_v
   float2 *Zp = reinterpret_cast<float2 *>(dyn_lds + plane_lds_bytes(D, F32));
   const int tid = threadIdx.x, h = tid & 1, q = tid >> 1, DP = D + 1;
   const act_t *src = in + (((int64_t)p * D + z) * D * D) * cin_pad + chunk * 8;
-  for (int v = tid; v < D * D; v += 256) {
+  auto put = [&](int v, const uint4 (&raw)[kEsz / 2]) {
     const int y = v / D, x = v - y * D;
 #pragma unroll
-    for (int qq = 0; qq < kEsz / 2; ++qq)
-      reinterpret_cast<uint4 *>(plane + (x * DP + y) * 8)[qq] =
-          reinterpret_cast<const uint4 *>(src + (int64_t)v * cin_pad)[qq];
+    for (int qq = 0; qq < kEsz / 2; ++qq) reinterpret_cast<uint4 *>(plane + (x * DP + y) * 8)[qq] = raw[qq];
+  };
+  auto get = [&](int v, uint4 (&raw)[kEsz / 2]) {
+#pragma unroll
+    for (int qq = 0; qq < kEsz / 2; ++qq) raw[qq] = reinterpret_cast<const uint4 *>(src + (int64_t)v * cin_pad)[qq];
+  };
+  if constexpr (DT != 0) {
+    // a thread's loads in flight together
+    constexpr int kU = (DT * DT + 255) / 256;
+    uint4 raw[kU][kEsz / 2];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) get(min(tid + u * 256, DT * DT - 1), raw[u]);
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+      if (tid + u * 256 < DT * DT) put(tid + u * 256, raw[u]);
+  } else {
+    for (int v = tid; v < D * D; v += 256) {
+      uint4 raw[kEsz / 2];
+      get(v, raw);
+      put(v, raw);
+    }
   }
   __syncthreads();
   // rows along x, two channels per complex transform: lane h takes x = 16 h + n
@@ -664,24 +699,11 @@ __global__ __launch_bounds__(256) void k_fft_fwd2d(const void *__restrict__ in_v
     const bool roww = tid < 8 * D;
     const int y = q >> 2, c0 = (q & 3) * 2;
     float re[16], im[16];
+    // (threads past the last row read rows of the plane region that they do not use)
 #pragma unroll
-    for (int n = 0; n < 16; ++n) {
-      const int x = 16 * h + n;
-      if (roww && x < D) {
-        if constexpr (F32) {
-          const float2 two = *reinterpret_cast<const float2 *>(plane + (x * DP + y) * 8 + c0);
-          re[n] = two.x;
-          im[n] = two.y;
-        } else {
-          const uint32_t two = *reinterpret_cast<const uint32_t *>(plane + (x * DP + y) * 8 + c0);
-          re[n] = __uint_as_float(two << 16);
-          im[n] = __uint_as_float(two & 0xffff0000u);
-        }
-      } else {
-        re[n] = 0.0f;
-        im[n] = 0.0f;
-      }
-    }
+    for (int n = 0; n < 16; ++n) re[n] = im[n] = 0.0f;
+    const act_t *v = plane + (16 * h * DP + y) * 8 + c0;
+    by_half<DT>(h, D, [&](int n) { two_channels(v + n * DP * 8, re[n], im[n]); }, [](int) {});
     __syncthreads();  // the plane is in registers; its LDS becomes the row spectra
     if (roww) {
       fft32_lanes_dif<false>(re, im, h);
