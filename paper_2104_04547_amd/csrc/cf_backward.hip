@@ -19,6 +19,7 @@
 //     (32x32x2), see k_conv_wgrad and k_conv_dgrad.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "cf_internal.h"
 
@@ -365,15 +366,20 @@ __global__ __launch_bounds__(kT) void k_fold_wt(const float *__restrict__ W, con
 // A workgroup takes 32 MB output channels and 32 NB columns (tx, ci) of one (tz, ty);
 // its four waves take the output rows (oz, oy) in turn, each with all MB x NB blocks of
 // accumulators, and add up in order at the end.  Per row a wave stages its dY row and
-// the X row that (tz, ty) pairs with it in LDS of its own, in runs of up to kRun
+// the X row that (tz, ty) pairs with it in LDS of its own, in runs of
 // output voxels (so no barrier inside): with the X row packed at cin floats per voxel,
 // column q = tx cin + ci at output voxel ox is float S ox cin + q, the same for every
 // tap of the row.
 // What bounds it: the float32 matrix instruction (64 cycles; MB NB of them per
-// MB + NB LDS reads), with two waves per SIMD to hide the staging.  The six layers of the
-// full model, 8 poses at 48^3: 25.4 ms, 55 TFLOP/s (LDS-tiled FMAs with an im2col division
-// per element: 62.0 ms).
-constexpr int kRun = 24;
+// MB + NB LDS reads).  A run's loads wait in registers while the run before it is
+// multiplied: with the loads between the runs, two waves per SIMD left the matrix cores
+// idle for more than half of the time.  The two stride-2 layers of the full model, 8 poses
+// at 48^3: 2.1 + 2.0 ms -> 1.28 + 0.87 ms (72 and 89 TFLOP/s; 17 % of the first one's
+// columns are padding).
+// voxels of a run at most, and pieces of X per lane that wait in registers (16 bytes each,
+// or 4): what the registers hold beside 2 x 5 blocks
+constexpr int wgrad_run(bool vec) { return vec ? 16 : 24; }
+constexpr int wgrad_xregs(bool vec) { return vec ? 8 : 16; }
 // floats of LDS per wave at a run of `run` voxels: dY run, X run, and zeros for the
 // columns past the row's last (at most 4 blocks of 32 and 31 more)
 inline int wgrad_wave_floats(int run, int KS, int S, int cin) {
@@ -381,82 +387,133 @@ inline int wgrad_wave_floats(int run, int KS, int S, int cin) {
   return (f < 1024 ? 1024 : f + 3) / 4 * 4;
 }
 
-template <int MB, int NB>
+// VEC: cin, xstride and the X pointer allow 16-byte loads of X.  A run's values are
+// loaded into registers while the run before it is multiplied: six 16-byte pieces of dY
+// (three with MB = 1) and the first kXV of X per lane; whatever X has beyond those
+// (bw_conv_wgrad picks runs that have none where it can) is loaded when it is stored.
+template <int MB, int NB, bool VEC>
 __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2))) void k_conv_wgrad(
     const float *__restrict__ X, int D, int xstride, int cin, const float *__restrict__ dY, int Do, int ystride,
     int cout, int KS, int S, int ncg, int nsplit, int run, int wave_floats, float *__restrict__ part) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
+  typedef typename std::conditional<VEC, float4, float>::type xv_t;
+  constexpr int kXV = wgrad_xregs(VEC), kE = VEC ? 4 : 1;
+  constexpr int kYQ = 8 * MB, kYV = 64 / kYQ, kYU = wgrad_run(VEC) / kYV;  // dY: pieces a voxel, voxels a pass, passes
   const int P = (KS - 1) / 2;
   const int cg = blockIdx.x % ncg, tzy = blockIdx.x / ncg, tz = tzy / KS, ty = tzy % KS;
   const int c0 = blockIdx.y * 32 * MB, q0 = cg * 32 * NB;
   const int p = blockIdx.z / nsplit, split = blockIdx.z % nsplit;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, khalf = lane >> 5, lrow = lane & 31;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int khalf = lane >> 5, lrow = lane & 31;
   float *sA = lds + wave * wave_floats, *sB = sA + run * 64;
   const int xw = S * (run - 1) + KS;           // X positions of a run
+  const int cw = cin / kE, xtot = xw * cw;     // their pieces
   const float *xp = X + (int64_t)p * D * D * D * xstride;
   const float *yp = dY + (int64_t)p * Do * Do * Do * ystride + c0;
-  const int nco = min(32 * MB, cout - c0);
+  const int ca = (lane % kYQ) * 4, va = lane / kYQ, nca = c0 + ca < ystride ? cout - c0 - ca : 0;
+  const int xi0 = lane / cw, xc0 = lane % cw, xdi = 64 / cw, xdc = 64 % cw;
   f32x16b acc[MB][NB];
 #pragma unroll
   for (int m = 0; m < MB; ++m)
 #pragma unroll
     for (int n = 0; n < NB; ++n) acc[m][n] = f32x16b{};
   for (int e = lane; e < 160; e += 64) sB[xw * cin + e] = 0.0f;  // columns past the row's last
-  for (int r = split * 4 + wave; r < Do * Do; r += 4 * nsplit) {
-    const int oz = r / Do, oy = r % Do, z = S * oz + tz - P, y = S * oy + ty - P;
-    if (z < 0 || z >= D || y < 0 || y >= D) continue;
-    const float *xr = xp + ((int64_t)z * D + y) * D * xstride;
-    const float *yr = yp + (int64_t)r * Do * ystride;
-    for (int o0 = 0; o0 < Do; o0 += run) {
-      const int no = min(run, Do - o0);
-      // the wave's own LDS: its operations stay in order, only the compiler is held
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      // dY run: [voxel][64], odd voxels with their two 32-channel halves swapped, so that
-      // the two K halves of a fragment read fall on different banks
-      constexpr int CW = 32 * MB;              // channels staged
-      constexpr int VPL = 64 / CW;             // voxels per pass of the wave
-      const int ca = lane % CW;
-#pragma unroll 4
-      for (int v = lane / CW; v < run; v += VPL) {
-        const float a = v < no && ca < nco ? yr[(int64_t)(o0 + v) * ystride + ca] : 0.0f;
-        sA[v * 64 + (ca ^ ((v & 1) << 5))] = a;
+  // this wave's output rows, those whose X row lies in the grid
+  auto row_ok = [&](int r) {
+    const int z = S * (r / Do) + tz - P, y = S * (r % Do) + ty - P;
+    return z >= 0 && z < D && y >= 0 && y < D;
+  };
+  auto next_row = [&](int r) {
+    while (r < Do * Do && !row_ok(r)) r += 4 * nsplit;
+    return r;
+  };
+  float4 ya[kYU];
+  xv_t xa[kXV];
+  auto load = [&](int r, int o0) {
+    const int no = min(run, Do - o0), x0 = S * o0 - P, xe = min(D, x0 + S * (no - 1) + KS);
+    const float *yr = yp + ((int64_t)r * Do + o0) * ystride;
+    int v0 = va;
+    asm volatile("" : "+v"(v0));
+#pragma unroll
+    for (int u = 0; u < kYU; ++u) {
+      const int v = u * kYV + v0;
+      ya[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (v < no && nca > 0) ya[u] = *reinterpret_cast<const float4 *>(yr + (uint32_t)(v * ystride + ca));
+    }
+    const float *xr = xp + ((int64_t)(S * (r / Do) + tz - P) * D + S * (r % Do) + ty - P) * D * xstride;
+    int i = xi0, c = xc0;
+    asm volatile("" : "+v"(i), "+v"(c));  // positions are stepped anew for each run, not held
+#pragma unroll
+    for (int u = 0; u < kXV; ++u) {
+      const int x = x0 + i;
+      xa[u] = xv_t{};
+      if (u * 64 + lane < xtot && x >= 0 && x < xe)
+        xa[u] = *reinterpret_cast<const xv_t *>(xr + (uint32_t)(x * xstride + kE * c));
+      i += xdi;
+      c += xdc;
+      if (c >= cw) c -= cw, ++i;
+    }
+  };
+  auto store = [&](int r, int o0) {
+    // dY run: [voxel][64], odd voxels with their two 32-channel halves swapped, so that
+    // the two K halves of a fragment read fall on different banks
+#pragma unroll
+    for (int u = 0; u < kYU; ++u) {
+      const int v = u * kYV + va;
+      float4 t = ya[u];
+      if (nca < 4) {
+        if (nca < 1) t.x = 0.0f;
+        if (nca < 2) t.y = 0.0f;
+        if (nca < 3) t.z = 0.0f;
+        t.w = 0.0f;
       }
-      // X run: positions S o0 - P + i, cin floats each; zero outside the grid and past the
-      // last one an output voxel of the run reaches
-      const int x0 = S * o0 - P, xe = min(D, x0 + S * (no - 1) + KS);
-      if ((cin & 3) == 0 && (xstride & 3) == 0) {
-        const int c4 = cin >> 2;
-#pragma unroll 4
-        for (int e = lane; e < xw * c4; e += 64) {
-          const int i = e / c4, c = e - i * c4, x = x0 + i;
-          reinterpret_cast<float4 *>(sB)[e] = x >= 0 && x < xe
-                                                  ? *reinterpret_cast<const float4 *>(xr + (int64_t)x * xstride + 4 * c)
-                                                  : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-      } else {
-#pragma unroll 4
-        for (int e = lane; e < xw * cin; e += 64) {
-          const int i = e / cin, c = e - i * cin, x = x0 + i;
-          sB[e] = x >= 0 && x < xe ? xr[(int64_t)x * xstride + c] : 0.0f;
-        }
+      if (v < run) *reinterpret_cast<float4 *>(sA + v * 64 + (ca ^ ((v & 1) << 5))) = t;
+    }
+    // X run: positions S o0 - P + i, cin floats each; zero outside the grid and past the
+    // last one an output voxel of the run reaches
+    xv_t *xb = reinterpret_cast<xv_t *>(sB);
+#pragma unroll
+    for (int u = 0; u < kXV; ++u)
+      if (u * 64 + lane < xtot) xb[u * 64 + lane] = xa[u];
+    if (xtot > kXV * 64) {
+      const int no = min(run, Do - o0), x0 = S * o0 - P, xe = min(D, x0 + S * (no - 1) + KS);
+      const float *xr = xp + ((int64_t)(S * (r / Do) + tz - P) * D + S * (r % Do) + ty - P) * D * xstride;
+      for (int e = kXV * 64 + lane; e < xtot; e += 64) {
+        const int i = e / cw, c = e - i * cw, x = x0 + i;
+        xv_t t = {};
+        if (x >= 0 && x < xe) t = *reinterpret_cast<const xv_t *>(xr + (int64_t)x * xstride + kE * c);
+        xb[e] = t;
       }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      const float *bp = sB + khalf * S * cin + q0 + lrow;
-      for (int k = 0; k < run; k += 2) {
-        const int v = k + khalf;
-        float a[MB], b[NB];
+    }
+  };
+  int r = next_row(split * 4 + wave), o0 = 0;
+  if (r < Do * Do) load(r, o0);
+  while (r < Do * Do) {
+    // the wave's own LDS: its operations stay in order, only the compiler is held
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    store(r, o0);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    o0 += run;
+    if (o0 >= Do) {
+      o0 = 0;
+      r = next_row(r + 4 * nsplit);
+    }
+    if (r < Do * Do) load(r, o0);
+    const float *bp = sB + khalf * S * cin + q0 + lrow;
+    for (int k = 0; k < run; k += 2) {
+      const int v = k + khalf;
+      float a[MB], b[NB];
 #pragma unroll
-        for (int m = 0; m < MB; ++m) a[m] = sA[v * 64 + ((32 * m + lrow) ^ (khalf << 5))];
+      for (int m = 0; m < MB; ++m) a[m] = sA[v * 64 + ((32 * m + lrow) ^ (khalf << 5))];
 #pragma unroll
-        for (int n = 0; n < NB; ++n) b[n] = bp[k * S * cin + 32 * n];
+      for (int n = 0; n < NB; ++n) b[n] = bp[k * S * cin + 32 * n];
 #pragma unroll
-        for (int m = 0; m < MB; ++m)
+      for (int m = 0; m < MB; ++m)
 #pragma unroll
-          for (int n = 0; n < NB; ++n)
-            acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[m], b[n], acc[m][n], 0, 0, 0);
-      }
+        for (int n = 0; n < NB; ++n)
+          acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[m], b[n], acc[m][n], 0, 0, 0);
     }
   }
   // the waves' sums in order, a block at a time
@@ -832,23 +889,32 @@ int bw_conv_wgrad_split(int cin, int cout, int KS, int Do, int np, int nparts) {
 hipError_t bw_conv_wgrad(const float *X, int D, int xstride, int cin, const float *dY, int Do, int ystride, int cout,
                          int KS, int S, int np, int nsplit, float *part, hipStream_t s) {
   const int nb = (KS * cin + 31) / 32, ncg = (nb + 4) / 5, nbw = (nb + ncg - 1) / ncg;
-  // voxels per run: even, at most kRun, two workgroups per CU (one needs a run of at most
-  // two voxels and 256 channels to fit)
-  int run = std::min(kRun, (Do + 1) / 2 * 2);
-  while (run > 2 && wgrad_wave_floats(run, KS, S, cin) * 16 > 81920) run -= 2;
+  // voxels per run: even, two workgroups per CU (one needs a run of at most two voxels and
+  // 256 channels to fit), X in its registers, and a row's runs alike
+  const bool vec = (cin & 3) == 0 && (xstride & 3) == 0 && ((uintptr_t)X & 15) == 0;
+  int run = std::min(wgrad_run(vec), (Do + 1) / 2 * 2);
+  while (run > 2 && (wgrad_wave_floats(run, KS, S, cin) * 16 > 81920 ||
+                     (S * (run - 1) + KS) * (vec ? cin / 4 : cin) > 64 * wgrad_xregs(vec)))
+    run -= 2;
+  const int nrun = (Do + run - 1) / run;
+  run = ((Do + nrun - 1) / nrun + 1) / 2 * 2;
   const int wf = wgrad_wave_floats(run, KS, S, cin);
   const size_t lds = sizeof(float) * 4 * wf;
   if (lds > 163840) return hipErrorInvalidValue;
   const int mb = cout <= 32 ? 1 : 2;
   const dim3 grid(KS * KS * ncg, (cout + 32 * mb - 1) / (32 * mb), np * nsplit);
-#define CF_WG(MB, NB)                                                                                              \
+#define CF_WG(MB, NB) \
+  do {                \
+    if (vec) CF_WGV(MB, NB, true); else CF_WGV(MB, NB, false); \
+  } while (0)
+#define CF_WGV(MB, NB, V)                                                                                          \
   do {                                                                                                             \
     if (lds > 65536) {                                                                                             \
-      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_conv_wgrad<MB, NB>),              \
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_conv_wgrad<MB, NB, V>),              \
                                                hipFuncAttributeMaxDynamicSharedMemorySize, 163840);                \
       if (e != hipSuccess) return e;                                                                               \
     }                                                                                                              \
-    hipLaunchKernelGGL((k_conv_wgrad<MB, NB>), grid, dim3(kT), lds, s, X, D, xstride, cin, dY, Do, ystride, cout,  \
+    hipLaunchKernelGGL((k_conv_wgrad<MB, NB, V>), grid, dim3(kT), lds, s, X, D, xstride, cin, dY, Do, ystride, cout,  \
                        KS, S, ncg, nsplit, run, wf, part);                                                              \
   } while (0)
   if (mb == 1) {
@@ -857,6 +923,7 @@ hipError_t bw_conv_wgrad(const float *X, int D, int xstride, int cin, const floa
     if (nbw <= 3) CF_WG(2, 3); else CF_WG(2, 5);
   }
 #undef CF_WG
+#undef CF_WGV
   return hipGetLastError();
 }
 hipError_t bw_conv_dgrad(const float *dY, int Do, int ystride, int cout, const float *WT, int cin, int KS, int S, int D,
