@@ -68,10 +68,16 @@ __global__ __launch_bounds__(kT) void k_rowmat(const float *__restrict__ X, int 
   f32x16b acc;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = bj;
-#pragma unroll 2
-  for (int k = 0; k < K; k += 8) {
+  // eight of K at k; WHOLE: they exist and lie aligned, so the loads of several such steps
+  // are in flight together (a test per load waits for each)
+  auto step = [&](int k, auto whole) {
+    constexpr bool WHOLE = decltype(whole)::value;
+    auto take = [&](const float *p, int left, bool al) {
+      if constexpr (WHOLE) return *reinterpret_cast<const float4 *>(p);
+      return take4(p, left, al);
+    };
     float a[4], v[4];  // k + 2 s + khalf
-    const float4 a0 = take4(x + k, K - k, xa), a1 = take4(x + k + 4, K - k - 4, xa);
+    const float4 a0 = take(x + k, K - k, xa), a1 = take(x + k + 4, K - k - 4, xa);
     a[0] = khalf ? a0.y : a0.x;
     a[1] = khalf ? a0.w : a0.z;
     a[2] = khalf ? a1.y : a1.x;
@@ -80,10 +86,10 @@ __global__ __launch_bounds__(kT) void k_rowmat(const float *__restrict__ X, int 
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int kk = k + 2 * q + khalf;
-        v[q] = kk < K ? w[(int64_t)kk * ldw] : 0.0f;
+        v[q] = WHOLE || kk < K ? w[(int64_t)kk * ldw] : 0.0f;
       }
     } else {
-      const float4 w0 = take4(w + k, K - k, wa), w1 = take4(w + k + 4, K - k - 4, wa);
+      const float4 w0 = take(w + k, K - k, wa), w1 = take(w + k + 4, K - k - 4, wa);
       v[0] = khalf ? w0.y : w0.x;
       v[1] = khalf ? w0.w : w0.z;
       v[2] = khalf ? w1.y : w1.x;
@@ -91,7 +97,13 @@ __global__ __launch_bounds__(kT) void k_rowmat(const float *__restrict__ X, int 
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], v[q], acc, 0, 0, 0);
+  };
+  int k = 0;
+  if (xa && (TRANS || wa)) {
+#pragma unroll 8
+    for (; k + 8 <= K; k += 8) step(k, std::true_type{});
   }
+  for (; k < K; k += 8) step(k, std::false_type{});
   if (j0 + lrow >= J) return;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
@@ -180,11 +192,22 @@ __global__ __launch_bounds__(kT) void k_readout(const float *__restrict__ Gpre, 
   const int base = atom_off[p0];
   const int a0 = atom_off[p0 + p], a1 = atom_off[p0 + p + 1];
   float acc = 0.0f;
-  for (int a = a0; a < a1; ++a)
-    if (is_lig[a]) {
-      const int64_t i = (int64_t)(a - base) * H + j;
-      acc = fmaf(sigm(Gpre[i]), V[i], acc);
+  // eight atoms' loads in flight, added in order
+  for (int a = a0; a < a1; a += 8) {
+    uint8_t lig[8];
+    float g[8], v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int au = min(a + u, a1 - 1);
+      const int64_t i = (int64_t)(au - base) * H + j;
+      lig[u] = is_lig[au];
+      g[u] = Gpre[i];
+      v[u] = V[i];
     }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (a + u < a1 && lig[u]) acc = fmaf(sigm(g[u]), v[u], acc);
+  }
   S[e] = acc;
 }
 
@@ -241,11 +264,19 @@ __global__ __launch_bounds__(kT) void k_outer_mfma(const float *__restrict__ U, 
   const int a = min(a0 + lrow, A - 1), b = min(b0 + lrow, B - 1);
   const int i0 = s * kRowsPerChunk, i1 = min(n, i0 + kRowsPerChunk);
   f32x16b acc = {};
+  if (i1 - i0 == kRowsPerChunk) {
+    // a whole chunk: no tests, so that many rows' loads are in flight
+    const float *u = U + (int64_t)(i0 + khalf) * ldu + a, *v = V + (int64_t)(i0 + khalf) * ldv + b;
+#pragma unroll 32
+    for (int i = 0; i < kRowsPerChunk; i += 2)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(u[(int64_t)i * ldu], v[(int64_t)i * ldv], acc, 0, 0, 0);
+  } else {
 #pragma unroll 8
-  for (int i = i0; i < i1; i += 2) {
-    const int r = i + khalf;
-    const float u = r < i1 ? U[(int64_t)r * ldu + a] : 0.0f, v = r < i1 ? V[(int64_t)r * ldv + b] : 0.0f;
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(u, v, acc, 0, 0, 0);
+    for (int i = i0; i < i1; i += 2) {
+      const int r = i + khalf;
+      const float u = r < i1 ? U[(int64_t)r * ldu + a] : 0.0f, v = r < i1 ? V[(int64_t)r * ldv + b] : 0.0f;
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(u, v, acc, 0, 0, 0);
+    }
   }
   if (b0 + lrow >= B) return;
 #pragma unroll
@@ -641,19 +672,21 @@ __global__ __launch_bounds__(kT) void k_conv_dgrad(const float *__restrict__ dY,
 //   dW = a dW', db = a db', dbeta = db', dmean = -a db',
 //   dgamma = g_a / sqrt(var + eps), dvar = -g_a a / (2 (var + eps)),
 // with g_a = sum dW' W + db' (b - mu).  dWf: [co][t][ci]; blob W: [co][ci][t].
-__global__ __launch_bounds__(kT) void k_fold_grad(const float *__restrict__ dWf, const float *__restrict__ dbf,
+constexpr int kFoldT = 1024;  // a workgroup per output channel: loads in flight count (256 threads: 48 us)
+__global__ __launch_bounds__(kFoldT) void k_fold_grad(const float *__restrict__ dWf, const float *__restrict__ dbf,
                                                   const float *__restrict__ W, const float *__restrict__ b,
                                                   const float *__restrict__ gamma, const float *__restrict__ mean,
                                                   const float *__restrict__ var, int cin, int taps,
                                                   float *__restrict__ gW, float *__restrict__ gb,
                                                   float *__restrict__ ggamma, float *__restrict__ gbeta,
                                                   float *__restrict__ gmean, float *__restrict__ gvar) {
-  __shared__ double red[kT];
+  __shared__ double red[kFoldT];
   const int co = blockIdx.x, tid = threadIdx.x;
   const double a = gamma ? (double)gamma[co] / sqrt((double)var[co] + 1e-5) : 1.0;
   const int64_t n = (int64_t)cin * taps;
   double ga = 0.0;
-  for (int64_t e = tid; e < n; e += kT) {
+#pragma unroll 4
+  for (int64_t e = tid; e < n; e += kFoldT) {
     const int ci = (int)(e / taps), t = (int)(e % taps);
     const float d = dWf[((int64_t)co * taps + t) * cin + ci];
     const int64_t wi = (int64_t)co * n + e;
@@ -662,7 +695,7 @@ __global__ __launch_bounds__(kT) void k_fold_grad(const float *__restrict__ dWf,
   }
   red[tid] = ga;
   __syncthreads();
-  for (int s = kT / 2; s > 0; s >>= 1) {
+  for (int s = kFoldT / 2; s > 0; s >>= 1) {
     if (tid < s) red[tid] += red[tid + s];
     __syncthreads();
   }
@@ -937,7 +970,7 @@ hipError_t bw_conv_dgrad(const float *dY, int Do, int ystride, int cout, const f
 hipError_t bw_fold_grad(const float *dWf, const float *dbf, const float *W, const float *b, const float *gamma,
                         const float *mean, const float *var, int cout, int cin, int taps, float *gW, float *gb,
                         float *ggamma, float *gbeta, float *gmean, float *gvar, hipStream_t s) {
-  hipLaunchKernelGGL(k_fold_grad, dim3(cout), dim3(kT), 0, s, dWf, dbf, W, b, gamma, mean, var, cin, taps, gW, gb,
+  hipLaunchKernelGGL(k_fold_grad, dim3(cout), dim3(kFoldT), 0, s, dWf, dbf, W, b, gamma, mean, var, cin, taps, gW, gb,
                      ggamma, gbeta, gmean, gvar);
   return hipGetLastError();
 }
