@@ -59,8 +59,8 @@ __device__ inline void sg_embed(const SgWeights &W, const float *__restrict__ fe
 // states into Hc; rows past the pose are zero.  Each thread owns four consecutive
 // features of a row (one 16-byte load per neighbour row segment) and H / 4 threads
 // share a row.  The block's CSR rows are consecutive, so their columns form one
-// contiguous range: it is staged in LDS (idx, up to icap entries; columns beyond
-// that are read from memory) with coalesced loads, and every thread then walks NU
+// contiguous range: it is staged in LDS (idx, up to icap entries, as row numbers in the
+// pose; a thread with rows beyond that reads columns from memory) with coalesced loads, and every thread then walks NU
 // of the block's rows at once (nblk <= NU * kThreads / (H / 4)), kSlots neighbours
 // per row per step, so that up to 4 NU row loads are in flight with no index load
 // in front of them.  Every feature's sum runs over the row's neighbours in CSR order.
@@ -102,7 +102,11 @@ __device__ inline void sg_aggregate(const float *__restrict__ cur, const int32_t
 #pragma unroll
     for (int u = 0; u < kStage; ++u) {
       const int64_t e = e0 + u * kThreads + threadIdx.x;
-      if (e < nst) idx[e] = cv[u];
+      if (e < nst) {
+        // the neighbour's row in the pose, -1 for one outside of it
+        const int64_t j = (csr_global ? (int64_t)cv[u] - base : (int64_t)cv[u]) - lb;
+        idx[e] = j >= 0 && j < n ? (int32_t)j : -1;
+      }
     }
   }
   bool anybad = false;
@@ -120,39 +124,84 @@ __device__ inline void sg_aggregate(const float *__restrict__ cur, const int32_t
   float4 s[NU];
 #pragma unroll
   for (int u = 0; u < NU; ++u) s[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-  // whole steps with a branch-free body: slots past a row's end and columns outside
-  // the pose read the row's own state (the pose's first row for rows past the
-  // block) and add nothing; a bad column is reported once after the loop
-  for (int64_t k = 0; k < len; k += kSlots) {
-    float4 v[NU][kSlots];
-    bool use[NU][kSlots];
+  // Whole steps with a branch-free body: slots past a row's end and neighbours outside
+  // the pose read the row's own state (the pose's first row for rows past the block) and
+  // add nothing; a bad neighbour is reported once after the loop.  Where the rows lie
+  // within the staged range, indices and offsets are 32 bits wide: a step's index work in
+  // 64 bits was two fifths of the round's vector instructions (200 ragged poses at width
+  // 64: 112 us a round, now 91).
+  bool staged = true;
+#pragma unroll
+  for (int u = 0; u < NU; ++u) staged &= e0[u] >= e1[u] || (e0[u] >= E0 && e1[u] <= E0 + nst);
+  if (staged) {
+    const float *rows = cur + lb * H;
+    int q0[NU], cnt[NU], self[NU];
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
       const int a = tr + RPI * u;
-      const int64_t self = lb + (a < nrow ? blk + a : 0);
-#pragma unroll
-      for (int w = 0; w < kSlots; ++w) {
-        const int64_t q = e0[u] + k + w;
-        const bool live = q < e1[u];
-        const int64_t qs = q - E0;
-        int64_t c = 0;
-        if (live) c = (qs >= 0 && qs < nst) ? (int64_t)idx[qs] : (int64_t)colp[q];
-        const int64_t j = csr_global ? c - base : c;
-        const bool bad = j < lb || j >= lb + n;
-        anybad |= live && bad;
-        use[u][w] = live && !bad;
-        v[u][w] = *reinterpret_cast<const float4 *>(cur + (use[u][w] ? j : self) * H + c4);
-      }
+      cnt[u] = e1[u] > e0[u] ? (int)(e1[u] - e0[u]) : 0;
+      q0[u] = cnt[u] ? (int)(e0[u] - E0) : 0;
+      self[u] = a < nrow ? blk + a : 0;
     }
+    const int last = nst > 0 ? (int)nst - 1 : 0;
+    for (int k = 0; k < (int)len; k += kSlots) {
+      float4 v[NU][kSlots];
+      bool use[NU][kSlots];
+      int j[NU][kSlots];
 #pragma unroll
-    for (int u = 0; u < NU; ++u)
+      for (int u = 0; u < NU; ++u)
 #pragma unroll
-      for (int w = 0; w < kSlots; ++w) {
-        s[u].x += use[u][w] ? v[u][w].x : 0.0f;
-        s[u].y += use[u][w] ? v[u][w].y : 0.0f;
-        s[u].z += use[u][w] ? v[u][w].z : 0.0f;
-        s[u].w += use[u][w] ? v[u][w].w : 0.0f;
+        for (int w = 0; w < kSlots; ++w) j[u][w] = idx[min(q0[u] + k + w, last)];
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int w = 0; w < kSlots; ++w) {
+          const bool live = k + w < cnt[u];
+          use[u][w] = live && j[u][w] >= 0;
+          anybad |= live && j[u][w] < 0;
+          v[u][w] = *reinterpret_cast<const float4 *>(rows + (uint32_t)((use[u][w] ? j[u][w] : self[u]) * H + c4));
+        }
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int w = 0; w < kSlots; ++w) {
+          s[u].x += use[u][w] ? v[u][w].x : 0.0f;
+          s[u].y += use[u][w] ? v[u][w].y : 0.0f;
+          s[u].z += use[u][w] ? v[u][w].z : 0.0f;
+          s[u].w += use[u][w] ? v[u][w].w : 0.0f;
+        }
+    }
+  } else {
+    for (int64_t k = 0; k < len; k += kSlots) {
+      float4 v[NU][kSlots];
+      bool use[NU][kSlots];
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const int a = tr + RPI * u;
+        const int64_t self = lb + (a < nrow ? blk + a : 0);
+#pragma unroll
+        for (int w = 0; w < kSlots; ++w) {
+          const int64_t q = e0[u] + k + w;
+          const bool live = q < e1[u];
+          int64_t c = 0;
+          if (live) c = colp[q];
+          const int64_t j = csr_global ? c - base : c;
+          const bool bad = j < lb || j >= lb + n;
+          anybad |= live && bad;
+          use[u][w] = live && !bad;
+          v[u][w] = *reinterpret_cast<const float4 *>(cur + (use[u][w] ? j : self) * H + c4);
+        }
       }
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int w = 0; w < kSlots; ++w) {
+          s[u].x += use[u][w] ? v[u][w].x : 0.0f;
+          s[u].y += use[u][w] ? v[u][w].y : 0.0f;
+          s[u].z += use[u][w] ? v[u][w].z : 0.0f;
+          s[u].w += use[u][w] ? v[u][w].w : 0.0f;
+        }
+    }
   }
   if (anybad) dev_fail(status, kDevBadGraph);
 #pragma unroll
