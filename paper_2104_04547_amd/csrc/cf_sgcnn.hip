@@ -61,10 +61,10 @@ __device__ inline void sg_embed(const SgWeights &W, const float *__restrict__ fe
 // share a row.  The block's CSR rows are consecutive, so their columns form one
 // contiguous range: it is staged in LDS (idx, up to icap entries, as row numbers in the
 // pose; a thread with rows beyond that reads columns from memory) with coalesced loads, and every thread then walks NU
-// of the block's rows at once (nblk <= NU * kThreads / (H / 4)), kSlots neighbours
+// of the block's rows at once (OVER: idx lies where Hc goes; nblk <= NU * kThreads / (H / 4)), kSlots neighbours
 // per row per step, so that up to 4 NU row loads are in flight with no index load
 // in front of them.  Every feature's sum runs over the row's neighbours in CSR order.
-template <int H, int NU>
+template <int H, int NU, bool OVER = false>
 __device__ inline void sg_aggregate(const float *__restrict__ cur, const int32_t *__restrict__ rowp,
                                     const int32_t *__restrict__ colp, int64_t cap, int csr_global, int a0, int base,
                                     int64_t lb, int n, int blk, int nblk, int ld, float *A, float *Hc, int32_t *idx,
@@ -204,6 +204,7 @@ __device__ inline void sg_aggregate(const float *__restrict__ cur, const int32_t
     }
   }
   if (anybad) dev_fail(status, kDevBadGraph);
+  if constexpr (OVER) __syncthreads();  // the staged rows are read, Hc lies over them
 #pragma unroll
   for (int u = 0; u < NU; ++u) {
     const int a = tr + RPI * u;
@@ -413,9 +414,22 @@ struct SgTile {
   static constexpr int FB = H / 32;     // 32-feature blocks
   static constexpr int MBK = 4 / FB;    // 32-atom blocks per workgroup block
   static constexpr int BLK = 32 * MBK;  // atoms per block
-  static constexpr int FLOATS = 3 * BLK * LD;  // A | M | Hc
   static_assert(H % 32 == 0 && H <= 128, "matrix-core widths are 32, 64 or 128");
 };
+
+// LDS of a round: A | M (first the staged rows) | Hc, or in two regions (A, then M | the
+// staged rows, then Hc) for two more barriers.  Two pay at width 32 in the split form,
+// where they let three workgroups run on a CU in place of two (96 poses of the paper's
+// model, covalent stage: 66 -> 58 us a round); at width 64 three run either way and the
+// barriers cost 9 %.
+template <int H, bool F32>
+constexpr bool sg_two_regions() {
+  return H == 32 && !F32;
+}
+template <int H, bool F32>
+constexpr int sg_lds_floats() {
+  return (sg_two_regions<H, F32>() ? 2 : 3) * SgTile<H>::BLK * SgTile<H>::LD;
+}
 
 // acc += A[row][0..K) W^T for this lane's output column `col` of N, W given as
 // split-bfloat16 MFMA B operands ([K/16][N][16], hi and lo) -- three products per
@@ -455,7 +469,8 @@ __device__ void sg_block(const SgWeights &W, int stage, int r, const int32_t *__
   using T = SgTile<H>;
   constexpr int LD = T::LD, BLK = T::BLK;
   static_assert(BLK % (4 * kThreads / H) == 0, "whole rows per thread in the neighbour sums");
-  float *A = lds, *M = lds + BLK * LD, *Hc = lds + 2 * BLK * LD;
+  constexpr bool TWO = sg_two_regions<H, F32>();
+  float *A = lds, *M = TWO ? lds : lds + BLK * LD, *Hc = lds + (TWO ? 1 : 2) * BLK * LD;
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
   const int mb = wave / T::FB, fb = wave % T::FB;  // this wave's 32-atom x 32-feature tile
@@ -464,13 +479,14 @@ __device__ void sg_block(const SgWeights &W, int stage, int r, const int32_t *__
   const float *bih = W.b_ih[stage], *bhh = W.b_hh[stage];
   const float bir = bih[ocol], biz = bih[H + ocol], bin = bih[2 * H + ocol];
   const float bhr = bhh[ocol], bhz = bhh[H + ocol], bhn = bhh[2 * H + ocol];
-    sg_aggregate<H, BLK / (4 * kThreads / H)>(cur, rowp, colp, cap, csr_global, a0, base, lb, n, blk, BLK, LD, A, Hc,
-                  reinterpret_cast<int32_t *>(M), BLK * LD, status);
+    sg_aggregate<H, BLK / (4 * kThreads / H), TWO>(cur, rowp, colp, cap, csr_global, a0, base, lb, n, blk, BLK, LD, A, Hc,
+                  reinterpret_cast<int32_t *>(TWO ? Hc : M), BLK * LD, status);
     __syncthreads();
     // messages: M[atoms, ocol] = sum_k A[atoms, k] W_t[ocol, k]
     {
       f32x16v acc = {};
       acc = mm_row<H, F32>(&A[(mb * 32 + lrow) * LD], W.msg_hi[r], W.msg_lo[r], W.msgT[r], H, ocol, khalf, acc);
+      if constexpr (TWO) __syncthreads();  // A is read, M takes its place
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
         const int row = mb * 32 + 8 * (j >> 2) + 4 * khalf + (j & 3);
@@ -752,7 +768,7 @@ struct SgCall {
 template <int H, bool F32, bool SEP>
 hipError_t launch_rounds(const SgWeights &W, const SgCall &c, int stage, int r0, int K, float *&cur, float *&nxt,
                          hipStream_t s) {
-  const size_t lds = sizeof(float) * SgTile<H>::FLOATS;
+  const size_t lds = sizeof(float) * sg_lds_floats<H, F32>();
   static bool attr = false;
   if (!attr) {
     set_lds_attr(&k_sg_round<H, F32, SEP>, lds);
