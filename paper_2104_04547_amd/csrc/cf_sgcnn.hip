@@ -38,7 +38,15 @@ namespace {
 
 constexpr int kThreads = 256;
 
-__device__ inline float sigm(float x) { return 1.0f / (1.0f + expf(-x)); }
+// 1 / d for d >= 1: the hardware's reciprocal and one Newton step, which is the correctly
+// rounded quotient for every float in [1, 2^126) (all of them compared), in four
+// instructions instead of a division's eleven.  Beyond, where the quotient is subnormal,
+// it is 0.
+__device__ inline float recip_ge1(float d) {
+  const float r = __builtin_amdgcn_rcpf(d);
+  return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r), d, 1.0f);
+}
+__device__ inline float sigm(float x) { return recip_ge1(1.0f + expf(-x)); }
 
 // ---- shared pieces ------------------------------------------------------------
 
