@@ -13,8 +13,8 @@
 // launch, and the workgroups of a pose are neighbours on one XCD, under one L2.  (One
 // workgroup per pose walking its blocks round by round took 1.32 ms for one
 // 690-atom pose, 2.9 ms for 200 poses of 200-1500 atoms and 4.8 ms for 33 poses of the
-// staged plain form: its chain of dependent phases was the whole time.  Now 0.24, 0.73
-// and 0.64 ms.)  The neighbour sums are segmented CSR reductions
+// staged plain form: its chain of dependent phases was the whole time.  Now 0.16, 0.56
+// and 0.52 ms.)  The neighbour sums are segmented CSR reductions
 // (consecutive lanes = consecutive features, so a neighbour row is one coalesced
 // read) staged in LDS, then the message and GRU products run on the block.
 //   * precision form (H = 32 or 64): the products run on the matrix cores as
