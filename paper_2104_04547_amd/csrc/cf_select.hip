@@ -10,17 +10,18 @@
 // cf_top_k: exact selection on 64-bit keys (order-preserving 32-bit image of
 // the value, then the complemented index, so every key is distinct and the
 // ranking is "value descending, index ascending").
-//   * up to 65,536 values: one workgroup with every value in registers.  The k-th largest
+//   * up to 65,536 values: one workgroup, up to 16,384 of them in registers.  The k-th largest
 //     of its 1024 threads' maxima bounds the k-th largest value from below; the few values
-//     at or above it are sorted.  Where too many are (large k, or values in an order that
+//     at or above it are ranked.  Where too many are (large k, or values in an order that
 //     defeats the bound), a binary search over the value and then the index finds the
 //     k-th key exactly.
 //   * more: radix select, 8 passes of an 8-bit digit histogram (the last workgroup of a pass
 //     picks the digit; passes after the key is certain return at once), one pass collects
 //     the keys at or above the k-th, and a single workgroup sorts those k keys.
 // What bounds it: launches, and latency on one CU.  For 50,000 values 19 launches took 75 us
-// (102 us with the maxima of 50,000 segments of 10^6 scores before them), one takes 26
-// (30).  Results are deterministic.
+// (102 us with the maxima of 50,000 segments of 10^6 scores before them), one takes 23
+// (27), of which reading the values twice on one CU is about ten.  Results are
+// deterministic.
 #include <algorithm>
 #include <cfloat>
 #include <climits>
@@ -112,9 +113,14 @@ __device__ inline void sort_keys(uint64_t *s, int m, int nth) {
 // ---- up to kSmallN values: one workgroup ----
 
 constexpr int kSmallT = 1024, kSmallN = 64 * kSmallT, kSmallCap = 8192;
+// keys that are ranked by counting instead of sorted: a wave reads all of them, so the
+// count grows with the square; a sort of 256 is 36 steps with a barrier each
+constexpr int kSmallRank = 256;
 
-// E values per thread, n <= E * 1024, 1 <= k <= min(n, 1024)
-template <int E>
+// 1 <= k <= min(n, 1024).  HOLD: n <= E * 1024 and a thread keeps its E values; else it
+// reads them again for each pass, E at a time (64 values do not fit beside their range
+// tests: spilled and unrolled they took 26 us for 50,000 values).
+template <int E, bool HOLD>
 __global__ __launch_bounds__(kSmallT) void k_topk_small(const float *__restrict__ v, int n, int k,
                                                        int32_t *__restrict__ idx_out, float *__restrict__ val_out) {
   __shared__ uint64_t cand[kSmallCap];
@@ -122,17 +128,32 @@ __global__ __launch_bounds__(kSmallT) void k_topk_small(const float *__restrict_
   __shared__ int cnt, total[2];
   const int tid = threadIdx.x, lane = tid & 63;
   uint32_t key[E];  // images of the values e * 1024 + tid; 0 past the end (as a NaN's, but never counted)
-  uint32_t mx = 0;
   // buffer loads: one offset register for all of them (past the end they return zero)
   const __amdgpu_buffer_rsrc_t rs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(v), (short)0, n * 4, 0x00020000);
+  auto load = [&](int base) {
 #pragma unroll
-  for (int e = 0; e < E; ++e) key[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, tid * 4, e * kSmallT * 4, 0);
+    for (int e = 0; e < E; ++e)
+      key[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, tid * 4, (base + e * kSmallT) * 4, 0);
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
-    key[e] = e * kSmallT + tid < n ? (uint32_t)(topk_key(__uint_as_float(key[e]), 0) >> 32) : 0u;
-    mx = key[e] > mx ? key[e] : mx;
-  }
+    for (int e = 0; e < E; ++e)
+      key[e] = base + e * kSmallT + tid < n ? (uint32_t)(topk_key(__uint_as_float(key[e]), 0) >> 32) : 0u;
+  };
+  if constexpr (HOLD) load(0);
+  // f(image, index) of this thread's values
+  auto each = [&](auto f) {
+    const int batches = HOLD ? 1 : (n + E * kSmallT - 1) / (E * kSmallT);
+    for (int q = 0; q < batches; ++q) {
+      if constexpr (!HOLD) load(q * E * kSmallT);
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int i = (q * E + e) * kSmallT + tid;
+        if (i < n) f(key[e], i);
+      }
+    }
+  };
+  uint32_t mx = 0;
+  each([&](uint32_t y, int) { mx = y > mx ? y : mx; });
   uint32_t *maxima = reinterpret_cast<uint32_t *>(cand);
   maxima[tid] = mx;
   if (tid == 0) cnt = 0;
@@ -148,20 +169,20 @@ __global__ __launch_bounds__(kSmallT) void k_topk_small(const float *__restrict_
 #pragma unroll
       for (int u = 0; u < kSmallT / 64; ++u) have += __popcll(__ballot(q[u] >= c));
       if (have >= k) t = c;
+      if (have == k) break;  // the lower bits only raise the bound
     }
     if (lane == 0) thr = t;
   }
   __syncthreads();
   const uint32_t lo = thr;
   // keys at or above the bound (each key's slot is arbitrary: they are sorted)
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int i = e * kSmallT + tid;
-    if (i < n && key[e] >= lo) {
-      const int slot = atomicAdd(&cnt, 1);
-      if (slot < kSmallCap) cand[slot] = ((uint64_t)key[e] << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i);
-    }
-  }
+  auto take = [&](uint32_t y, int i) {
+    const int slot = atomicAdd(&cnt, 1);
+    if (slot < kSmallCap) cand[slot] = ((uint64_t)y << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i);
+  };
+  each([&](uint32_t y, int i) {
+    if (y >= lo) take(y, i);
+  });
   __syncthreads();
   int m = cnt;
   if (m > kSmallCap) {
@@ -169,11 +190,7 @@ __global__ __launch_bounds__(kSmallT) void k_topk_small(const float *__restrict_
     // bound x such that k keys are above t or at t with an index below x
     auto count = [&](auto pred, int slot) {
       int c = 0;
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const int i = e * kSmallT + tid;
-        c += i < n && pred(key[e], i) ? 1 : 0;
-      }
+      each([&](uint32_t y, int i) { c += pred(y, i) ? 1 : 0; });
       for (int o = 32; o >= 1; o >>= 1) c += __shfl_xor(c, o, 64);
       if (lane == 0 && c) atomicAdd(&total[slot], c);
     };
@@ -199,16 +216,26 @@ __global__ __launch_bounds__(kSmallT) void k_topk_small(const float *__restrict_
     __syncthreads();
     if (tid == 0) cnt = 0;
     __syncthreads();
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int i = e * kSmallT + tid;
-      if (i < n && (key[e] > t || (key[e] == t && (uint32_t)i <= below))) {
-        const int slot = atomicAdd(&cnt, 1);
-        if (slot < kSmallCap) cand[slot] = ((uint64_t)key[e] << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i);
-      }
-    }
+    each([&](uint32_t y, int i) {
+      if (y > t || (y == t && (uint32_t)i <= below)) take(y, i);
+    });
     __syncthreads();
     m = cnt;
+  }
+  if (m <= kSmallRank) {
+    // few: a key's rank is the number of keys above it (all keys differ), with no barrier
+    if (tid < m) {
+      const uint64_t mine = cand[tid];
+      int r = 0;
+#pragma unroll 8
+      for (int i = 0; i < m; ++i) r += cand[i] > mine ? 1 : 0;
+      if (r < k) {
+        const int j = (int)(0xFFFFFFFFu - (uint32_t)(mine & 0xFFFFFFFFu));
+        idx_out[r] = j;
+        if (val_out) val_out[r] = v[j];
+      }
+    }
+    return;
   }
   int p2 = 1;
   while (p2 < m) p2 <<= 1;
@@ -353,11 +380,11 @@ hipError_t launch_topk(const float *v, int n, int k, int32_t *idx_out, float *va
                        hipStream_t s) {
   if (n <= kSmallN && k <= kTopkMaxK) {
     if (n <= 4 * kSmallT)
-      hipLaunchKernelGGL(k_topk_small<4>, dim3(1), dim3(kSmallT), 0, s, v, n, k, idx_out, val_out);
+      hipLaunchKernelGGL((k_topk_small<4, true>), dim3(1), dim3(kSmallT), 0, s, v, n, k, idx_out, val_out);
     else if (n <= 16 * kSmallT)
-      hipLaunchKernelGGL(k_topk_small<16>, dim3(1), dim3(kSmallT), 0, s, v, n, k, idx_out, val_out);
+      hipLaunchKernelGGL((k_topk_small<16, true>), dim3(1), dim3(kSmallT), 0, s, v, n, k, idx_out, val_out);
     else
-      hipLaunchKernelGGL(k_topk_small<64>, dim3(1), dim3(kSmallT), 0, s, v, n, k, idx_out, val_out);
+      hipLaunchKernelGGL((k_topk_small<32, false>), dim3(1), dim3(kSmallT), 0, s, v, n, k, idx_out, val_out);
     return hipGetLastError();
   }
   uint32_t *hist = reinterpret_cast<uint32_t *>(scratch);
