@@ -772,12 +772,6 @@ __global__ __launch_bounds__(kThreads) void k_sg_readout(SgWeights W, const int3
   }
 }
 
-template <typename K>
-void set_lds_attr(K kernel, size_t lds) {
-  (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lds);
-}
-
 // arguments of one SG-CNN call
 struct SgCall {
   const int32_t *atom_off;
@@ -798,12 +792,8 @@ struct SgCall {
 template <int H, bool F32, bool SEP>
 hipError_t launch_rounds(const SgWeights &W, const SgCall &c, int stage, int r0, int K, float *&cur, float *&nxt,
                          hipStream_t s) {
-  const size_t lds = sizeof(float) * sg_lds_floats<H, F32>();
-  static bool attr = false;
-  if (!attr) {
-    set_lds_attr(&k_sg_round<H, F32, SEP>, lds);
-    attr = true;
-  }
+  constexpr size_t lds = sizeof(float) * sg_lds_floats<H, F32>();
+  static_assert(lds <= 65536, "a launch needs no attribute for this much");
   const int nbx = pose_blocks(c.n_atoms, c.mean_atoms, SgTile<H>::BLK);
   for (int r = r0; r < r0 + K; ++r) {
     hipLaunchKernelGGL((k_sg_round<H, F32, SEP>), dim3((unsigned)c.n_poses * nbx), dim3(kThreads), lds, s, W, stage, r,
