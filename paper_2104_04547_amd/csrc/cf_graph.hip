@@ -25,7 +25,8 @@
 // 2-way dot products give the sum of squares, < 3 * 2^30.  With every atom i of the
 // block within 32766 - r of the middle on each axis, an atom j that saturates is more
 // than r away from each of them, in truth and as computed, and the rest is exact.  A
-// block that spans more (27 A to either side at the usual cutoffs) takes the 32-bit form
+// block that spans more (27 A to either side at the usual cutoffs), and every block at a
+// cutoff above 32766 u, which a saturated difference does not exceed, takes the 32-bit form
 // (15 instructions; the whole batch in it: 174 + 204 us): |x_i - x_j| of two int32 is an exact unsigned 32-bit number
 // (v_sad_u32 on offset-binary values); clamped to C = r + 1 per axis, the sum of
 // squares is exact where it decides (all axes <= r) and above r^2 where an axis was
@@ -107,8 +108,9 @@ __device__ inline Frame block_frame(uint4 me, uint32_t r_nc) {
   f.mx = lo[0] + (hi[0] - lo[0]) / 2;
   f.my = lo[1] + (hi[1] - lo[1]) / 2;
   f.mz = lo[2] + (hi[2] - lo[2]) / 2;
-  const uint32_t reach = r_nc < 32766u ? 32766u - r_nc : 0u;
-  f.ok = hi[0] - f.mx <= reach && hi[1] - f.my <= reach && hi[2] - f.mz <= reach;
+  // a cutoff above 32766 lets no block through, not even one whose atoms share a place
+  const uint32_t reach = 32766u - r_nc;
+  f.ok = r_nc <= 32766u && hi[0] - f.mx <= reach && hi[1] - f.my <= reach && hi[2] - f.mz <= reach;
   return f;
 }
 __device__ inline int sat16(uint32_t q, uint32_t m) {
