@@ -28,6 +28,7 @@
 #include <mutex>
 
 #include "cf_internal.h"
+#include "cf_topk_pick.h"
 
 namespace cf {
 
@@ -251,8 +252,7 @@ __global__ __launch_bounds__(kSmallT) void k_topk_small(const float *__restrict_
 
 // ---- more values: radix select ----
 
-// state: [0] prefix (uint64), [1] mask of decided bits, [2] k remaining, [3] collected
-// count, [4] workgroups done with the pass, [5] 1 when the prefix already cuts off exactly k keys
+// state: see topk_pick
 __global__ void k_topk_init(uint32_t *hist, uint64_t *state, int k) {
   for (int i = threadIdx.x; i < 256; i += blockDim.x) hist[i] = 0;
   if (threadIdx.x < 6) state[threadIdx.x] = threadIdx.x == 2 ? (uint64_t)k : 0;
@@ -267,7 +267,8 @@ __global__ __launch_bounds__(kSelThreads) void k_topk_digit(const float *__restr
   if (state[5]) return;  // written by an earlier launch only: the same for all workgroups
   h[threadIdx.x] = 0;
   __syncthreads();
-  const uint64_t prefix = state[0], mask = state[1];
+  // krem too: the last workgroup writes the three, after the barriers below
+  const uint64_t prefix = state[0], mask = state[1], krem = state[2];
   for (int64_t i = blockIdx.x * (int64_t)kSelThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kSelThreads) {
     const uint64_t key = topk_key(v[i], (int)i);
     if ((key & mask) == prefix) atomicAdd(&h[(key >> shift) & 0xFF], 1u);
@@ -291,15 +292,7 @@ __global__ __launch_bounds__(kSelThreads) void k_topk_digit(const float *__restr
     h[threadIdx.x] += add;
     __syncthreads();
   }
-  const uint64_t krem = state[2];
-  const uint64_t at = h[threadIdx.x], above = at - own;  // keys with this digit or a larger one; a larger one
-  if (above < krem && at >= krem) {                      // exactly one digit
-    state[0] = prefix | (uint64_t)threadIdx.x << shift;
-    state[1] = mask | (uint64_t)0xFF << shift;
-    state[2] = krem - above;
-    state[4] = 0;
-    state[5] = krem - above == own ? 1 : 0;  // the whole bucket: no key below it has to be told apart
-  }
+  topk_pick(prefix, mask, krem, threadIdx.x, shift, own, h[threadIdx.x], state);
   hist[threadIdx.x] = 0;
 }
 
