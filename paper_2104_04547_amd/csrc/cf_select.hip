@@ -129,13 +129,14 @@ __global__ __launch_bounds__(kSmallT) void k_topk_small(const float *__restrict_
   __shared__ int cnt, total[2];
   const int tid = threadIdx.x, lane = tid & 63;
   uint32_t key[E];  // images of the values e * 1024 + tid; 0 past the end (as a NaN's, but never counted)
-  // buffer loads: one offset register for all of them (past the end they return zero)
+  // buffer loads: past the end of the values they return zero, which takes the whole offset
+  // in the vector operand (the scalar one is not part of the range check)
   const __amdgpu_buffer_rsrc_t rs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(v), (short)0, n * 4, 0x00020000);
   auto load = [&](int base) {
 #pragma unroll
     for (int e = 0; e < E; ++e)
-      key[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, tid * 4, (base + e * kSmallT) * 4, 0);
+      key[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, (base + e * kSmallT + tid) * 4, 0, 0);
 #pragma unroll
     for (int e = 0; e < E; ++e)
       key[e] = base + e * kSmallT + tid < n ? (uint32_t)(topk_key(__uint_as_float(key[e]), 0) >> 32) : 0u;
