@@ -12,9 +12,9 @@
 // ranking is "value descending, index ascending").
 //   * up to 65,536 values: one workgroup, up to 16,384 of them in registers.  The k-th largest
 //     of its 1024 threads' maxima bounds the k-th largest value from below; the few values
-//     at or above it are ranked.  Where too many are (large k, or values in an order that
-//     defeats the bound), a binary search over the value and then the index finds the
-//     k-th key exactly.
+//     at or above it are ranked.  Where too many are (ties, or values in an order that
+//     defeats the bound), histograms narrow the k-th value's range and ties are counted in
+//     the order of their indices.
 //   * more: radix select, 8 passes of an 8-bit digit histogram (the last workgroup of a pass
 //     picks the digit; passes after the key is certain return at once), one pass collects
 //     the keys at or above the k-th, and a single workgroup sorts those k keys.
@@ -113,7 +113,11 @@ __device__ inline void sort_keys(uint64_t *s, int m, int nth) {
 
 // ---- up to kSmallN values: one workgroup ----
 
-constexpr int kSmallT = 1024, kSmallN = 64 * kSmallT, kSmallCap = 8192;
+// Candidates beyond kSmallCap are narrowed first: a pass over 50,000 values takes about 7 us,
+// a sort of 2048 keys 20 and one of 8192 115.  Every call measured (n 1,024 .. 65,536, k 1 ..
+// 1024, random, sorted, rounded and equal values) is below the separate launches' 57 - 123 us:
+// the 1024 best of 50,000 random values 60 us, of equal ones 53.
+constexpr int kSmallT = 1024, kSmallN = 64 * kSmallT, kSmallCap = 2048;
 // keys that are ranked by counting instead of sorted: a wave reads all of them, so the
 // count grows with the square; a sort of 256 is 36 steps with a barrier each
 constexpr int kSmallRank = 256;
@@ -125,8 +129,9 @@ template <int E, bool HOLD>
 __global__ __launch_bounds__(kSmallT) void k_topk_small(const float *__restrict__ v, int n, int k,
                                                        int32_t *__restrict__ idx_out, float *__restrict__ val_out) {
   __shared__ uint64_t cand[kSmallCap];
-  __shared__ uint32_t thr;
-  __shared__ int cnt, total[2];
+  __shared__ uint32_t thr, top;
+  __shared__ int cnt, pick[3], wsum[kSmallT / 64];
+  __shared__ int bin[kSmallN / 64];  // counts of a digit's 256 values, or of the 64-index groups
   const int tid = threadIdx.x, lane = tid & 63;
   uint32_t key[E];  // images of the values e * 1024 + tid; 0 past the end (as a NaN's, but never counted)
   // buffer loads: past the end of the values they return zero, which takes the whole offset
@@ -171,9 +176,23 @@ __global__ __launch_bounds__(kSmallT) void k_topk_small(const float *__restrict_
 #pragma unroll
       for (int u = 0; u < kSmallT / 64; ++u) have += __popcll(__ballot(q[u] >= c));
       if (have >= k) t = c;
-      if (have == k) break;  // the lower bits only raise the bound
+      if (have == k) {  // exactly these: the smallest of them
+        uint32_t least = 0xFFFFFFFFu;
+#pragma unroll
+        for (int u = 0; u < kSmallT / 64; ++u) least = q[u] >= c && q[u] < least ? q[u] : least;
+        for (int o = 32; o >= 1; o >>= 1) least = min(least, (uint32_t)__shfl_xor((int)least, o, 64));
+        t = least;
+        break;
+      }
     }
-    if (lane == 0) thr = t;
+    uint32_t most = 0;
+#pragma unroll
+    for (int u = 0; u < kSmallT / 64; ++u) most = q[u] > most ? q[u] : most;
+    for (int o = 32; o >= 1; o >>= 1) most = max(most, (uint32_t)__shfl_xor((int)most, o, 64));
+    if (lane == 0) {
+      thr = t;
+      top = most;
+    }
   }
   __syncthreads();
   const uint32_t lo = thr;
@@ -188,38 +207,82 @@ __global__ __launch_bounds__(kSmallT) void k_topk_small(const float *__restrict_
   __syncthreads();
   int m = cnt;
   if (m > kSmallCap) {
-    // exact: the largest value image t that at least k values reach, then the smallest index
-    // bound x such that k keys are above t or at t with an index below x
-    auto count = [&](auto pred, int slot) {
-      int c = 0;
-      each([&](uint32_t y, int i) { c += pred(y, i) ? 1 : 0; });
-      for (int o = 32; o >= 1; o >>= 1) c += __shfl_xor(c, o, 64);
-      if (lane == 0 && c) atomicAdd(&total[slot], c);
-    };
-    auto reach = [&](auto pred, int step) {  // number of keys for which pred holds
-      const int slot = step & 1;
-      if (tid == 0) total[slot] = 0;
+    // Too many: the range [lo2, hi2] of the k-th largest image is split 256-fold, by a
+    // histogram of the images in it, until few enough keys reach its lower end or it is a
+    // single image, of which the keys with the lowest indices are taken.  The keys of a wave
+    // that share the first one's digit are added together: where many are too many, they
+    // are mostly equal.
+    uint32_t lo2 = lo, hi2 = top;
+    int krem = k, reach = m;  // the krem-th largest of the range is sought; keys at or above lo2
+    while (reach > kSmallCap && lo2 != hi2) {
+      const int shift = max(0, 24 - __clz((int)(hi2 - lo2)));
+      if (tid < 256) bin[tid] = 0;
       __syncthreads();
-      count(pred, slot);
+      each([&](uint32_t y, int) {
+        if (y < lo2 || y > hi2) return;
+        const int d = (int)((y - lo2) >> shift);
+        const uint64_t same = __ballot(d == __builtin_amdgcn_readfirstlane(d));
+        if (!(same >> lane & 1))
+          atomicAdd(&bin[d], 1);
+        else if (lane == __ffsll((unsigned long long)same) - 1)
+          atomicAdd(&bin[d], __popcll(same));
+      });
       __syncthreads();
-      return total[slot];
-    };
-    uint32_t t = 0;
-    int step = 0;
-    for (int bit = 31; bit >= 0; --bit) {
-      const uint32_t c = t | 1u << bit;
-      if (reach([&](uint32_t y, int) { return y >= c; }, step++) >= k) t = c;
+      if (tid < 64) {
+        int own[4], sum = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) sum += own[u] = bin[4 * lane + u];
+        int at = sum;  // keys of this lane's digits and of larger ones
+        for (int o = 1; o < 64; o <<= 1) {
+          const int w = __shfl_down(at, o, 64);
+          if (lane + o < 64) at += w;
+        }
+        int above = at - sum;
+#pragma unroll
+        for (int u = 3; u >= 0; --u) {
+          if (above < krem && above + own[u] >= krem) {  // exactly one digit
+            pick[0] = 4 * lane + u;
+            pick[1] = above;
+            pick[2] = own[u];
+          }
+          above += own[u];
+        }
+      }
+      __syncthreads();
+      lo2 += (uint32_t)pick[0] << shift;
+      hi2 = lo2 + min(hi2 - lo2, (1u << shift) - 1u);
+      krem -= pick[1];
+      reach = k - krem + pick[2];
     }
-    uint32_t below = 0;  // the largest x with fewer than k such keys; the k-th has index x
-    for (int bit = 16; bit >= 0; --bit) {
-      const uint32_t x = below | 1u << bit;
-      if (reach([&](uint32_t y, int i) { return y > t || (y == t && (uint32_t)i < x); }, step++) < k) below = x;
+    const bool ties = reach > kSmallCap;  // of image lo2, of which the first krem indices are taken
+    if (ties) {
+      // the ties before each group of 64 indices (one wave's share of one load)
+      each([&](uint32_t y, int i) {
+        const uint64_t b = __ballot(y == lo2);
+        if (lane == 0) bin[i >> 6] = __popcll(b);
+      });
+      __syncthreads();
+      const int own = tid * 64 < n ? bin[tid] : 0;
+      int in = own;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int w = __shfl_up(in, o, 64);
+        if (lane >= o) in += w;
+      }
+      if (lane == 63) wsum[tid >> 6] = in;
+      __syncthreads();
+      int before = in - own;
+      for (int w = 0; w < tid >> 6; ++w) before += wsum[w];
+      bin[tid] = before;
     }
-    __syncthreads();
     if (tid == 0) cnt = 0;
     __syncthreads();
     each([&](uint32_t y, int i) {
-      if (y > t || (y == t && (uint32_t)i <= below)) take(y, i);
+      bool mine = y >= lo2;
+      if (ties) {
+        const uint64_t b = __ballot(y == lo2);
+        if (y == lo2) mine = bin[i >> 6] + __popcll(b & ((1ull << lane) - 1ull)) < krem;
+      }
+      if (mine) take(y, i);
     });
     __syncthreads();
     m = cnt;
