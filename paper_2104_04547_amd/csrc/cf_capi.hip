@@ -457,8 +457,8 @@ std::vector<T> pack_conv(const std::vector<float> &W, int cout, int cin, int k, 
   const int CC = sizeof(T) == 2 ? 16 : 8;
   const int nchunks = cin_pad / CC;
   const int taps = k * k * k;
-  // two extra zero taps: the conv kernel prefetches weights two taps ahead
-  std::vector<T> out((size_t)(taps + 2) * nchunks * cout_pad32 * CC, to_t<T>(0.0f));
+  // zero taps past the end: the conv kernels prefetch weights up to that many taps ahead
+  std::vector<T> out((size_t)(taps + cf::kConvPadTaps) * nchunks * cout_pad32 * CC, to_t<T>(0.0f));
   for (int tap = 0; tap < taps; ++tap)
     for (int ch = 0; ch < nchunks; ++ch)
       for (int n = 0; n < cout; ++n)

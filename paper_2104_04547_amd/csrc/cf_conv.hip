@@ -153,8 +153,9 @@ __global__ __launch_bounds__(NW * 64) void k_conv(const T *__restrict__ in, cons
     __syncthreads();
     // Taps are consecutive in the packed weights, so the B fragments of tap t+1 and
     // t+2 are in flight while tap t's MFMAs issue.  They are buffer loads with the
-    // tap offset in a scalar register (no per-tap address arithmetic); reads past
-    // the buffer return zero.
+    // tap offset in a scalar register (no per-tap address arithmetic); past the last
+    // tap they read the zero taps of the padding.
+    static_assert(2 <= kConvPadTaps, "prefetch past the weight padding");
     int vb[C::NB];
 #pragma unroll
     for (int nb = 0; nb < C::NB; ++nb)
@@ -355,6 +356,7 @@ struct Conv8Cfg {
   static constexpr bool AHEAD = FINE && HITER <= 9;
   static constexpr int PF = PP > 1 ? 6 : BLOCKS == 1 ? 16 : BLOCKS == 2 ? 8 : ((NB <= 2 && KS > 3) ? 4 : 2);
   static_assert(PF % AD == 0 && (!FINE || PF % 8 == 0), "the unrolled walk indexes the rings at compile time");
+  static_assert(PF <= kConvPadSteps, "prefetch past the weight padding");
   static_assert(!FINE || HALO / 16 < 65536, "16-bit table entries");
   static constexpr int WGCU = (163840 / LDS < WPE * 4 / NW ? 163840 / LDS : WPE * 4 / NW) < 1 ? 1 : (163840 / LDS < WPE * 4 / NW ? 163840 / LDS : WPE * 4 / NW);
   static_assert(NW % WN == 0 && NT % (32 * WN) == 0, "waves split the columns in 32-column blocks");
@@ -445,8 +447,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(Conv8Cf
     const int t1 = (2 * p + 1 < C::TAPS) ? tapoff(ez, ey, ex) : t0;
     return khalf ? t1 : t0;
   };
-  // the rings read past the last pair: zero weights of the padding, or zeros from
-  // beyond the buffer; neither reaches an MFMA
+  // the rings read past the last pair: zero weights of the padding, which reach no MFMA
   constexpr int kPF = C::PF, AD = C::AD;
   uint16_t *tab = reinterpret_cast<uint16_t *>(lds_all);
   if constexpr (C::FINE) {
@@ -737,6 +738,7 @@ struct Conv4Cfg {
   static_assert(WM % 32 == 0, "rows per wave must be a multiple of 32");
   static_assert(LDS <= 163840, "halo exceeds LDS");
   static_assert(AD == 2 || (PF == 8 && AD == 4 && HALO / 8 < 65536), "packed table of the deep walk");
+  static_assert(PF <= kConvPadSteps, "prefetch past the weight padding");
 };
 
 template <int KS, int S, int TZ, int TY, int TX, int NW, int NT>
@@ -789,7 +791,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(Conv4Cf
   const int oz = tz0 * S - C::PAD, oy = ty0 * S - C::PAD, ox = tx0 * S - C::PAD;
   const int64_t pose_in = (int64_t)pose * D * D * D;
   constexpr int NV = C::HZ * C::HY * C::HX;
-  constexpr int kPF = C::PF;  // past the last quad: zeros of the padding or from beyond the buffer
+  constexpr int kPF = C::PF;  // past the last quad: zero weights of the padding
   const int quad_bytes = nchunks * cout_pad32 * 16 * 2;
   const __amdgpu_buffer_rsrc_t wrs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(wpk), (short)0, wbytes, 0x00020000);
@@ -1033,6 +1035,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     constexpr int STEPS = decltype(steps_c)::value;
     const int vb = ((chunk * cout_pad32 + n0 + lrow) * 8 + khalf * 4) * 4;
     constexpr int PF = 4;
+    static_assert(PF <= kConvPadTaps, "prefetch past the weight padding");
     float4 b[PF];
 #pragma unroll
     for (int q = 0; q < PF; ++q)

@@ -92,9 +92,11 @@ inline int pose_blocks(int n_atoms, int mean_atoms, int rows) {
   return want < 1 ? 1 : (want + rows - 1) / rows;
 }
 
-// Zero K steps past the end of the packed tap-pair / tap-quad weights: the conv
-// kernels prefetch weight fragments up to this many steps ahead.
-constexpr int kConvPadSteps = 6;
+// Zero K steps past the end of the packed weights (tap pairs and tap quads; single taps):
+// the conv kernels read weight fragments up to this many steps ahead, and the scalar offset
+// those reads step by is not part of a buffer load's range check.
+constexpr int kConvPadSteps = 16;
+constexpr int kConvPadTaps = 4;
 
 // ---- per-layer conv launch description (host side) ----
 struct ConvLayer {

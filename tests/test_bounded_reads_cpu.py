@@ -34,3 +34,20 @@ def test_top_k_reads_have_no_scalar_offset(tmp_path):
     assert len(loads) >= 3, "no buffer loads found in k_topk_small"
     bad = [line for line, soffset in loads.items() if soffset != "0"]
     assert not bad, bad[:3]
+
+
+@pytest.mark.skipif(not os.path.exists("/opt/rocm/bin/hipcc"), reason="hipcc absent")
+@pytest.mark.parametrize("name,steps", [("kConvPadSteps", 15), ("kConvPadTaps", 3)])
+def test_conv_weight_prefetch_stays_within_the_padding(tmp_path, name, steps):
+    """The deepest prefetch equals the padding of the packed weights: with one step less
+    the kernels do not compile."""
+    shutil.copytree(os.path.join(ROOT, "include"), tmp_path / "include")
+    csrc = shutil.copytree(os.path.join(ROOT, "paper_2104_04547_amd", "csrc"), tmp_path / "a" / "csrc")
+    header = os.path.join(csrc, "cf_internal.h")
+    text, n = re.subn(rf"constexpr int {name} = \d+;", f"constexpr int {name} = {steps};", open(header).read())
+    assert n == 1
+    with open(header, "w") as f:
+        f.write(text)
+    r = subprocess.run(["/opt/rocm/bin/hipcc", "--offload-arch=gfx950", "-std=c++17", "-fsyntax-only", "--cuda-device-only",
+                        "-I", str(tmp_path / "include"), os.path.join(csrc, "cf_conv.hip")], capture_output=True, text=True)
+    assert r.returncode != 0 and "prefetch past the weight padding" in r.stderr, r.stderr[-2000:]
