@@ -223,17 +223,23 @@ int cf_model_info(const cf_ctx *ctx, int32_t *latent_cnn, int32_t *latent_sg, in
 
 /* Conv autotuning (batching form): time the candidate tile / wave layouts of
  * every conv layer at grid size G on a synthetic batch of n_poses poses and keep
- * the fastest per layer (cached in the context and reused for that G). */
+ * the fastest per layer (cached in the context and reused for that G): launches of
+ * at least as many poses run exactly those (n_poses, or as many as one launch of
+ * the context takes).  Smaller launches, and all launches without autotuning or
+ * pinned variants, may take another tile of the same kernel that suits their size,
+ * with the same results bit for bit; cf_timing_read names the tile that ran. */
 int cf_autotune(cf_ctx *ctx, int G, int32_t n_poses, void *stream);
 
 /* Chosen kernel variant per conv layer for grid size G (after cf_autotune or the
  * default table): variant_out[n_conv]. */
 int cf_conv_variants(const cf_ctx *ctx, int G, int32_t *variant_out, int32_t max_layers);
 /* Pin the conv kernel variant of every layer for grid size G (e.g. a cached
- * autotuning result).  CF_ERR_UNSUPPORTED if a variant does not fit its layer. */
+ * autotuning result): launches of any size run exactly these.  CF_ERR_UNSUPPORTED
+ * if a variant does not fit its layer. */
 int cf_set_conv_variants(cf_ctx *ctx, int G, const int32_t *variants, int32_t n_layers);
 /* Number of conv kernel variants in the library and the name of one (tile shape,
- * waves, output-channel tile; "p8" = bf16 tap-pair kernel). */
+ * waves, output-channel tile; "p8" = bf16 tap-pair kernel, "q4" = bf16 tap quads,
+ * "f32" = the plain form's small tiles). */
 int cf_conv_variant_count(void);
 const char *cf_conv_variant_name(int32_t variant);
 

@@ -10,7 +10,6 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
-#include <set>
 #include <string>
 #include <vector>
 
@@ -114,8 +113,14 @@ struct cf_ctx {
   std::vector<char> gspec_t_set;           // ... built by the first backward call that takes them
   DevBuf splatwork;                        // per-atom normalisers and per-tile atom lists
   DevBuf convwork;          // scratch of the frequency-domain conv (spectra)
-  std::map<int, std::vector<int>> variants;  // per G
-  std::set<int> pinned;                      // G whose variants the caller set: run exactly those
+  // Per G: the conv variants, and the fewest poses of a launch that runs exactly those (1
+  // where the caller set them, the measured batch where they were autotuned).  Smaller
+  // launches, and all of them where the variants are the default table's, fit their tiles.
+  struct Variants {
+    std::vector<int> v;
+    int exact_from = 1 << 30;
+  };
+  std::map<int, Variants> variants;
 };
 
 namespace {
@@ -307,7 +312,7 @@ int validate_G(int G) {
 int variants_for(cf_ctx *c, int G, std::vector<int> &out) {
   auto it = c->variants.find(G);
   if (it != c->variants.end()) {
-    out = it->second;
+    out = it->second.v;
     return CF_OK;
   }
   out.clear();
@@ -319,7 +324,7 @@ int variants_for(cf_ctx *c, int G, std::vector<int> &out) {
     D = conv_out_dim(D, L.k, L.stride);
     if (D < 1) return fail(CF_ERR_UNSUPPORTED, "grid too small for the conv stack");
   }
-  c->variants[G] = out;
+  c->variants[G].v = out;
   return CF_OK;
 }
 
@@ -343,7 +348,13 @@ int run_cnn(cf_ctx *c, int G, int np, float *cnn_lat, hipStream_t s, hipEvent_t 
   std::vector<int> var;
   int rc = variants_for(c, G, var);
   if (rc) return rc;
-  const bool fit = c->pinned.count(G) == 0;
+  if (np < c->variants[G].exact_from) {
+    int D = G;
+    for (size_t i = 0; i < c->conv.size(); ++i) {
+      var[i] = cf::conv_fit_variant(var[i], c->conv[i], c->bf16, D, np);
+      D = conv_out_dim(D, c->conv[i].k, c->conv[i].stride);
+    }
+  }
   {
     int64_t work = 0;
     int D = G;
@@ -408,7 +419,7 @@ int run_cnn(cf_ctx *c, int G, int np, float *cnn_lat, hipStream_t s, hipEvent_t 
       continue;
     }
     hipEvent_t e = tbegin(c, s);
-    CF_HIP(cf::launch_conv(var[i], L, c->bf16, t[i], res, c->act[i].p, np, D, c->convwork.p, s, fit));
+    CF_HIP(cf::launch_conv(var[i], L, c->bf16, t[i], res, c->act[i].p, np, D, c->convwork.p, s));
     if (e) {
       const double vox = (double)Do * Do * Do * np;
       const double flop = 2.0 * L.cin * L.cout * L.k * L.k * L.k * vox;
@@ -1531,8 +1542,9 @@ int cf_set_conv_variants(cf_ctx *c, int G, const int32_t *variants, int32_t n_la
     D = conv_out_dim(D, c->conv[i].k, c->conv[i].stride);
     if (D < 1) return fail(CF_ERR_UNSUPPORTED, "grid too small for the conv stack");
   }
-  c->variants[G] = v;
-  c->pinned.insert(G);
+  auto &set = c->variants[G];
+  set.v = std::move(v);
+  set.exact_from = 1;
   return CF_OK;
 }
 
@@ -1604,8 +1616,9 @@ int cf_autotune(cf_ctx *c, int G, int32_t n_poses, void *stream) {
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  c->variants[G] = best;
-  c->pinned.erase(G);
+  auto &set = c->variants[G];
+  set.v = std::move(best);
+  set.exact_from = np;
   return CF_OK;
 }
 

@@ -1126,7 +1126,9 @@ hipError_t launch_f(const ConvLayer &L, const void *in, const void *res, void *o
 struct Variant {
   const char *name;
   int ks, s, tz, ty, tx, nw, nt;
-  int pairs;  // 1: bf16 8-channel tap-pair kernel (k_conv8, weights in wpk8); 2: 4-channel tap quads (k_conv4, wpk4)
+  // 0: k_conv; 1: bf16 8-channel tap-pair kernel (k_conv8, weights in wpk8); 2: 4-channel tap quads (k_conv4,
+  // wpk4); 3: the plain form's small tiles (k_conv_f32)
+  int pairs;
   hipError_t (*launch_bf16)(const ConvLayer &, const void *, const void *, void *, int, int, hipStream_t);
   hipError_t (*launch_f32)(const ConvLayer &, const void *, const void *, void *, int, int, hipStream_t);
   int pp, blocks, wgcu;  // poses per workgroup, 32 x 32 blocks per wave, workgroups per CU (tap kernels)
@@ -1181,6 +1183,11 @@ hipError_t launch_t(const ConvLayer &L, const void *in, const void *res, void *o
     "q4k" #KS "s" #S "_t" #TZ "x" #TY "x" #TX "_w" #NW "_n" #NT, KS, S, TZ, TY, TX, NW, NT, 2,   \
         &launch_q<KS, S, TZ, TY, TX, NW, NT>, nullptr, 1,                                        \
         Conv4Cfg<KS, S, TZ, TY, TX, NW, NT>::BLOCKS, Conv4Cfg<KS, S, TZ, TY, TX, NW, NT>::WGCU   \
+  }
+#define CF_VARIANTF(KS, S, TZ, TY, TX, RW)                                                       \
+  Variant {                                                                                      \
+    "f32k" #KS "s" #S "_t" #TZ "x" #TY "x" #TX "_w4", KS, S, TZ, TY, TX, 4, ConvFCfg<KS, S, TZ, TY, TX, RW>::NT, 3, \
+        nullptr, &launch_f<KS, S, TZ, TY, TX, RW>, 1, 1, 2                                       \
   }
 // ... and PP poses per workgroup
 #define CF_VARIANT8P(KS, S, TZ, TY, TX, NW, NT, WN, PP)                                                           \
@@ -1249,8 +1256,9 @@ const Variant kVariants[] = {
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
-// Finer tiles for batches that leave the chip idle at the variants above; chosen by
-// fit_tile only, so that variant ids stay what callers may have stored.
+// Finer tiles for batches that leave the chip idle at the variants above, then the plain
+// form's small tiles (64 columns before 32).  Their ids follow the frequency-domain path's,
+// so that the ids callers may have stored stay what they were.
 const Variant kFineTiles[] = {
     CF_VARIANT8N(7, 2, 4, 4, 4, 4, 64, 2),   // 12^3 outputs exactly, one 32 x 32 block per wave
     CF_VARIANT8N(3, 1, 4, 4, 4, 4, 64, 2),
@@ -1258,8 +1266,28 @@ const Variant kFineTiles[] = {
     CF_VARIANT8(5, 1, 4, 4, 8, 4, 32),
     CF_VARIANT4(7, 2, 4, 4, 8, 4, 64),
     CF_VARIANT4(5, 2, 4, 4, 8, 4, 32),
-    CF_VARIANT4(5, 1, 4, 4, 8, 4, 32)
+    CF_VARIANT4(5, 1, 4, 4, 8, 4, 32),
+    CF_VARIANTF(7, 2, 4, 4, 4, 2),
+    CF_VARIANTF(5, 2, 4, 4, 4, 2),
+    CF_VARIANTF(3, 2, 4, 4, 4, 2),
+    CF_VARIANTF(7, 1, 4, 4, 4, 2),
+    CF_VARIANTF(5, 1, 4, 4, 4, 2),
+    CF_VARIANTF(3, 1, 4, 4, 4, 2),
+    CF_VARIANTF(5, 2, 4, 4, 8, 4),
+    CF_VARIANTF(3, 2, 4, 4, 8, 4),
+    CF_VARIANTF(7, 1, 4, 4, 8, 4),
+    CF_VARIANTF(5, 1, 4, 4, 8, 4),
+    CF_VARIANTF(3, 1, 4, 4, 8, 4)
 };
+constexpr int kNumFine = sizeof(kFineTiles) / sizeof(kFineTiles[0]);
+// one id past the direct kernels: the frequency-domain path
+constexpr int kFftVariant = kNumVariants;
+
+// the direct kernel of an id (null: the frequency-domain path, or no such id)
+const Variant *variant_of(int v) {
+  if (v >= 0 && v < kNumVariants) return &kVariants[v];
+  return v > kFftVariant && v <= kFftVariant + kNumFine ? &kFineTiles[v - kFftVariant - 1] : nullptr;
+}
 
 bool tap_kernel_ok(const Variant &V, const ConvLayer &L) {
   if (V.ks != L.k || V.s != L.stride || L.cout_pad32 % V.nt != 0) return false;
@@ -1291,38 +1319,40 @@ double tile_cost(const Variant &V, const ConvLayer &L, int Do, int n_poses) {
 // tiles: 411 / 73 us for one 24^3 pose (9 workgroups of the big tile on 256 CUs), 492 /
 // 381 for 24, 537 / 539 for 40, 996 / 873 for 64 (a second round), 1065 / 671 for 19 poses
 // of 32^3; first layer, 512- against 128-row tiles: 110 / 51 us for one pose, 120 / 75 for four.
-const Variant &fit_tile(const Variant &V, const ConvLayer &L, int D_in, int n_poses) {
+int fit_tile(int v, const ConvLayer &L, int D_in, int n_poses) {
+  const Variant &V = *variant_of(v);
   const int Do = (D_in + 2 * ((L.k - 1) / 2) - L.k) / L.stride + 1;
-  const Variant *best = &V;
+  int best = v;
   double cost = 0.9 * tile_cost(V, L, Do, n_poses);
-  auto consider = [&](const Variant &C) {
+  auto consider = [&](int id) {
+    const Variant &C = *variant_of(id);
     if (C.pairs != V.pairs || !tap_kernel_ok(C, L)) return;
     const double t = tile_cost(C, L, Do, n_poses);
     if (t < cost) {
       cost = t;
-      best = &C;
+      best = id;
     }
   };
-  for (const Variant &C : kFineTiles) consider(C);
-  for (const Variant &C : kVariants) consider(C);
-  return *best;
+  for (int i = 0; i < kNumFine; ++i) consider(kFftVariant + 1 + i);
+  for (int i = 0; i < kNumVariants; ++i) consider(i);
+  return best;
 }
 
 }  // namespace
 
-// one more variant id past the direct kernels: the frequency-domain path
-constexpr int kFftVariant = kNumVariants;
-
-int conv_num_variants() { return kNumVariants + 1; }
+int conv_num_variants() { return kNumVariants + 1 + kNumFine; }
 const char *conv_variant_name(int v) {
-  return (v >= 0 && v < kNumVariants) ? kVariants[v].name : (v == kFftVariant ? "fft32" : "?");
+  const Variant *V = variant_of(v);
+  return V ? V->name : (v == kFftVariant ? "fft32" : "?");
 }
 
 bool conv_variant_ok(int v, const ConvLayer &L, int bf16, int D_in) {
   if (v == kFftVariant) return (bf16 ? !L.spec_f32 : L.spec_f32) && fft_conv_ok(L, D_in);
-  if (v < 0 || v >= kNumVariants) return false;
-  const Variant &V = kVariants[v];
-  if (V.pairs) return bf16 && tap_kernel_ok(V, L);
+  const Variant *p = variant_of(v);
+  if (!p) return false;
+  const Variant &V = *p;
+  if (V.pairs == 1 || V.pairs == 2) return bf16 && tap_kernel_ok(V, L);
+  if (V.pairs == 3 && bf16) return false;
   const int cc = bf16 ? 16 : 8;
   return V.ks == L.k && V.s == L.stride && L.cout_pad32 % V.nt == 0 && L.cin_pad % cc == 0;
 }
@@ -1373,34 +1403,22 @@ hipError_t launch_fill_random(void *p, int64_t bytes, int bf16, uint64_t seed, h
   return hipGetLastError();
 }
 
+int conv_fit_variant(int v, const ConvLayer &L, int bf16, int D_in, int n_poses) {
+  const Variant *V = variant_of(v);
+  if (!V || !conv_variant_ok(v, L, bf16, D_in)) return v;
+  if (bf16) return V->pairs ? fit_tile(v, L, D_in, n_poses) : v;
+  // the plain form's small tiles are the faster ones at every batch size measured (1 .. 256
+  // poses, see k_conv_f32)
+  for (int i = 0; i < kNumFine; ++i)
+    if (kFineTiles[i].pairs == 3 && conv_variant_ok(kFftVariant + 1 + i, L, bf16, D_in)) return kFftVariant + 1 + i;
+  return v;
+}
+
 hipError_t launch_conv(int variant, const ConvLayer &L, int bf16, const void *in, const void *res,
-                       void *out, int n_poses, int D_in, void *work, hipStream_t s, bool fit) {
+                       void *out, int n_poses, int D_in, void *work, hipStream_t s) {
   if (!conv_variant_ok(variant, L, bf16, D_in)) return hipErrorInvalidValue;
   if (variant == kFftVariant) return launch_fft_conv(L, in, res, out, n_poses, D_in, work, s);
-  // the plain form's small tiles are the faster ones at every batch size measured (1 .. 256
-  // poses, see k_conv_f32); the variants themselves run when the caller sets them
-  if (fit && !bf16) {
-#define CF_F(KS, S)                                                                                          \
-  if (L.k == KS && L.stride == S && L.cout_pad32 % 64 == 0)                                                  \
-    return launch_f<KS, S, 4, 4, 4, 2>(L, in, res, out, n_poses, D_in, s);
-#define CF_F32(KS, S)                                                                                        \
-  if (L.k == KS && L.stride == S) return launch_f<KS, S, 4, 4, 8, 4>(L, in, res, out, n_poses, D_in, s);
-    CF_F(7, 2)
-    CF_F(5, 2)
-    CF_F(3, 2)
-    CF_F(7, 1)
-    CF_F(5, 1)
-    CF_F(3, 1)
-    CF_F32(5, 2)
-    CF_F32(3, 2)
-    CF_F32(7, 1)
-    CF_F32(5, 1)
-    CF_F32(3, 1)
-#undef CF_F
-#undef CF_F32
-  }
-  const Variant &V = fit && bf16 && kVariants[variant].pairs ? fit_tile(kVariants[variant], L, D_in, n_poses)
-                                                             : kVariants[variant];
+  const Variant &V = *variant_of(variant);
   return bf16 ? V.launch_bf16(L, in, res, out, n_poses, D_in, s) : V.launch_f32(L, in, res, out, n_poses, D_in, s);
 }
 

@@ -143,10 +143,11 @@ bool conv_variant_ok(int v, const ConvLayer &L, int bf16, int D_in);
 int conv_default_variant(const ConvLayer &L, int D_in, int bf16);
 // device scratch a variant needs for n_poses (0 for the direct kernels)
 int64_t conv_work_bytes(int v, const ConvLayer &L, int D_in, int n_poses);
-// fit: a batch too small for the variant's tile may take a finer tile of the same kernel
-// (the same sums in the same order)
+// the variant that a launch of n_poses runs in place of v where the choice is free: another
+// tile of the same kernel (the same sums in the same order), or v itself
+int conv_fit_variant(int v, const ConvLayer &L, int bf16, int D_in, int n_poses);
 hipError_t launch_conv(int variant, const ConvLayer &L, int bf16, const void *in, const void *res,
-                       void *out, int n_poses, int D_in, void *work, hipStream_t s, bool fit = false);
+                       void *out, int n_poses, int D_in, void *work, hipStream_t s);
 // seeded values uniform in [0, 0.5) over `bytes` of bf16 or fp32 elements
 hipError_t launch_fill_random(void *p, int64_t bytes, int bf16, uint64_t seed, hipStream_t s);
 
