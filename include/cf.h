@@ -282,8 +282,11 @@ int cf_timing_read(cf_ctx *ctx, cf_kernel_stat *out, int32_t max_entries, int32_
  * head and the unstaged SG-CNN (H_nc = 0); otherwise CF_ERR_UNSUPPORTED.  Unlike
  * the scoring calls it reads batch->atom_off back to the host (one synchronous
  * copy on `stream`) to size its per-atom launches, and checks it there.  Poses
- * are processed in chunks of at most 32; every reduction runs in a fixed order,
- * so the result is reproducible bit for bit.  Device-detected input errors are
+ * are processed in chunks of at most 32; every reduction runs in a fixed order, and
+ * how the work is split follows from the shapes and the context's budget, so the
+ * result is reproducible bit for bit.  (Only where earlier calls left so much scratch
+ * allocated that this does not fit the budget beside it does a call take smaller
+ * chunks or other kernels, which round differently.)  Device-detected input errors are
  * reported by cf_stream_status as for scoring. */
 int cf_backward(cf_ctx *ctx, const cf_pose_batch *batch, int G, const float *dscore, float *grad, float *scores,
                 void *stream);

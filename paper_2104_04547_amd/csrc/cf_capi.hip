@@ -11,6 +11,7 @@
 #include <cstring>
 #include <map>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "cf_internal.h"
@@ -241,52 +242,58 @@ int64_t pose_bytes(const cf_ctx *c, int G) {
 }
 
 
-// Scratch the context will hold after a call that needs buffers for n poses at
-// grid size G and, when atoms > 0, per-atom buffers for that many atoms: the
-// buffers only grow (ensure keeps a larger allocation), so each one counts as
-// the larger of what it holds and what the call needs.
-int64_t scratch_after(const cf_ctx *c, int G, int64_t n, int64_t atoms) {
-  int64_t t = c->scratch_bytes;
-  auto grow = [&](const DevBuf &b, int64_t need) {
-    if (need > (int64_t)b.n) t += need - (int64_t)b.n;
-  };
-  grow(c->grid, n * G * G * G * grid_cpad(c) * (int64_t)elem_size(c));
+// f(buffer, bytes) for every buffer that the forward pass needs for n poses at grid size G
+// and, when atoms > 0, that many atoms (buffer null: not there yet)
+template <typename F>
+void forward_needs(const cf_ctx *c, int G, int64_t n, int64_t atoms, F f) {
+  f(&c->grid, n * G * G * G * grid_cpad(c) * (int64_t)elem_size(c));
   int D = G;
   int64_t work = 0;
   for (size_t i = 0; i < c->conv.size(); ++i) {
     // the frequency-domain path's spectra, wherever it may be selected
     if (cf::fft_conv_ok(c->conv[i], D)) work = std::max(work, cf::fft_conv_work_bytes(c->conv[i], D, n));
     D = conv_out_dim(D, c->conv[i].k, c->conv[i].stride);
-    const int64_t need = n * D * D * D * c->conv[i].cout_store * (int64_t)elem_size(c);
-    if (i < c->act.size()) grow(c->act[i], need);
-    else t += need;
+    f(i < c->act.size() ? &c->act[i] : nullptr, n * D * D * D * c->conv[i].cout_store * (int64_t)elem_size(c));
   }
-  grow(c->convwork, work);
-  grow(c->centers, n * 3 * 4);
-  grow(c->cnn_lat, n * c->lc * 4);
-  grow(c->sg_lat, n * c->sgw * 4);
+  f(&c->convwork, work);
+  f(&c->centers, n * 3 * 4);
+  f(&c->cnn_lat, n * c->lc * 4);
+  f(&c->sg_lat, n * c->sgw * 4);
   if (atoms > 0) {
-    grow(c->splatwork, cf::splat_work_bytes((int)n, atoms, G));
-    grow(c->deg, 2 * atoms * 4);
-    grow(c->pose_tot, 4 * n * 8);
-    grow(c->cov_row, (atoms + 1) * 4);
-    grow(c->nc_row, (atoms + 1) * 4);
-    grow(c->cov_col, atoms * 16 * 4);
-    grow(c->nc_col, atoms * 96 * 4);
-    grow(c->hbuf, atoms * c->sg_floats * 4);
+    f(&c->splatwork, cf::splat_work_bytes((int)n, atoms, G));
+    f(&c->deg, 2 * atoms * 4);
+    f(&c->pose_tot, 4 * n * 8);
+    f(&c->cov_row, (atoms + 1) * 4);
+    f(&c->nc_row, (atoms + 1) * 4);
+    f(&c->cov_col, atoms * 16 * 4);
+    f(&c->nc_col, atoms * 96 * 4);
+    f(&c->hbuf, atoms * c->sg_floats * 4);
   }
+}
+
+// Scratch the context will hold after a call that needs those: the buffers only grow
+// (ensure keeps a larger allocation), so each one counts as the larger of what it
+// holds and what the call needs.  fresh: as if the context held nothing yet.
+int64_t scratch_after(const cf_ctx *c, int G, int64_t n, int64_t atoms, bool fresh = false) {
+  int64_t t = fresh ? 0 : c->scratch_bytes;
+  forward_needs(c, G, n, atoms, [&](const DevBuf *b, int64_t need) {
+    t += std::max<int64_t>(0, need - (b && !fresh ? (int64_t)b->n : 0));
+  });
   return t;
 }
+
+// what chunk_poses may fill
+int64_t scratch_avail(const cf_ctx *c) { return c->budget - c->weight_bytes - ((int64_t)64 << 20); }
 
 // Poses per launch: at most 512, such that everything the call allocates (conv
 // tensors of the chunk and, with atom stages, the per-atom scratch of at most
 // n_atoms atoms) fits the context's HBM budget next to what it already holds.
-int chunk_poses(const cf_ctx *c, int G, int P, int64_t n_atoms = 0) {
-  const int64_t avail = c->budget - c->weight_bytes - ((int64_t)64 << 20);
+int chunk_poses(const cf_ctx *c, int G, int P, int64_t n_atoms = 0, bool fresh = false) {
+  const int64_t avail = scratch_avail(c);
   int n = std::min(512, P);
   while (n > 1) {
     const int64_t atoms = n_atoms > 0 ? std::min<int64_t>(n_atoms, (int64_t)n * CF_MAX_POSE_ATOMS) : 0;
-    if (scratch_after(c, G, n, atoms) <= avail) break;
+    if (scratch_after(c, G, n, atoms, fresh) <= avail) break;
     n = n > 64 ? n - 32 : n - 1;
   }
   return n < 1 ? 1 : n;
@@ -1186,30 +1193,34 @@ int cf_backward(cf_ctx *c, const cf_pose_batch *b, int G, const float *dscore, f
     if (off[p + 1] - off[p] < 1 || off[p + 1] - off[p] > CF_MAX_POSE_ATOMS)
       return fail(CF_ERR_INVALID_ARG, "atom_off malformed (each pose needs 1..4096 atoms)");
 
+  // How the work is split follows from the shapes and the budget alone, so that a gradient
+  // has the same bits whatever the context did before: its scratch is counted as if it held
+  // nothing yet.  Only where that does not fit next to what earlier calls left allocated
+  // does the call take less (smaller chunks, fewer partial sums, direct kernels).
   constexpr int kBwChunk = 32;
-  const int chunk = std::min(kBwChunk, chunk_poses(c, G, b->n_poses, b->n_atoms));
+  int chunk = std::min(kBwChunk, chunk_poses(c, G, b->n_poses, b->n_atoms, true));
+  {
+    const int64_t atoms = std::min<int64_t>(b->n_atoms, (int64_t)chunk * CF_MAX_POSE_ATOMS);
+    const int64_t then = scratch_after(c, G, chunk, atoms);
+    if (then > c->scratch_bytes && then > scratch_avail(c))
+      chunk = std::min(chunk, chunk_poses(c, G, b->n_poses, b->n_atoms));
+  }
   int64_t max_atoms = 0;
   for (int p0 = 0; p0 < b->n_poses; p0 += chunk)
     max_atoms = std::max<int64_t>(max_atoms, off[std::min(b->n_poses, p0 + chunk)] - off[p0]);
   const int64_t acap = max_atoms;
-  if ((rc = ensure_act(c, G, chunk))) return rc;
-  if ((rc = ensure_atoms(c, acap, chunk))) return rc;
-  if ((rc = ensure(c, c->centers, (size_t)chunk * 3 * sizeof(int32_t)))) return rc;
-  if ((rc = ensure(c, c->cnn_lat, (size_t)chunk * c->lc * sizeof(float)))) return rc;
-  if ((rc = ensure(c, c->sg_lat, (size_t)chunk * c->sgw * sizeof(float)))) return rc;
-  if ((rc = ensure(c, c->splatwork, (size_t)cf::splat_work_bytes(chunk, acap, G)))) return rc;
   // layer sizes
-  std::vector<int> dims{G};
+  std::vector<int> dims{G}, var;
   for (auto &Lr : c->conv) dims.push_back(conv_out_dim(dims.back(), Lr.k, Lr.stride));
   auto vox = [&](int i) { return (int64_t)dims[i] * dims[i] * dims[i]; };
+  if ((rc = variants_for(c, G, var))) return rc;
+  if ((int)c->act.size() != L) c->act.resize(L);
   if ((int)c->dact.size() != L) c->dact.resize(L);
-  for (int i = 0; i < L; ++i)
-    if ((rc = ensure(c, c->dact[i], (size_t)chunk * vox(i + 1) * c->conv[i].cout_store * sizeof(float)))) return rc;
+  if ((int)c->gspec_t.size() != L) c->gspec_t.resize(L), c->gspec_t_set.assign(L, 0);
   // SG scratch (floats): states H[R+1], messages M[R], gate inputs GI[R], GH[R]
   // (3H each), then per-atom work rows
   const int64_t nH = acap * H, n3 = acap * 3 * H;
   const int64_t sg_floats = (R + 1) * nH + R * nH + 2 * R * n3 + 9 * nH + 2 * n3;
-  if ((rc = ensure(c, c->bw_sg, (size_t)sg_floats * sizeof(float)))) return rc;
   int64_t wq = 0, wt = 0;
   for (int i = 0; i < L; ++i) {
     const auto &Lr = c->conv[i];
@@ -1217,11 +1228,9 @@ int cf_backward(cf_ctx *c, const cf_pose_batch *b, int G, const float *dscore, f
     wq = std::max<int64_t>(wq, (int64_t)Lr.cout * Lr.cin * taps);
     if (i > 0) wt = std::max(wt, cf::bw_fold_wt_floats(Lr.cout, Lr.cin, taps));
   }
-  wq = (wq + 3) / 4 * 4;  // the packed weights after the partials are read 16 bytes at a time
   const int dmax = 256;
   // head: per-pose parameter gradients and the latents' gradients
   const int64_t head_floats = (int64_t)chunk * c->tr.head_n + (int64_t)chunk * (c->lc + H) + 2 * (int64_t)chunk;
-  if ((rc = ensure(c, c->bw_head, (size_t)head_floats * sizeof(float)))) return rc;
   // partial sums of the ordered reductions (the largest any call below needs)
   int64_t part = cf::bw_outer_scratch(chunk, (int)c->tr.head_n, 1);
   part = std::max(part, cf::bw_outer_scratch((int)acap, 3 * H, H));
@@ -1229,42 +1238,61 @@ int cf_backward(cf_ctx *c, const cf_pose_batch *b, int G, const float *dscore, f
   part = std::max(part, cf::bw_outer_scratch(chunk, (int)wq, 1));
   part = std::max(part, cf::bw_outer_scratch(chunk, dmax, dmax));
   for (int i = 0; i < L; ++i) part = std::max(part, cf::bw_outer_scratch((int)(chunk * vox(i + 1)), c->conv[i].cout, 1));
-  if ((rc = ensure(c, c->bw_part, (size_t)part * sizeof(float)))) return rc;
-  // CNN scratch: weight-gradient partials (one per pose, or several when few poses would
-  // leave the chip idle and the budget has room), their sum, folded weights packed for the
-  // data gradient, bias gradient; pool / dense rows
-  const int64_t cnn_rest = wq + wt + 256 + 8 * (int64_t)chunk * dmax;
-  int nparts = chunk;
-  if (nparts < 8 && c->scratch_bytes - (int64_t)c->bw_cnn.n + c->weight_bytes +
-                            (8 * wq + cnn_rest) * (int64_t)sizeof(float) <= c->budget)
-    nparts = 8;
-  if ((rc = ensure(c, c->bw_cnn, (size_t)(nparts * wq + cnn_rest) * sizeof(float)))) return rc;
-
-  // stride-1 layers in the frequency domain: weight spectra of the data gradient, the
-  // weight gradient's spectrum and the plane spectra, where they leave half the budget free
-  // (later calls of this context keep their room); the direct kernels otherwise
-  std::vector<char> spectral(L, 0);
-  {
-    int64_t keep = 0, sum = 0, work = 0;
-    auto more = [](const DevBuf &b, int64_t need) { return std::max<int64_t>(0, need - (int64_t)b.n); };
-    if ((int)c->gspec_t.size() != L) c->gspec_t.resize(L), c->gspec_t_set.assign(L, 0);
+  // CNN scratch: weight-gradient partials and their sum -- once a layer's are folded, its
+  // weights packed for the data gradient lie in their place --, bias gradient; pool / dense rows
+  auto cnn_floats = [&](int parts) { return std::max((parts + 1) * wq, wt) + 256 + 8 * (int64_t)chunk * dmax; };
+  // everything the call needs with `parts` partials and these layers in the frequency domain
+  // (weight spectra of their data gradients, the weight gradient's spectrum, plane spectra)
+  typedef std::vector<std::pair<DevBuf *, int64_t>> Needs;
+  auto needs = [&](int parts, const std::vector<char> &fft) {
+    Needs v;
+    forward_needs(c, G, chunk, acap, [&](const DevBuf *buf, int64_t n) {
+      if (buf != &c->convwork) v.push_back({const_cast<DevBuf *>(buf), n});
+    });
+    int64_t sum = 0, work = 0;
     for (int i = 0; i < L; ++i) {
       const auto &Lr = c->conv[i];
-      if (!cf::fft_grad_ok(Lr, dims[i], chunk)) continue;
-      const int64_t g = i > 0 ? more(c->gspec_t[i], cf::fft_grad_layer(Lr).gspec_bytes) : 0;
-      const int64_t sm = std::max(sum, cf::fft_grad_sum_bytes(Lr)), wk = std::max(work, cf::fft_grad_work_bytes(Lr, dims[i], chunk));
-      if (2 * (c->scratch_bytes + c->weight_bytes + keep + g + more(c->bw_sum, sm) + more(c->convwork, wk)) > c->budget)
-        continue;
-      keep += g;
-      sum = sm;
-      work = wk;
-      spectral[i] = 1;
+      work = std::max(work, cf::conv_work_bytes(var[i], Lr, dims[i], chunk));
+      v.push_back({&c->dact[i], chunk * vox(i + 1) * Lr.cout_store * (int64_t)sizeof(float)});
+      if (!fft[i]) continue;
+      sum = std::max(sum, cf::fft_grad_sum_bytes(Lr));
+      work = std::max(work, cf::fft_grad_work_bytes(Lr, dims[i], chunk));
+      if (i > 0) v.push_back({&c->gspec_t[i], cf::fft_grad_layer(Lr).gspec_bytes});
     }
-    if (sum && (rc = ensure(c, c->bw_sum, (size_t)sum))) return rc;
-    if (work && (rc = ensure(c, c->convwork, (size_t)work))) return rc;
-    for (int i = 1; i < L; ++i)
-      if (spectral[i] && (rc = ensure(c, c->gspec_t[i], (size_t)cf::fft_grad_layer(c->conv[i]).gspec_bytes))) return rc;
+    v.push_back({&c->convwork, work});
+    v.push_back({&c->bw_sum, sum});
+    v.push_back({&c->bw_sg, sg_floats * (int64_t)sizeof(float)});
+    v.push_back({&c->bw_head, head_floats * (int64_t)sizeof(float)});
+    v.push_back({&c->bw_part, part * (int64_t)sizeof(float)});
+    v.push_back({&c->bw_cnn, cnn_floats(parts) * (int64_t)sizeof(float)});
+    return v;
+  };
+  auto alone = [&](const Needs &v) {  // the call in a context that holds nothing else
+    int64_t t = c->weight_bytes;
+    for (auto &n : v) t += n.second;
+    return t;
+  };
+  auto beside = [&](const Needs &v) {  // the call beside what the context holds
+    int64_t t = c->weight_bytes + c->scratch_bytes;
+    for (auto &n : v) t += std::max<int64_t>(0, n.second - (int64_t)n.first->n);
+    return t;
+  };
+  // one partial per pose, or several when few poses would leave the chip idle; stride-1
+  // layers in the frequency domain while half of the budget stays free (later calls of this
+  // context keep their room)
+  std::vector<char> spectral(L, 0);
+  int nparts = chunk;
+  if (chunk < 8 && alone(needs(8, spectral)) <= c->budget) nparts = 8;
+  for (int i = 0; i < L; ++i) {
+    if (!cf::fft_grad_ok(c->conv[i], dims[i], chunk)) continue;
+    spectral[i] = 1;
+    if (2 * alone(needs(nparts, spectral)) > c->budget) spectral[i] = 0;
   }
+  if (beside(needs(nparts, spectral)) > c->budget) nparts = chunk;
+  for (int i = L - 1; i >= 0; --i)
+    if (spectral[i] && beside(needs(nparts, spectral)) > c->budget) spectral[i] = 0;
+  for (auto &n : needs(nparts, spectral))
+    if (n.second && (rc = ensure(c, *n.first, (size_t)n.second))) return rc;
 
   const float *P = c->raw;
   const TrainOffsets &T = c->tr;
@@ -1344,7 +1372,9 @@ int cf_backward(cf_ctx *c, const cf_pose_batch *b, int G, const float *dscore, f
     CF_HIP(cf::bw_outer(dH, H, x, CF_NCH, n, H, CF_NCH, grad + T.embed_w, CF_NCH, 1, pt, s));
     CF_HIP(cf::bw_outer(dH, H, nullptr, 0, n, H, 1, grad + T.embed_b, 1, 1, pt, s));
     // ---- 3D-CNN backward ----
-    float *part = (float *)c->bw_cnn.p, *dWf = part + (int64_t)nparts * wq, *WT = dWf + wq, *dbf = WT + wt;
+    // WT takes the place of the partials and of dWf once both are read
+    float *part = (float *)c->bw_cnn.p, *dWf = part + (int64_t)nparts * wq, *WT = part;
+    float *dbf = part + std::max((nparts + 1) * wq, wt);
     float *pool = dbf + 256, *pre1 = pool + (int64_t)chunk * dmax, *lat1 = pre1 + (int64_t)chunk * dmax;
     float *pre2 = lat1 + (int64_t)chunk * dmax, *dl2 = pre2 + (int64_t)chunk * dmax, *dl1 = dl2 + (int64_t)chunk * dmax;
     float *dpool = dl1 + (int64_t)chunk * dmax;
