@@ -170,64 +170,6 @@ __device__ inline void dc_nyquist_split(const float2 *Zp, void *O, int tid) {
 // fused transform, five workgroups per CU; 153 with one transform per lane).  Lane h = tid & 1 of a pair, partner tid ^ 1 (a quad
 // permutation, so the exchange is a DPP operand).
 
-// (r, i) times e^{-+2 pi i t / 32}, t = 0 .. 15 (NEG: times minus that), in place.  Which
-// product of each part is rounded by itself is written out: left to the compiler, it
-// depends on the code around the transform.
-template <bool INV, bool NEG = false>
-__device__ inline void lane_twiddle(float &r, float &i, int t) {
-  const float c = NEG ? -kFftCos32[t] : kFftCos32[t], s = NEG ? -kFftSin32[t] : kFftSin32[t];
-  if (t == 0) {
-    r *= c;
-    i *= c;
-  } else if (t == 8) {
-    const float is = INV ? i * -s : i * s;
-    i = INV ? r * s : r * -s;
-    r = is;
-  } else if (INV) {
-    const float is = i * -s, ic = i * c;
-    i = __builtin_fmaf(r, s, ic);
-    r = __builtin_fmaf(r, c, is);
-  } else if (NEG && t < 8 && t != 4) {
-    const float is = i * s, rs = r * -s;
-    i = __builtin_fmaf(i, c, rs);
-    r = __builtin_fmaf(r, c, is);
-  } else {
-    const float rs = r * -s, rc = r * c;
-    r = __builtin_fmaf(i, s, rc);
-    i = __builtin_fmaf(i, c, rs);
-  }
-}
-
-// fft16 with those multiplications
-template <bool INV>
-__device__ inline void lane_fft16(float (&re)[16], float (&im)[16]) {
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int j = ((i & 1) << 3) | ((i & 2) << 1) | ((i & 4) >> 1) | ((i & 8) >> 3);
-    if (j > i) {
-      const float tr = re[i], ti = im[i];
-      re[i] = re[j];
-      im[i] = im[j];
-      re[j] = tr;
-      im[j] = ti;
-    }
-  }
-#pragma unroll
-  for (int half = 1; half < 16; half <<= 1) {
-#pragma unroll
-    for (int a = 0; a < 16; ++a) {
-      if (a & half) continue;
-      const int b = a + half;
-      float br = re[b], bi = im[b];
-      lane_twiddle<INV>(br, bi, (a & (half - 1)) * (16 / half));
-      re[b] = re[a] - br;
-      im[b] = im[a] - bi;
-      re[a] = re[a] + br;
-      im[a] = im[a] + bi;
-    }
-  }
-}
-
 // v[k] += s * (the value of v[k] in the neighbouring lane, lane ^ 1), k = 0 .. 15: a
 // multiply-add that reads the other lane by itself (the compiler makes a move and a
 // multiply-add of it).  A lane reads registers that the instructions before have
@@ -244,33 +186,13 @@ __device__ inline void pair_fma(float (&v)[16], float s) {
 #undef CF_PAIR_FMA
 }
 
-// fft32_pair_dit and fft32_pair_dif on two neighbouring lanes.  The half h = 1 is held
-// negated across the exchange (by its twiddles, which is exact), so both lanes combine as
-// mine + s * theirs with a sign s = +-1 per lane, in place of an add, a subtract, a
-// select and a move for each value.
-template <bool INV>
-__device__ inline void fft32_lanes_dit(float (&re)[16], float (&im)[16], int h) {
-  lane_fft16<INV>(re, im);
-  if (h) {
-#pragma unroll
-    for (int k = 0; k < 16; ++k) lane_twiddle<INV, true>(re[k], im[k], k);
+// the exchange of fft32_lanes_dit / _dif between neighbouring lanes
+struct LanePair {
+  __device__ inline void operator()(float (&re)[16], float (&im)[16], float s) const {
+    pair_fma(re, s);
+    pair_fma(im, s);
   }
-  const float s = h ? 1.0f : -1.0f;
-  pair_fma(re, s);
-  pair_fma(im, s);
-}
-
-template <bool INV>
-__device__ inline void fft32_lanes_dif(float (&re)[16], float (&im)[16], int h) {
-  const float s = h ? -1.0f : 1.0f;
-  pair_fma(re, s);
-  pair_fma(im, s);
-  if (h) {
-#pragma unroll
-    for (int n = 0; n < 16; ++n) lane_twiddle<INV, true>(re[n], im[n], n);
-  }
-  lane_fft16<INV>(re, im);
-}
+};
 
 // Calls in(n) for the n = 0 .. 15 with 16 h + n < D and out(n) for the others, with one
 // branch on the lane's half where D is a constant (a test per n costs a mask, a branch
@@ -483,7 +405,7 @@ __global__ __launch_bounds__(256) void k_fft_fwd2d_t(const void *__restrict__ in
     by_window<TS, P>(h, plane + wy * 8 + c0, WP * 8, [&](int n, const act_t *v) { two_channels(v, re[n], im[n]); });
     __syncthreads();  // the plane is in registers; its LDS becomes the row spectra
     if (roww) {
-      fft32_lanes_dif<false>(re, im, h);
+      fft32_lanes_dif<false>(re, im, h, LanePair{});
       row_fwd_store2(T, wy, c0, h, W, re, im);
     }
   }
@@ -497,7 +419,7 @@ __global__ __launch_bounds__(256) void k_fft_fwd2d_t(const void *__restrict__ in
     re[n] = v->x;
     im[n] = v->y;
   });
-  fft32_lanes_dif<false>(re, im, h);
+  fft32_lanes_dif<false>(re, im, h, LanePair{});
   __syncthreads();
   act_t *O = reinterpret_cast<act_t *>(T);  // [col][re | im][8]
   float2 *Zp = reinterpret_cast<float2 *>(dyn_lds + plane_lds_bytes(W, F32));
@@ -571,7 +493,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(F32 || RES 
     col_inv_load2<F32>(Y, kxp, c, h, re, im);
     __syncthreads();
     if (!kxp) col_inv_load_dc2(Zp, c, h, re, im);
-    fft32_lanes_dit<true>(re, im, h);
+    fft32_lanes_dit<true>(re, im, h, LanePair{});
     col_inv_store2<DT>(T, kxp, c, h, D, re, im);
   }
   __syncthreads();
@@ -583,7 +505,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(F32 || RES 
     float re[16], im[16];
     if (roww) {
       row_inv_load2(T, y, c0, h, D, re, im);
-      fft32_lanes_dit<true>(re, im, h);
+      fft32_lanes_dit<true>(re, im, h, LanePair{});
       constexpr float kScale = 1.0f / (kN * kN);
       const float b0 = bias[chunk * 8 + c0], b1 = bias[chunk * 8 + c0 + 1];
       by_half<DT>(
@@ -615,7 +537,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(F32 || RES 
             }
           },
           [&](int j) { re[j] = im[j] = 0.0f; });
-      fft32_lanes_dif<false>(re, im, h);
+      fft32_lanes_dif<false>(re, im, h, LanePair{});
       // no barrier between reading and rewriting T: each lane reads the row spectra
       // at the frequencies of its own parity (the mirror 32 - k has the same parity)
       // and writes back exactly those slots; the partner's values came by DPP
@@ -631,7 +553,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(F32 || RES 
   // forward columns along y
   float re[16], im[16];
   col_fwd_load2<DT>(T, kxp, c, h, D, re, im);
-  fft32_lanes_dif<false>(re, im, h);
+  fft32_lanes_dif<false>(re, im, h, LanePair{});
   __syncthreads();
   act_t *O = reinterpret_cast<act_t *>(T);
   col_fwd_store2<F32>(O, Zp, kxp, c, h, re, im);
@@ -706,7 +628,7 @@ __global__ __launch_bounds__(256) void k_fft_fwd2d(const void *__restrict__ in_v
     by_half<DT>(h, D, [&](int n) { two_channels(v + n * DP * 8, re[n], im[n]); }, [](int) {});
     __syncthreads();  // the plane is in registers; its LDS becomes the row spectra
     if (roww) {
-      fft32_lanes_dif<false>(re, im, h);
+      fft32_lanes_dif<false>(re, im, h, LanePair{});
       row_fwd_store2(T, y, c0, h, D, re, im);
     }
   }
@@ -715,7 +637,7 @@ __global__ __launch_bounds__(256) void k_fft_fwd2d(const void *__restrict__ in_v
   const int kxp = q >> 3, c = q & 7;
   float re[16], im[16];
   col_fwd_load2<DT>(T, kxp, c, h, D, re, im);
-  fft32_lanes_dif<false>(re, im, h);
+  fft32_lanes_dif<false>(re, im, h, LanePair{});
   __syncthreads();
   act_t *O = reinterpret_cast<act_t *>(T);  // [col][re | im][8]
   col_fwd_store2<F32>(O, Zp, kxp, c, h, re, im);
@@ -766,7 +688,7 @@ __global__ __launch_bounds__(256) void k_fft_inv2d(const void *__restrict__ ys_v
     col_inv_load2<F32>(Y, kxp, c, h, re, im);
     __syncthreads();
     if (!kxp) col_inv_load_dc2(Zp, c, h, re, im);
-    fft32_lanes_dit<true>(re, im, h);
+    fft32_lanes_dit<true>(re, im, h, LanePair{});
     col_inv_store2<DT>(T, kxp, c, h, D, re, im);
   }
   __syncthreads();
@@ -775,7 +697,7 @@ __global__ __launch_bounds__(256) void k_fft_inv2d(const void *__restrict__ ys_v
   float re[16], im[16];
   if (roww) {
     row_inv_load2(T, y, c0, h, D, re, im);
-    fft32_lanes_dit<true>(re, im, h);
+    fft32_lanes_dit<true>(re, im, h, LanePair{});
   }
   __syncthreads();  // the row spectra are read; T becomes the output plane
   float *O = reinterpret_cast<float *>(T);  // [x][y (pitch D + 1)][8] conv result + bias
