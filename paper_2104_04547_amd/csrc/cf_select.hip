@@ -63,18 +63,21 @@ __global__ __launch_bounds__(kSelThreads) void k_segmax(const float *__restrict_
   }
   float m = -FLT_MAX;
   int idx = -1;
-  for (int p0 = a; p0 < b; p0 += 4 * LPS) {
+  // counted from the segment's start, unsigned: past the end of one that ends near 2^31 too
+  const uint32_t len = (uint32_t)(b - a);
+  const float *seg = scores + a;
+  for (uint32_t d = 0; d < len; d += 4 * LPS) {
     float v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int p = p0 + u * LPS + q;
-      v[u] = p < b ? scores[p] : __builtin_nanf("");
+      const uint32_t p = d + u * LPS + q;
+      v[u] = p < len ? seg[p] : __builtin_nanf("");
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u)
       if (v[u] == v[u] && (idx < 0 || v[u] > m)) {
         m = v[u];
-        idx = p0 + u * LPS + q;
+        idx = (int)(d + u * LPS + q);
       }
   }
 #pragma unroll
@@ -88,7 +91,7 @@ __global__ __launch_bounds__(kSelThreads) void k_segmax(const float *__restrict_
   }
   if (q == 0) {
     best[c] = idx < 0 ? -INFINITY : m;
-    best_idx[c] = idx;
+    best_idx[c] = idx < 0 ? -1 : a + idx;
   }
 }
 
