@@ -53,45 +53,47 @@ __global__ __launch_bounds__(kSelThreads) void k_segmax(const float *__restrict_
                                                         const int32_t *__restrict__ off, int n_seg,
                                                         float *__restrict__ best, int32_t *__restrict__ best_idx,
                                                         int64_t *status) {
-  const int64_t t = blockIdx.x * (int64_t)kSelThreads + threadIdx.x;
-  const int c = (int)(t / LPS), q = (int)(t % LPS);
-  if (c >= n_seg) return;  // whole groups
-  int a = off[c], b = off[c + 1];
-  if (a < 0 || b < a || b > n_scores) {
-    if (q == 0) dev_fail(status, kDevBadOffsets);
-    a = b = 0;
-  }
-  float m = -FLT_MAX;
-  int idx = -1;
-  // counted from the segment's start, unsigned: past the end of one that ends near 2^31 too
-  const uint32_t len = (uint32_t)(b - a);
-  const float *seg = scores + a;
-  for (uint32_t d = 0; d < len; d += 4 * LPS) {
-    float v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const uint32_t p = d + u * LPS + q;
-      v[u] = p < len ? seg[p] : __builtin_nanf("");
+  const int q = threadIdx.x % LPS;
+  const int64_t t = (blockIdx.x * (int64_t)kSelThreads + threadIdx.x) / LPS, step = (int64_t)gridDim.x * kSelThreads / LPS;
+  for (int64_t seg_id = t; seg_id < n_seg; seg_id += step) {  // whole groups
+    const int c = (int)seg_id;
+    int a = off[c], b = off[c + 1];
+    if (a < 0 || b < a || b > n_scores) {
+      if (q == 0) dev_fail(status, kDevBadOffsets);
+      a = b = 0;
     }
+    float m = -FLT_MAX;
+    int idx = -1;
+    // counted from the segment's start, unsigned: past the end of one that ends near 2^31 too
+    const uint32_t len = (uint32_t)(b - a);
+    const float *seg = scores + a;
+    for (uint32_t d = 0; d < len; d += 4 * LPS) {
+      float v[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (v[u] == v[u] && (idx < 0 || v[u] > m)) {
-        m = v[u];
-        idx = (int)(d + u * LPS + q);
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t p = d + u * LPS + q;
+        v[u] = p < len ? seg[p] : __builtin_nanf("");
       }
-  }
 #pragma unroll
-  for (int o = LPS / 2; o >= 1; o >>= 1) {
-    const float mo = __shfl_xor(m, o, LPS);
-    const int io = __shfl_xor(idx, o, LPS);
-    if (io >= 0 && (idx < 0 || mo > m || (mo == m && io < idx))) {
-      m = mo;
-      idx = io;
+      for (int u = 0; u < 4; ++u)
+        if (v[u] == v[u] && (idx < 0 || v[u] > m)) {
+          m = v[u];
+          idx = (int)(d + u * LPS + q);
+        }
     }
-  }
-  if (q == 0) {
-    best[c] = idx < 0 ? -INFINITY : m;
-    best_idx[c] = idx < 0 ? -1 : a + idx;
+#pragma unroll
+    for (int o = LPS / 2; o >= 1; o >>= 1) {
+      const float mo = __shfl_xor(m, o, LPS);
+      const int io = __shfl_xor(idx, o, LPS);
+      if (io >= 0 && (idx < 0 || mo > m || (mo == m && io < idx))) {
+        m = mo;
+        idx = io;
+      }
+    }
+    if (q == 0) {
+      best[c] = idx < 0 ? -INFINITY : m;
+      best_idx[c] = idx < 0 ? -1 : a + idx;
+    }
   }
 }
 
@@ -396,13 +398,16 @@ __global__ __launch_bounds__(1024) void k_topk_sort(const uint64_t *cand, int k,
 hipError_t launch_segmax(const float *scores, int n_scores, const int32_t *off, int n_seg, float *best,
                          int32_t *best_idx, int64_t *status, hipStream_t s) {
   if (n_seg <= 0) return hipSuccess;
-  // 8 lanes per segment (a compound has up to 40 poses), a wave where segments are long
-  if ((int64_t)n_scores > 128 * (int64_t)n_seg)
-    hipLaunchKernelGGL(k_segmax<64>, dim3((unsigned)(((int64_t)n_seg * 64 + kSelThreads - 1) / kSelThreads)),
-                       dim3(kSelThreads), 0, s, scores, n_scores, off, n_seg, best, best_idx, status);
+  // 8 lanes per segment (a compound has up to 40 poses), a wave where segments are long; a
+  // launch has fewer than 2^32 threads, so the workgroups of more segments take several
+  const int lps = (int64_t)n_scores > 128 * (int64_t)n_seg ? 64 : 8;
+  const unsigned blocks = (unsigned)std::min<int64_t>(((int64_t)n_seg * lps + kSelThreads - 1) / kSelThreads, 1 << 22);
+  if (lps == 64)
+    hipLaunchKernelGGL(k_segmax<64>, dim3(blocks), dim3(kSelThreads), 0, s, scores, n_scores, off, n_seg, best, best_idx,
+                       status);
   else
-    hipLaunchKernelGGL(k_segmax<8>, dim3((unsigned)(((int64_t)n_seg * 8 + kSelThreads - 1) / kSelThreads)),
-                       dim3(kSelThreads), 0, s, scores, n_scores, off, n_seg, best, best_idx, status);
+    hipLaunchKernelGGL(k_segmax<8>, dim3(blocks), dim3(kSelThreads), 0, s, scores, n_scores, off, n_seg, best, best_idx,
+                       status);
   return hipGetLastError();
 }
 

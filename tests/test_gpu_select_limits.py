@@ -1,5 +1,5 @@
 """Segment maxima at the ends of the int32 ranges: segments that end at the last of 2^31 - 1
-scores (8 and 64 lanes per segment)."""
+scores (8 and 64 lanes per segment), and more segments than a launch has groups of threads."""
 import numpy as np
 import pytest
 
@@ -32,4 +32,21 @@ def test_segments_at_the_end_of_the_index_range(n_seg):
         assert idx[k].item() == LAST - 300 + a + int(np.argmax(tail[a:b]))
         assert best[k].item() == tail[a:b].max()
     assert (idx[:n_seg - 2] == -1).all().item() and torch.isinf(best[:n_seg - 2]).all().item()
+    s.close()
+
+
+def test_more_segments_than_one_launch_has_threads_for():
+    import torch
+    n = 2 ** 29 + 3       # 8 lanes each: 2^32 threads and 24
+    print(f"\n[gpu-case] cf_compound_max {n} segments", flush=True)
+    s = _scorer()
+    off = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    off[n // 2:] = 2
+    off[n - 1], off[n] = 3, 8
+    scores = torch.tensor([1.0, -2.0, 0.5, 7.0, 9.0, 9.0, -1.0, 4.0], device="cuda")
+    best, idx = s.compound_max(scores, off)
+    s.check()
+    assert [idx[k].item() for k in (0, n // 2 - 1, n // 2, n - 2, n - 1)] == [-1, 0, -1, 2, 4]
+    assert [best[k].item() for k in (n // 2 - 1, n - 2, n - 1)] == [1.0, 0.5, 9.0]
+    assert int((idx >= 0).sum()) == 3
     s.close()
