@@ -32,9 +32,8 @@
 // squares is exact where it decides (all axes <= r) and above r^2 where an axis was
 // clamped.  For 3 C^2 < 2^32 (r <= 37836 u, 36.9 A) it takes 24-bit multiplies and
 // 32-bit sums, above that 64-bit ones.
-#include <algorithm>
-
 #include "cf_internal.h"
+#include "cf_launch.h"
 
 namespace cf {
 
@@ -444,7 +443,7 @@ hipError_t launch_graph(const int32_t *atom_off, int n_atoms, const int32_t *xyz
   // items per pose: blocks for poses up to twice the mean (larger ones loop), never
   // more than the largest pose has
   const int nbx = pose_blocks(n_atoms, mean_atoms, kRows);
-  const dim3 grid((unsigned)std::min<int64_t>((int64_t)n_poses * nbx, 1 << 20));
+  const dim3 grid(item_groups((int64_t)n_poses * nbx));
   const bool small = r_nc <= kR32;
   if (small)
     hipLaunchKernelGGL(k_graph_count<true>, grid, dim3(kThreads), 0, s, atom_off, n_atoms, xyz, p0, n_poses, nbx, r_cov,

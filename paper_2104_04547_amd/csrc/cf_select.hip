@@ -28,6 +28,7 @@
 #include <mutex>
 
 #include "cf_internal.h"
+#include "cf_launch.h"
 #include "cf_topk_pick.h"
 
 namespace cf {
@@ -401,7 +402,7 @@ hipError_t launch_segmax(const float *scores, int n_scores, const int32_t *off, 
   // 8 lanes per segment (a compound has up to 40 poses), a wave where segments are long; a
   // launch has fewer than 2^32 threads, so the workgroups of more segments take several
   const int lps = (int64_t)n_scores > 128 * (int64_t)n_seg ? 64 : 8;
-  const unsigned blocks = (unsigned)std::min<int64_t>(((int64_t)n_seg * lps + kSelThreads - 1) / kSelThreads, 1 << 22);
+  const unsigned blocks = item_groups(((int64_t)n_seg * lps + kSelThreads - 1) / kSelThreads);
   if (lps == 64)
     hipLaunchKernelGGL(k_segmax<64>, dim3(blocks), dim3(kSelThreads), 0, s, scores, n_scores, off, n_seg, best, best_idx,
                        status);

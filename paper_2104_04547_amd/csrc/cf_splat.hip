@@ -27,6 +27,7 @@
 // Results are bitwise independent of launch shape, list order and atom
 // scheduling, so a 90 degree rotation of a pose permutes its grid exactly.
 #include "cf_internal.h"
+#include "cf_launch.h"
 
 namespace cf {
 
@@ -132,19 +133,20 @@ constexpr int kMaxTilesPerAtom = tiles_spanned(kTA) * tiles_spanned(kTB);
 
 constexpr int kNormRows = kBinThreads / 4;   // atoms per workgroup of the normaliser part
 
-// Workgroups past the first n_poses: Zs[a - base] = the normaliser of atom a.  Every w >=
-// exp(-4.5) > 2^-7 is an exact multiple of 2^-31, so w * 2^40 is an exact integer and the
-// integer sum is the exact sum of the float weights, in any order.
+// Workgroups past the first n_poses, an item (pose, first block b0) at a time: Zs[a - base] =
+// the normaliser of atom a.  Every w >= exp(-4.5) > 2^-7 is an exact multiple of 2^-31, so
+// w * 2^40 is an exact integer and the integer sum is the exact sum of the float weights,
+// in any order.
 __device__ void splat_norm(const int32_t *__restrict__ atom_off, int n_atoms, const int32_t *__restrict__ xyz,
-                           const int32_t *__restrict__ centers, int p0, int item, int nbx, int G, int64_t atoms_cap,
-                           double *__restrict__ Zs) {
-  const int pl = item / nbx, tid = threadIdx.x;
+                           const int32_t *__restrict__ centers, int p0, int pl, int b0, int nbx, int G,
+                           int64_t atoms_cap, double *__restrict__ Zs) {
+  const int tid = threadIdx.x;
   int a0, a1;
   pose_range(atom_off, p0 + pl, n_atoms, a0, a1);
   const int base = min(max(atom_off[p0], 0), n_atoms);
   if (a0 < base || (int64_t)a1 - base > atoms_cap) return;
   const int64_t c0 = centers[3 * pl], c1 = centers[3 * pl + 1], c2 = centers[3 * pl + 2];
-  for (int r0 = (item % nbx) * kNormRows; r0 < a1 - a0; r0 += nbx * kNormRows) {
+  for (int r0 = b0 * kNormRows; r0 < a1 - a0; r0 += nbx * kNormRows) {
     const int a = a0 + r0 + (tid >> 2);
     const bool live = a < a1;
     const AtomBox b = atom_box(xyz, live ? a : a0, c0, c1, c2, G);
@@ -171,7 +173,8 @@ __global__ __launch_bounds__(kBinThreads) void k_splat_bin(const int32_t *__rest
                                                           int32_t *__restrict__ bin_off,
                                                           int32_t *__restrict__ bin_atoms) {
   if ((int)blockIdx.x >= n_poses) {
-    splat_norm(atom_off, n_atoms, xyz, centers, p0, blockIdx.x - n_poses, nbx, G, atoms_cap, Zs);
+    for (int64_t item = (int)blockIdx.x - n_poses; item < (int64_t)n_poses * nbx; item += (int)gridDim.x - n_poses)
+      splat_norm(atom_off, n_atoms, xyz, centers, p0, (int)(item / nbx), (int)(item % nbx), nbx, G, atoms_cap, Zs);
     return;
   }
   __shared__ int cnt[kMaxTiles];
@@ -506,7 +509,7 @@ hipError_t launch_splat(const int32_t *atom_off, int n_atoms, const int32_t *xyz
   int32_t *bin_off = reinterpret_cast<int32_t *>(Zs + atoms_cap);
   int32_t *bin_atoms = bin_off + (int64_t)n_poses * (ntiles + 1);
   const int nbx = pose_blocks(n_atoms, mean_atoms, kNormRows);
-  hipLaunchKernelGGL(k_splat_bin, dim3((unsigned)n_poses * (1 + nbx)), dim3(kBinThreads), 0, s, atom_off, n_atoms, xyz,
+  hipLaunchKernelGGL(k_splat_bin, dim3((unsigned)n_poses + item_groups((int64_t)n_poses * nbx)), dim3(kBinThreads), 0, s, atom_off, n_atoms, xyz,
                      centers, p0, n_poses, nbx, G, atoms_cap, Zs, bin_off, bin_atoms);
   // a caller's grid need not be aligned to the wide stores
   const bool wide = reinterpret_cast<uintptr_t>(grid) % (out_mode == 0 ? 16 : 8) == 0;
