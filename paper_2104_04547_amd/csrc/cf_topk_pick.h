@@ -6,7 +6,7 @@
 namespace cf {
 
 // Select state: [0] prefix, [1] mask of decided bits, [2] k remaining, [3] collected count,
-// [4] workgroups done with the pass, [5] 1 when the prefix already cuts off exactly k keys.
+// [5] 1 when the prefix already cuts off exactly k keys ([4] is free).
 //
 // One thread per digit: `own` keys under the prefix have it, `at` have it or a larger one.
 // The one thread whose digit holds the k-th largest key writes the state.  prefix, mask and
@@ -20,7 +20,6 @@ __host__ __device__ inline void topk_pick(uint64_t prefix, uint64_t mask, uint64
     state[0] = prefix | (uint64_t)digit << shift;
     state[1] = mask | (uint64_t)0xFF << shift;
     state[2] = krem - above;
-    state[4] = 0;
     state[5] = krem - above == own ? 1 : 0;  // the whole bucket: no key below it has to be told apart
   }
 }
