@@ -198,13 +198,15 @@ __device__ inline void sweep(GraphShared &S, const int32_t *__restrict__ xyz, in
 }
 
 // Pass 1: degrees.  Work items (pose, block) in a grid-stride loop; a pose of more
-// than nbx blocks gives each of its items several.
-template <bool R32>
+// than nbx blocks gives each of its items several.  WHOLE (nbx = 1): an item is a whole pose
+// and writes its edge totals too.
+template <bool R32, bool WHOLE>
 __global__ __launch_bounds__(kThreads) void k_graph_count(const int32_t *__restrict__ atom_off, int n_atoms,
                                                           const int32_t *__restrict__ xyz, int p0, int n_poses,
                                                           int nbx, int r_cov, int r_nc,
                                                           int32_t *__restrict__ deg,  // [2][n_chunk_cap]
-                                                          int64_t n_chunk_cap, int64_t *status) {
+                                                          int64_t n_chunk_cap, int64_t *__restrict__ pose_tot,
+                                                          int64_t *status) {
   __shared__ GraphShared S;
   const int base = atom_off[p0];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -212,6 +214,7 @@ __global__ __launch_bounds__(kThreads) void k_graph_count(const int32_t *__restr
     const int pl = (int)(it / nbx), b0 = (int)(it % nbx);
     int a0;
     const int n = item_pose(atom_off, n_atoms, p0, pl, base, b0 == 0 && threadIdx.x == 0, a0, status);
+    long long tot = 0;  // edges of this lane's atoms, by waves 0 and 1
     for (int i0 = b0 * kRows; i0 < n; i0 += nbx * kRows) {
       const int i = i0 + lane;
       const uint4 me = atom_pos(xyz, (int64_t)a0 + (i < n ? i : i0));
@@ -234,7 +237,12 @@ __global__ __launch_bounds__(kThreads) void k_graph_count(const int32_t *__restr
         int d = 0;
         for (int w = 0; w < kParts; ++w) d += S.cnt[wave][w][lane];
         deg[wave * n_chunk_cap + li] = d;
+        if constexpr (WHOLE) tot += d;
       }
+    }
+    if (WHOLE && wave < 2) {
+      for (int o = 32; o >= 1; o >>= 1) tot += __shfl_xor(tot, o, 64);
+      if (lane == 0) pose_tot[(int64_t)wave * n_poses + pl] = tot;
     }
   }
 }
@@ -445,19 +453,27 @@ hipError_t launch_graph(const int32_t *atom_off, int n_atoms, const int32_t *xyz
   const int nbx = pose_blocks(n_atoms, mean_atoms, kRows);
   const dim3 grid(item_groups((int64_t)n_poses * nbx));
   const bool small = r_nc <= kR32;
-  if (small)
-    hipLaunchKernelGGL(k_graph_count<true>, grid, dim3(kThreads), 0, s, atom_off, n_atoms, xyz, p0, n_poses, nbx, r_cov,
-                       r_nc, deg_scratch, n_chunk_cap, status);
-  else
-    hipLaunchKernelGGL(k_graph_count<false>, grid, dim3(kThreads), 0, s, atom_off, n_atoms, xyz, p0, n_poses, nbx, r_cov,
-                       r_nc, deg_scratch, n_chunk_cap, status);
-  // totals inside the scan's 16 waves while that is at most two poses a wave
-  if (n_poses <= 32) {
+  const bool whole = nbx == 1;  // poses of one block each: totals with the degrees
+#define CF_COUNT(R32, WHOLE)                                                                                        \
+  hipLaunchKernelGGL((k_graph_count<R32, WHOLE>), grid, dim3(kThreads), 0, s, atom_off, n_atoms, xyz, p0, n_poses, nbx, \
+                     r_cov, r_nc, deg_scratch, n_chunk_cap, pose_scratch, status)
+  if (small) {
+    if (whole) CF_COUNT(true, true); else CF_COUNT(true, false);
+  } else {
+    if (whole) CF_COUNT(false, true); else CF_COUNT(false, false);
+  }
+#undef CF_COUNT
+  // Totals of larger poses: inside the scan's 16 waves while that is at most two poses a wave,
+  // else a launch of their own.  Inside and apart, for ragged poses of 200-1500 atoms: one pose
+  // 22.4 and 23.4 us for the whole build, 16 poses 35.5 and 36.6, 19 poses 64.3 and 64.8, 32
+  // poses 70.3 and 69.1.  (300 poses of 12 atoms: 21.9 us apart, 18.7 with the degrees.)
+  if (n_poses <= 32 && !whole) {
     hipLaunchKernelGGL(k_graph_scan<true>, dim3(1), dim3(1024), 0, s, atom_off, n_atoms, p0, n_poses, deg_scratch,
                        n_chunk_cap, pose_scratch, cov_row, cov_cap, nc_row, nc_cap, status);
   } else {
-    hipLaunchKernelGGL(k_graph_tot, dim3((n_poses + 3) / 4), dim3(kThreads), 0, s, atom_off, n_atoms, p0, n_poses,
-                       deg_scratch, n_chunk_cap, pose_scratch);
+    if (!whole)
+      hipLaunchKernelGGL(k_graph_tot, dim3((n_poses + 3) / 4), dim3(kThreads), 0, s, atom_off, n_atoms, p0, n_poses,
+                         deg_scratch, n_chunk_cap, pose_scratch);
     hipLaunchKernelGGL(k_graph_scan<false>, dim3(1), dim3(1024), 0, s, atom_off, n_atoms, p0, n_poses, deg_scratch,
                        n_chunk_cap, pose_scratch, cov_row, cov_cap, nc_row, nc_cap, status);
   }
