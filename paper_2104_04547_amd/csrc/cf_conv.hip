@@ -464,6 +464,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(Conv8Cf
   // Fine tiles run when few workgroups do, all in step and all missing L2 on the same
   // weights, a ring's depth per trip to memory.  So the first workgroups of an XCD each
   // touch a share of the next chunk's weights (one word per 128-byte line) a chunk ahead.
+  // Measured alone: one pose's score 390 us without, 378 with; 96 poses of the paper-sized
+  // model 1923 and 1914; 19 poses of 64^3 and 77 of 32^3 0.2 % apart.
   constexpr int kLinesPair = NT * 32 / 128, kLines = kLinesPair * C::PAIRS;
   constexpr int kWarm = 4;  // lines per thread at most
   const int wg = (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) / 8;
